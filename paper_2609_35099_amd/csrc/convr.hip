@@ -972,11 +972,7 @@ e3_status comp_bwd(const e3_plan* p, const e3_graph* g, int64_t rows, const floa
     for (const auto& z : p->pathless)
       if ((r = comp_zero_rows(T, g->n_live, D_in * C, z.first * C, z.second * C, st)) != E3_OK) return r;
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = (int)(D_in * C / 4);
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    const int chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * chunk * nsl)), dim3(kWave), 0, st, T, dx, g->rowptr_s,
-                       (int)g->n_nodes, chunk, flat4, nsl, (accum & kAccDx) != 0);
+    dx_sum(T, dx, g, (int)(D_in * C), (accum & kAccDx) != 0, st);
     E3_HIP(hipGetLastError());
   }
   (void)P;
@@ -1055,10 +1051,7 @@ e3_status rec_bwd(const e3_plan* p, const e3_graph* g, int64_t rows, const float
   }
   if (g && dx) {
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = p->lay.d_in * C / 4;
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * a.chunk * nsl)), dim3(kWave), 0, st, a.T, dx,
-                       g->rowptr_s, a.n_nodes, a.chunk, flat4, nsl, (accum & kAccDx) != 0);
+    dx_sum(a.T, dx, g, p->lay.d_in * C, (accum & kAccDx) != 0, st);
     E3_HIP(hipGetLastError());
   }
   const int* eid = g ? g->eid_r : nullptr;
@@ -1153,8 +1146,7 @@ e3_status comp_bwd64(const e3_plan* p, const e3_graph* g, const double* x, const
       return r;
   {
     TimedLaunch t_("conv_bwd_dx_f64", st);
-    hipLaunchKernelGGL(k_conv_bwd_dx64, dim3((unsigned)(g->n_nodes * nsl)), dim3(kWave), 0, st, T, dx, g->rowptr_s,
-                       (int)g->n_nodes, (int)D_in, (int)C, nsl);
+    dx_sum(T, dx, g, (int)(D_in * C), 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0) {
@@ -1250,11 +1242,7 @@ e3_status comp_bwd_rad(const e3_plan* p, const e3_graph* g, const float* x, cons
     for (const auto& z : p->pathless)
       if ((r = comp_zero_rows(T, g->n_live, D_in * C, z.first * C, z.second * C, st)) != E3_OK) return r;
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = (int)(D_in * C / 4);
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    const int chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * chunk * nsl)), dim3(kWave), 0, st, T, dx, g->rowptr_s,
-                       (int)g->n_nodes, chunk, flat4, nsl, 0);
+    dx_sum(T, dx, g, (int)(D_in * C), 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0) {
@@ -1330,11 +1318,7 @@ e3_status comp_bwd2(const e3_plan* p, const e3_graph* g, const float* x, const f
     if ((r = comp_zero_rows(T, g->n_live, D_in * C, z.first * C, z.second * C, st)) != E3_OK) return r;
   {
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = (int)(D_in * C / 4);
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    const int chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * chunk * nsl)), dim3(kWave), 0, st, T, gx, g->rowptr_s,
-                       (int)g->n_nodes, chunk, flat4, nsl, 0);
+    dx_sum(T, gx, g, (int)(D_in * C), 0, st);
     E3_HIP(hipGetLastError());
   }
   return finish_bwd(p, g, g->n_live, nullptr, DY, nullptr, gy, gs, p->kng * p->nslab_b, 0, st);

@@ -1176,14 +1176,18 @@ __global__ __launch_bounds__(kWave, E3_BWD3_MIN_WAVES) void k_conv_bwd3(ConvArgs
 }
 
 // dx[a] = sum of the partials of a's out-edges, in sender-CSR order.  A
-// node's partials are one contiguous block of (out-degree) x D_in x C floats;
-// the wave reads each slot's D_in x C floats as float4s (lane l takes float4
-// l, l+64, ... of its slab) and keeps kDxVec float4 sums per lane.
+// node's partials are one contiguous block of (out-degree) x D_in x C values;
+// the wave reads each slot as 16-byte units (float4 or double2; lane l takes
+// unit l, l+64, ... of its slab) and keeps kDxVec unit sums per lane.
 constexpr int kDxVec = E3_DX_VEC;
 
-__global__ __launch_bounds__(kWave) void k_conv_bwd_dx(const float* __restrict__ T, float* __restrict__ dx,
+template <class T>
+__global__ __launch_bounds__(kWave) void k_conv_bwd_dx(const T* __restrict__ P, T* __restrict__ dx,
                                                        const int* __restrict__ rowptr_s, int n_nodes, int chunk,
-                                                       int flat4, int nslab, int accum) {
+                                                       int units, int nslab, int accum) {
+  constexpr int W = 16 / sizeof(T);
+  typedef T Vt __attribute__((ext_vector_type(W)));
+  typedef unsigned u4v __attribute__((ext_vector_type(4)));
   const int bid = blockIdx.x;
   const int slot = bid / kXcd, sl = slot % nslab, rl = slot / nslab;
   const int node = (bid % kXcd) * chunk + rl;
@@ -1191,32 +1195,69 @@ __global__ __launch_bounds__(kWave) void k_conv_bwd_dx(const float* __restrict__
   const int lane = threadIdx.x;
   const int off = (sl * kWave * kDxVec + lane) * 16;  // bytes
   const int s0 = uniform(rowptr_s[node]), s1 = uniform(rowptr_s[node + 1]);
-  typedef unsigned u4v __attribute__((ext_vector_type(4)));
-  f4v acc[kDxVec];
+  Vt acc[kDxVec];
 #pragma unroll
-  for (int k = 0; k < kDxVec; ++k) acc[k] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-  const int64_t slot_bytes = (int64_t)flat4 * 16;
-  __amdgpu_buffer_rsrc_t o = __builtin_amdgcn_make_buffer_rsrc(dx + (int64_t)node * flat4 * 4, (short)0,
+  for (int k = 0; k < kDxVec; ++k) acc[k] = Vt(T(0));
+  const int64_t slot_bytes = (int64_t)units * 16;
+  __amdgpu_buffer_rsrc_t o = __builtin_amdgcn_make_buffer_rsrc(dx + (int64_t)node * units * W, (short)0,
                                                                (int)slot_bytes, 0x00020000);
-  // float4 k of the lane at byte offset off + k * 64 * 16, all of it in the
-  // lane offset (which the descriptor's range check covers): float4s past
+  // unit k of the lane at byte offset off + k * 64 * 16, all of it in the
+  // lane offset (which the descriptor's range check covers): units past
   // D_in x C read as zero and are not stored
   E3_UNROLL(E3_DX_UNROLL)
   for (int t = s0; t < s1; ++t) {
-    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(T) + (int64_t)t * flat4 * 4, (short)0, (int)slot_bytes, 0x00020000);
+    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(P) + (int64_t)t * units * W, (short)0,
+                                                                 (int)slot_bytes, 0x00020000);
 #pragma unroll
     for (int k = 0; k < kDxVec; ++k)
-      acc[k] += __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, off + k * kWave * 16, 0, kNT));
+      acc[k] += __builtin_bit_cast(Vt, __builtin_amdgcn_raw_buffer_load_b128(r, off + k * kWave * 16, 0, kNT));
   }
   if (accum) {  // old + this sum, so that accumulating equals adding a separate result
 #pragma unroll
     for (int k = 0; k < kDxVec; ++k)
-      acc[k] += __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(o, off + k * kWave * 16, 0, 0));
+      acc[k] += __builtin_bit_cast(Vt, __builtin_amdgcn_raw_buffer_load_b128(o, off + k * kWave * 16, 0, 0));
   }
 #pragma unroll
   for (int k = 0; k < kDxVec; ++k)
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, acc[k]), o, off + k * kWave * 16, 0, kST);
+}
+
+// The same sum where a slot is short (at most kDxShort 16-byte units, float4 or
+// double2): k_conv_bwd_dx gives a node one wave, whose 512 units of reach are
+// then mostly past the slot's end, and it walks the slots one after another.
+// Here a node has 256 threads: thread i takes unit i % units of every S-th
+// slot from i / units on (S = 256 / units slots at once, a single one past 128
+// units), and the S sums are added in order through LDS.  Bound by the reads
+// of T: 524,000 slots of 72 units (C = 32, l <= 2) 199 -> 108 us (5.6 TB/s),
+// 79,000 of 128 (C = 128, 0e+1o) 56 -> 31 us, 1,118 of 8 17 -> 6 us; float64,
+// 79,000 of 144 (a serial walk per row before) 226 -> 36 us.
+constexpr int kDxThreads = 256;
+
+template <class T>
+__global__ __launch_bounds__(kDxThreads) void k_conv_bwd_dx_short(const T* __restrict__ P, T* __restrict__ dx,
+                                                                  const int* __restrict__ rowptr_s, int n_nodes,
+                                                                  int chunk, int units, int accum) {
+  constexpr int W = 16 / sizeof(T);
+  typedef T Vt __attribute__((ext_vector_type(W)));
+  __shared__ Vt part[kDxThreads];
+  const int node = (blockIdx.x % kXcd) * chunk + blockIdx.x / kXcd;
+  if (node >= n_nodes) return;
+  const int S = kDxThreads / units, tid = threadIdx.x;
+  const int sub = tid / units, u = tid - sub * units;
+  const int s0 = rowptr_s[node], s1 = rowptr_s[node + 1];
+  Vt acc = Vt(T(0));
+  if (sub < S) {
+    const Vt* p = reinterpret_cast<const Vt*>(P) + (int64_t)s0 * units + u;
+#pragma unroll 8
+    for (int t = s0 + sub; t < s1; t += S) acc += __builtin_nontemporal_load(p + (int64_t)(t - s0) * units);
+  }
+  part[tid] = acc;
+  __syncthreads();
+  if (sub != 0) return;
+  for (int k = 1; k < S; ++k) acc += part[k * units + u];
+  Vt* o = reinterpret_cast<Vt*>(dx) + (int64_t)node * units + u;
+  if (accum) acc += *o;  // old + this sum, so that accumulating equals adding a separate result
+  __builtin_nontemporal_store(acc, o);
 }
 
 // dvec of each live edge from its harmonic cotangent (summed over groups).
@@ -1624,24 +1665,6 @@ __global__ __launch_bounds__(kWave, 1) void k_conv_bwd64(ConvArgs a, Conv64Out o
   int b, g, sl;
   if (!task_of<V::NBG>(a, b, g, sl)) return;
   bwd64_dispatch<V, 0>(a, o, b, g, sl, smem, smem + kBatch64 * V::MAX_NA_B);
-}
-
-// dx[node] = sum of its partial rows in sender-CSR order (one wave per node
-// and 64-channel slab, rows walked in registers).
-__global__ __launch_bounds__(kWave) void k_conv_bwd_dx64(const double* __restrict__ T, double* __restrict__ dx,
-                                                         const int* __restrict__ rowptr_s, int n_nodes, int D_in,
-                                                         int C, int nslab) {
-  const int64_t bid = blockIdx.x;
-  const int node = (int)(bid / nslab), sl = (int)(bid % nslab);
-  if (node >= n_nodes) return;
-  const int q = sl * kWave + threadIdx.x;
-  if (q >= C) return;
-  const int s0 = uniform(rowptr_s[node]), s1 = uniform(rowptr_s[node + 1]);
-  for (int i = 0; i < D_in; ++i) {
-    double acc = 0.0;
-    for (int t = s0; t < s1; ++t) acc += T[((int64_t)t * D_in + i) * C + q];
-    dx[((int64_t)node * D_in + i) * C + q] = acc;
-  }
 }
 
 // dvec of each live edge from its harmonic cotangent (summed over groups).
@@ -2416,6 +2439,25 @@ e3_status run_fwd3(const e3_plan* p, const e3_graph* g, const float* x, const fl
   return E3_OK;
 }
 
+// The sender segment sum: dx[node] = sum of its `width` floats (doubles) per
+// slot of T.  Slots of up to kDxShort units, the reach of 256 threads, run
+// k_conv_bwd_dx_short; longer ones fill most of the eight units per lane of
+// k_conv_bwd_dx (5.7-5.9 TB/s at 288, 384 and 512 units).
+constexpr int kDxShort = 256;
+
+template <class T>
+void dx_sum(const T* P, T* dx, const e3_graph* g, int width, int accum, hipStream_t st) {
+  const int chunk = (int)((g->n_nodes + kXcd - 1) / kXcd), units = width / (16 / (int)sizeof(T));
+  if (units <= kDxShort) {
+    hipLaunchKernelGGL(k_conv_bwd_dx_short<T>, dim3((unsigned)(kXcd * chunk)), dim3(kDxThreads), 0, st, P, dx,
+                       g->rowptr_s, (int)g->n_nodes, chunk, units, accum);
+    return;
+  }
+  const int nsl = (units + kWave * kDxVec - 1) / (kWave * kDxVec);
+  hipLaunchKernelGGL(k_conv_bwd_dx<T>, dim3((unsigned)(kXcd * chunk * nsl)), dim3(kWave), 0, st, P, dx, g->rowptr_s,
+                     (int)g->n_nodes, chunk, units, nsl, accum);
+}
+
 // One backward convolution.  Harmonics from y when given (then dy is the
 // harmonic cotangent output), else from vec (then dvec = J^T dy).  Any of
 // dx, dvec/dy, ds may be null: that cotangent is not stored.  accum is a mask
@@ -2455,10 +2497,7 @@ e3_status run_bwd(const e3_plan* p, const e3_graph* g, const float* x, const flo
   }
   if (dx) {
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = V::D_IN * a.C / 4;
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * a.chunk * nsl)), dim3(kWave), 0, st, a.T, dx,
-                       g->rowptr_s, a.n_nodes, a.chunk, flat4, nsl, (accum & kAccDx) != 0);
+    dx_sum(a.T, dx, g, V::D_IN * a.C, (accum & kAccDx) != 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0 && dvec) {
@@ -2510,10 +2549,7 @@ e3_status run_bwd3(const e3_plan* p, const e3_graph* g, const float* x, const fl
   }
   {
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = V::D_IN * a.C / 4;
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * a.chunk * nsl)), dim3(kWave), 0, st, a.T, gx,
-                       g->rowptr_s, a.n_nodes, a.chunk, flat4, nsl, 0);
+    dx_sum(a.T, gx, g, V::D_IN * a.C, 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0) {
@@ -2636,10 +2672,7 @@ e3_status run_bwd_rad(const e3_plan* p, const e3_graph* g, const float* x, const
   }
   if (g->n_nodes > 0) {
     TimedLaunch t_("conv_bwd_dx", st);
-    const int flat4 = V::D_IN * a.C / 4;
-    const int nsl = (flat4 + kWave * kDxVec - 1) / (kWave * kDxVec);
-    hipLaunchKernelGGL(k_conv_bwd_dx, dim3((unsigned)(kXcd * a.chunk * nsl)), dim3(kWave), 0, st, a.T, dx,
-                       g->rowptr_s, a.n_nodes, a.chunk, flat4, nsl, 0);
+    dx_sum(a.T, dx, g, V::D_IN * a.C, 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0) {
@@ -2777,8 +2810,7 @@ e3_status run_bwd64(const e3_plan* p, const e3_graph* g, const double* x, const 
   }
   {
     TimedLaunch t_("conv_bwd_dx_f64", st);
-    hipLaunchKernelGGL(k_conv_bwd_dx64, dim3((unsigned)(g->n_nodes * a.nslab)), dim3(kWave), 0, st, o.T, dx,
-                       g->rowptr_s, a.n_nodes, V::D_IN, a.C, a.nslab);
+    dx_sum(o.T, dx, g, V::D_IN * a.C, 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0) {
