@@ -343,35 +343,59 @@ __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 
+// The same for doubles, on both halves.
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, (uint64_t)h[0] << 32 | l[0]);
+  b = __builtin_bit_cast(double, (uint64_t)h[1] << 32 | l[1]);
+}
+__device__ __forceinline__ void swap16(double& a, double& b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, (uint64_t)h[0] << 32 | l[0]);
+  b = __builtin_bit_cast(double, (uint64_t)h[1] << 32 | l[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, v);
+  const unsigned l = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const unsigned h = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)h << 32 | l);
+}
+
 // Sum of v[16] over the 64 lanes of the wave by a fixed tree (transposed
 // halving: each stage keeps half of the values and exchanges the other half,
 // on lane bits 5, 4, 3, then 2 paired by the half-row mirror, then a quad
 // sum; bk below is bit k of the lane); lane l ends with the total of index
 // l / 4.
-__device__ __forceinline__ float wave_reduce16(const float (&v)[16], int lane) {
-  float w8[8], w4[4], w2[2];
+template <class T>
+__device__ __forceinline__ T wave_reduce16(const T (&v)[16], int lane) {
+  T w8[8], w4[4], w2[2];
   const bool b3 = lane & 8, b2 = lane & 4;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {  // index i + 8 b5, summed over lane bit 5
-    float a = v[i], b = v[i + 8];
+    T a = v[i], b = v[i + 8];
     swap32(a, b);
     w8[i] = a + b;
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {  // index i + 4 b4 + 8 b5, summed over bits 4, 5
-    float a = w8[i], b = w8[i + 4];
+    T a = w8[i], b = w8[i + 4];
     swap16(a, b);
     w4[i] = a + b;
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {  // index i + 2 b3 + 4 b4 + 8 b5, summed over bits 3..5
-    const float send = b3 ? w4[i] : w4[i + 2];
-    const float keep = b3 ? w4[i + 2] : w4[i];
+    const T send = b3 ? w4[i] : w4[i + 2];
+    const T keep = b3 ? w4[i + 2] : w4[i];
     w2[i] = keep + dpp<kDppXor8>(send);
   }
   // index l / 4; the partner l ^ 7 has the same bits 3..5 and the other bit 2,
   // and the quad sum then covers all eight values of the low three bits
-  float w1 = (b2 ? w2[1] : w2[0]) + dpp<kDppXor7>(b2 ? w2[0] : w2[1]);
+  T w1 = (b2 ? w2[1] : w2[0]) + dpp<kDppXor7>(b2 ? w2[0] : w2[1]);
   w1 += dpp<kDppXor1>(w1);
   w1 += dpp<kDppXor2>(w1);
   return w1;
@@ -1344,13 +1368,6 @@ __device__ __forceinline__ void bst64(const RowBuf64& b, int row, const double (
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, v[0]), b.r, b.voff, row * b.rowbytes, 0);
 }
 
-// Sum over the 64 lanes, the same fixed butterfly on every lane.
-__device__ __forceinline__ double wave_sum64(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
-  return v;
-}
-
 __device__ __forceinline__ void unit_of64(const double* __restrict__ vec, int64_t e, double& ux, double& uy,
                                           double& uz, double& inv) {
   const double vx = vec[3 * e], vy = vec[3 * e + 1], vz = vec[3 * e + 2];
@@ -1435,9 +1452,9 @@ __device__ __forceinline__ void tpb64_task(const Tpb64Args& a, int64_t r0, int s
   __syncthreads();
   for (int j = 0; j < n; ++j) {
     const int64_t r = r0 + j;
-    double dyl[V::D_SH];
+    double dy[16];
 #pragma unroll
-    for (int i = 0; i < V::D_SH; ++i) dyl[i] = 0.0;
+    for (int i = 0; i < 16; ++i) dy[i] = 0.0;
     if (act) {
       const RowBuf64 xb = row_buf64(a.x + r * x_rows<V>(a) * C, (int64_t)V::D_IN * C * 8, q, C);
       const RowBuf64 wb = row_buf64(a.w + r * p_rows<V>(a) * C, (int64_t)V::NP * C * 8, q, C);
@@ -1453,16 +1470,18 @@ __device__ __forceinline__ void tpb64_task(const Tpb64Args& a, int64_t r0, int s
       for (int i = 0; i < V::D_SH; ++i) Yv[i] = sY[j * V::D_SH + i];
       const RowBuf64 dwb = row_buf64(a.dw + r * p_rows<V>(a) * C, (int64_t)V::NP * C * 8, q, C);
       auto st = [&](int pl, const double (&v)[1]) { bst64(dwb, B::PATH[pl], v); };
+      double dyl[V::D_SH];
+#pragma unroll
+      for (int i = 0; i < V::D_SH; ++i) dyl[i] = 0.0;
       B::template edge<false, 1>(sA + j * B::NA, Yv, xv, wv, dzv, t, dyl, st);
+#pragma unroll
+      for (int i = 0; i < V::D_SH; ++i) dy[i] = dyl[i];
       const RowBuf64 dxb = row_buf64(a.dx + r * x_rows<V>(a) * C, (int64_t)V::D_IN * C * 8, q, C);
 #pragma unroll
       for (int i = 0; i < B::NXR; ++i) bst64(dxb, B::XROW[i], t[i]);
     }
-#pragma unroll
-    for (int i = 0; i < V::D_SH; ++i) {
-      const double tot = wave_sum64(dyl[i]);
-      if (lane == 0) a.DY[(dy_group<V, G>(a, r) * a.nslab + sl) * 16 + i] = tot;
-    }
+    const double tot = wave_reduce16(dy, lane);
+    if ((lane & 3) == 0) a.DY[(dy_group<V, G>(a, r) * a.nslab + sl) * 16 + (lane >> 2)] = tot;
   }
 }
 
@@ -1499,172 +1518,366 @@ __global__ __launch_bounds__(256) void k_dy_sum64(const double* __restrict__ DY,
   dy[(eid ? (int64_t)eid[r] : r) * V::D_SH + c] = v;
 }
 
-// Convolution forward: one wave per (receiver, forward group, slab); the
-// receiver's sums in registers, stored once.
-template <class V, int G>
-__device__ __forceinline__ void fwd64_task(const ConvArgs& a, const double* x, const double* vec, const double* s,
-                                           double* m, int b, int sl, double* sA) {
-  using F = typename V::template FG<G>;
-  const int lane = threadIdx.x;
-  int ch0, lanes;
-  slab_of<1>(a.C, sl, ch0, lanes);
-  const bool act = lane < lanes;
-  const int C = a.C, q = ch0 + lane;
-  const int e0 = uniform(a.rowptr[b]), e1 = uniform(a.rowptr[b + 1]);
-  double acc[F::NROW][1];
+// ------------------------------------------------------------ sub-wave sweeps
+// The convolution sweeps with 2^lgl lanes per edge instead of a whole wave, so
+// that a wave of few channels works on 64 / 2^lgl edges of its receiver at
+// once: the float32 sweeps of narrow layouts (C <= 32; above, k_conv_fwd and
+// k_conv_bwd_edges) and the float64 ones (any C; 64 lanes per edge from 33
+// channels on).  A narrow edge row is at most 128 bytes, so the whole-wave
+// sweeps left half to 15/16 of the lanes idle and were held by the serial
+// chain of edges; here a step's row loads fetch 64 / 2^lgl rows each, and the
+// forward's sums of the sub-waves are added once per receiver.  One channel
+// per lane.  Rows are addressed with a 32-bit lane offset from the tensor's
+// start, so sub-waves need every tensor below kSubMaxBytes; a float64 tensor
+// beyond it runs with whole waves (wide: a descriptor per edge).
+constexpr unsigned kSubMaxBytes = 0xf0000000u;  // below kSubOff
+constexpr unsigned kSubOff = 0xfffffff0u;       // lane offset past every descriptor: reads zero, stores dropped
+
+template <class T>
+struct SubArgs {
+  const T *x, *vec, *y, *s, *dm;
+  T *m, *ds, *P, *DY;
+  const int *rowptr, *eid, *src, *r2s;
+  int n_nodes, chunk, C, nslab;
+  int lgl;    // log2 of the lanes per edge, 3..6 (6: one edge per wave)
+  int wide;   // -1: one edge per wave, descriptors based at the edge's rows; else 0
+  int fb;     // edges per staged batch, a multiple of the edges per step
+  int accum;  // forward: add to m instead of overwriting it
+  unsigned xn, sn, dsn, tn;  // descriptor sizes of x, s, ds, P (0: that output is not wanted, its stores are dropped)
+  int xr, pr, orr, ng, g0;   // as in ConvArgs
+};
+
+template <class T>
+struct SubRow {
+  __amdgpu_buffer_rsrc_t r;
+  unsigned voff;
+  int rowbytes;
+};
+
+// Rows of `stride` elements per index at `base`; `at` is the lane's index and
+// must be wave-uniform when wide.
+template <class T>
+__device__ __forceinline__ SubRow<T> sub_row(const T* base, unsigned nbytes, int at, int stride, int q, bool on, int C,
+                                             int wide) {
+  SubRow<T> b;
+  // masks, not selects: a selected base would not be known to be uniform
+  const T* p = base + (int64_t)(uniform(at) & wide) * stride;
+  b.r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), (short)0, (int)nbytes, 0x00020000);
+  b.voff = on ? ((unsigned)(at & ~wide) * (unsigned)stride + (unsigned)q) * (unsigned)sizeof(T) : kSubOff;
+  b.rowbytes = C * (int)sizeof(T);
+  return b;
+}
+
+template <int AUX = 0, class T>
+__device__ __forceinline__ void sld(const SubRow<T>& b, int row, T (&v)[1]) {
+  if constexpr (sizeof(T) == 4)
+    v[0] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.voff, row * b.rowbytes, AUX));
+  else
+    v[0] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b.r, (int)b.voff, row * b.rowbytes, AUX));
+}
+template <int AUX = 0, class T>
+__device__ __forceinline__ void sst(const SubRow<T>& b, int row, const T (&v)[1]) {
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  if constexpr (sizeof(T) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v[0]), b.r, (int)b.voff, row * b.rowbytes, AUX);
+  else
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, v[0]), b.r, (int)b.voff, row * b.rowbytes, AUX);
+}
+
+// One halving step of a transposed reduction: the lane keeps the half of v
+// that bit b of its lane number selects and adds the partner's copy of it.
+template <int CTRL, int N, class T>
+__device__ __forceinline__ void halve(const T (&v)[N], T (&o)[N / 2], bool b) {
 #pragma unroll
-  for (int i = 0; i < F::NROW; ++i) acc[i][0] = 0.0;
-  for (int eb = e0; eb < e1; eb += kBatch64) {
-    const int n = imin(kBatch64, e1 - eb);
+  for (int i = 0; i < N / 2; ++i) o[i] = (b ? v[i + N / 2] : v[i]) + dpp<CTRL>(b ? v[i] : v[i + N / 2]);
+}
+
+// Sums v[16] over each sub-wave of 2^lgl lanes by a fixed tree and stores the
+// totals at out[0..15] (out is the lane's own edge's; not stored when !on).
+// The lane ^ 7 partner of the second step keeps bits 1 and 0 mixed until the
+// two steps after it.
+template <class T>
+__device__ __forceinline__ void sub_reduce16_store(const T (&v)[16], int lane, int lgl, T* out, bool on) {
+  const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
+  if (lgl == 3) {
+    T w8[8], w4[4], w2[2];
+    halve<kDppXor7>(v, w8, b2);
+    halve<kDppXor2>(w8, w4, b1);
+    halve<kDppXor1>(w4, w2, b0);
+    const int i = 2 * (int)b0 + 4 * (int)b1 + 8 * (int)b2;
+    if (on) out[i] = w2[0], out[i + 1] = w2[1];
+    return;
+  }
+  T w8[8], w4[4], w2[2], w1[1];
+  halve<kDppXor8>(v, w8, b3);
+  halve<kDppXor7>(w8, w4, b2);
+  halve<kDppXor2>(w4, w2, b1);
+  halve<kDppXor1>(w2, w1, b0);
+  T tot = w1[0];
+  if (lgl >= 5) {
+    T a = tot, b = tot;
+    swap16(a, b);
+    tot = a + b;
+  }
+  if (lgl == 6) {
+    T a = tot, b = tot;
+    swap32(a, b);
+    tot = a + b;
+  }
+  if (on && (lane & ((1 << lgl) - 1)) < 16) out[(int)b0 + 2 * (int)b1 + 4 * (int)b2 + 8 * (int)b3] = tot;
+}
+
+// Harmonics of edge e in either precision.
+template <class V>
+__device__ __forceinline__ void sub_harmonics(const SubArgs<float>& a, int64_t e, float (&Y)[V::D_SH]) {
+  if (a.y) {
+#pragma unroll
+    for (int i = 0; i < V::D_SH; ++i) Y[i] = a.y[e * V::D_SH + i];
+  } else {
+    float ux, uy, uz, inv;
+    unit_of(a.vec, e, ux, uy, uz, inv);
+    V::sh(ux, uy, uz, Y);
+  }
+}
+template <class V>
+__device__ __forceinline__ void sub_harmonics(const SubArgs<double>& a, int64_t e, double (&Y)[V::D_SH]) {
+  double ux, uy, uz, inv;
+  unit_of64(a.vec, e, ux, uy, uz, inv);
+  V::sh(ux, uy, uz, Y);
+}
+
+template <int NG, class T>
+__device__ __forceinline__ bool sub_task_of(const SubArgs<T>& a, int& b, int& g, int& sl) {
+  const int xcd = blockIdx.x % kXcd, slot = blockIdx.x / kXcd, per = NG * a.nslab, t = slot % per;
+  g = t / a.nslab, sl = t % a.nslab;
+  const int rl = slot / per;
+  b = xcd * a.chunk + rl;
+  return rl < a.chunk && b < a.n_nodes;
+}
+
+template <class V, int G, class T>
+__device__ __forceinline__ void sub_fwd_task(const SubArgs<T>& a, int b, int sl, T* sA) {
+  using F = typename V::template FG<G>;
+  const int lane = threadIdx.x, lgl = a.lgl, S = kWave >> lgl, sub = lane >> lgl;
+  const int C = a.C, q = sl * kWave + (lane & ((1 << lgl) - 1));
+  const bool act = q < C;
+  const int e0 = uniform(a.rowptr[b]), e1 = uniform(a.rowptr[b + 1]);
+  T acc[F::NROW][1];
+#pragma unroll
+  for (int i = 0; i < F::NROW; ++i) acc[i][0] = T(0);
+  for (int eb = e0; eb < e1; eb += a.fb) {
+    const int n = imin(a.fb, e1 - eb), nr = (n + S - 1) & ~(S - 1);
     int my_e = 0, my_src = 0;
-    if (lane < n) {
-      my_e = a.eid[eb + lane];
-      my_src = a.src[eb + lane];
-      double ux, uy, uz, inv, Y[V::D_SH];
-      unit_of64(vec, my_e, ux, uy, uz, inv);
-      V::sh(ux, uy, uz, Y);
+    if (lane < nr) {  // edges past the end stage a zero pre-contraction
+      T Y[V::D_SH];
+#pragma unroll
+      for (int i = 0; i < V::D_SH; ++i) Y[i] = T(0);
+      if (lane < n) {
+        my_e = a.eid[eb + lane];
+        my_src = a.src[eb + lane];
+        sub_harmonics<V>(a, my_e, Y);
+      }
       F::make_A(Y, sA + lane * F::NA);
     }
     __syncthreads();
-    if (act) {
-      for (int j = 0; j < n; ++j) {
-        const int64_t e = __builtin_amdgcn_readlane(my_e, j);
-        const int64_t snd = __builtin_amdgcn_readlane(my_src, j);
-        const RowBuf64 xb = row_buf64(x + snd * x_rows<V>(a) * C, (int64_t)V::D_IN * C * 8, q, C);
-        const RowBuf64 sb = row_buf64(s + e * p_rows<V>(a) * C, (int64_t)V::NP * C * 8, q, C);
-        double xv[F::NXR][1], sv[F::NPATH][1];
+    T xa[F::NXR][1], sa[F::NPATH][1], xb[F::NXR][1], sb[F::NPATH][1];
+    auto load = [&](int j, T (&xv)[F::NXR][1], T (&sv)[F::NPATH][1]) {
+      const int je = j + sub;
+      const bool on = act && je < n;
+      const SubRow<T> xr = sub_row(a.x, a.xn, __shfl(my_src, je, kWave), x_rows<V>(a) * C, q, on, C, a.wide);
+      const SubRow<T> sr = sub_row(a.s, a.sn, __shfl(my_e, je, kWave), p_rows<V>(a) * C, q, on, C, a.wide);
 #pragma unroll
-        for (int i = 0; i < F::NXR; ++i) bld64(xb, F::XROW[i], xv[i]);
+      for (int i = 0; i < F::NXR; ++i) sld(xr, F::XROW[i], xv[i]);
 #pragma unroll
-        for (int i = 0; i < F::NPATH; ++i) bld64(sb, F::PATH[i], sv[i]);
-        F::template edge<1>(sA + j * F::NA, xv, sv, acc);
+      for (int i = 0; i < F::NPATH; ++i) sld<kNT>(sr, F::PATH[i], sv[i]);
+    };
+    load(0, xa, sa);
+    for (int j = 0; j < nr; j += 2 * S) {
+      if (j + S < nr) load(j + S, xb, sb);
+      F::template edge<1>(sA + (j + sub) * F::NA, xa, sa, acc);
+      if (j + S < nr) {
+        if (j + 2 * S < nr) load(j + 2 * S, xa, sa);
+        F::template edge<1>(sA + (j + S + sub) * F::NA, xb, sb, acc);
       }
     }
     __syncthreads();
   }
-  if (act) {
-    const RowBuf64 mb = row_buf64(m + (int64_t)b * o_rows<V>(a) * C, (int64_t)V::D_OUT * C * 8, q, C);
+  // the sub-waves' sums, added pairwise
+  if (lgl <= 3) {
 #pragma unroll
-    for (int i = 0; i < F::NROW; ++i) bst64(mb, F::OROW[i], acc[i]);
+    for (int i = 0; i < F::NROW; ++i) acc[i][0] += dpp<kDppXor8>(acc[i][0]);
   }
+  if (lgl <= 4) {
+#pragma unroll
+    for (int i = 0; i < F::NROW; ++i) {
+      T u = acc[i][0], v = u;
+      swap16(u, v);
+      acc[i][0] = u + v;
+    }
+  }
+  if (lgl <= 5) {
+#pragma unroll
+    for (int i = 0; i < F::NROW; ++i) {
+      T u = acc[i][0], v = u;
+      swap32(u, v);
+      acc[i][0] = u + v;
+    }
+  }
+  SubRow<T> mb;
+  mb.r = __builtin_amdgcn_make_buffer_rsrc(a.m + (int64_t)b * o_rows<V>(a) * C, (short)0,
+                                           V::D_OUT * C * (int)sizeof(T), 0x00020000);
+  mb.voff = act && sub == 0 ? (unsigned)q * (unsigned)sizeof(T) : kSubOff;
+  mb.rowbytes = C * (int)sizeof(T);
+  if (a.accum) {
+#pragma unroll
+    for (int i = 0; i < F::NROW; ++i) {
+      T o[1];
+      sld(mb, F::OROW[i], o);
+      acc[i][0] += o[0];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < F::NROW; ++i) sst<kST>(mb, F::OROW[i], acc[i]);
 }
 
-template <class V, int G>
-__device__ __forceinline__ void fwd64_dispatch(const ConvArgs& a, const double* x, const double* vec,
-                                               const double* s, double* m, int b, int g, int sl, double* sA) {
+template <class V, int G, class T>
+__device__ __forceinline__ void sub_fwd_dispatch(const SubArgs<T>& a, int b, int g, int sl, T* sA) {
   if constexpr (G < V::NFG) {
     if (g == G)
-      fwd64_task<V, G>(a, x, vec, s, m, b, sl, sA);
+      sub_fwd_task<V, G, T>(a, b, sl, sA);
     else
-      fwd64_dispatch<V, G + 1>(a, x, vec, s, m, b, g, sl, sA);
+      sub_fwd_dispatch<V, G + 1, T>(a, b, g, sl, sA);
   }
 }
 
-template <class V>
-__global__ __launch_bounds__(kWave, 1) void k_conv_fwd64(ConvArgs a, const double* __restrict__ x,
-                                                         const double* __restrict__ vec,
-                                                         const double* __restrict__ s, double* __restrict__ m) {
-  __shared__ __align__(32) double sA[kBatch64 * V::MAX_NA_F];
+constexpr int sub_min_waves(size_t elem) { return elem == 4 ? 2 : 1; }
+
+// dynamic LDS: fb * V::MAX_NA_F values
+template <class V, class T>
+__global__ __launch_bounds__(kWave, sub_min_waves(sizeof(T))) void k_conv_fwd_sub(SubArgs<T> a) {
+  extern __shared__ __align__(32) unsigned char sub_lds[];
   int b, g, sl;
-  if (!task_of<V::NFG>(a, b, g, sl)) return;
-  fwd64_dispatch<V, 0>(a, x, vec, s, m, b, g, sl, sA);
+  if (!sub_task_of<V::NFG>(a, b, g, sl)) return;
+  sub_fwd_dispatch<V, 0, T>(a, b, g, sl, reinterpret_cast<T*>(sub_lds));
 }
 
-// Convolution backward sweep in receiver order: ds per edge, the x-cotangent
-// partials T at the edge's sender-CSR slot, the per-wave harmonic cotangents.
-struct Conv64Out {
-  const double* x;
-  const double* vec;
-  const double* s;
-  const double* dm;
-  double* ds;
-  double* T;   // [n_live, D_in, C]
-  double* DY;  // [n_live, NBG * nslab, 16]
-};
-
-template <class V, int G>
-__device__ __forceinline__ void bwd64_task(const ConvArgs& a, const Conv64Out& o, int b, int sl, double* sA,
-                                           double* sY) {
+// Backward sweep in receiver order: ds per edge, the x-cotangent partials P at
+// the edge's sender-CSR slot, the harmonic cotangent partials.  ACC: ds += the
+// result; the old rows are loaded before the contraction (as in bwd_task).
+template <class V, int G, class T, bool ACC>
+__device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl, T* sA, T* sY) {
   using B = typename V::template BG<G>;
-  const int lane = threadIdx.x;
-  int ch0, lanes;
-  slab_of<1>(a.C, sl, ch0, lanes);
-  const bool act = lane < lanes;
-  const int C = a.C, q = ch0 + lane;
+  const int lane = threadIdx.x, lgl = a.lgl, S = kWave >> lgl, sub = lane >> lgl;
+  const int C = a.C, q = sl * kWave + (lane & ((1 << lgl) - 1));
+  const bool act = q < C;
   const int e0 = uniform(a.rowptr[b]), e1 = uniform(a.rowptr[b + 1]);
   if (e0 == e1) return;
-  double dmv[B::NROW][1];
-  if (act) {
-    const RowBuf64 db = row_buf64(o.dm + (int64_t)b * o_rows<V>(a) * C, (int64_t)V::D_OUT * C * 8, q, C);
+  T dmv[B::NROW][1];
+  {
+    SubRow<T> db;
+    db.r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(a.dm) + (int64_t)b * o_rows<V>(a) * C, (short)0,
+                                             V::D_OUT * C * (int)sizeof(T), 0x00020000);
+    db.voff = act ? (unsigned)q * (unsigned)sizeof(T) : kSubOff;
+    db.rowbytes = C * (int)sizeof(T);
 #pragma unroll
-    for (int i = 0; i < B::NROW; ++i) bld64(db, B::OROW[i], dmv[i]);
+    for (int i = 0; i < B::NROW; ++i) sld(db, B::OROW[i], dmv[i]);
   }
-  for (int eb = e0; eb < e1; eb += kBatch64) {
-    const int n = imin(kBatch64, e1 - eb);
+  for (int eb = e0; eb < e1; eb += a.fb) {
+    const int n = imin(a.fb, e1 - eb), nr = (n + S - 1) & ~(S - 1);
     int my_e = 0, my_src = 0, my_slot = 0;
-    if (lane < n) {
-      my_e = a.eid[eb + lane];
-      my_src = a.src[eb + lane];
-      my_slot = a.r2s[eb + lane];
-      double ux, uy, uz, inv, Y[V::D_SH];
-      unit_of64(o.vec, my_e, ux, uy, uz, inv);
-      V::sh(ux, uy, uz, Y);
+    if (lane < nr) {
+      T Y[V::D_SH];
+#pragma unroll
+      for (int i = 0; i < V::D_SH; ++i) Y[i] = T(0);
+      if (lane < n) {
+        my_e = a.eid[eb + lane];
+        my_src = a.src[eb + lane];
+        my_slot = a.r2s[eb + lane];
+        sub_harmonics<V>(a, my_e, Y);
+      }
 #pragma unroll
       for (int i = 0; i < V::D_SH; ++i) sY[lane * V::D_SH + i] = Y[i];
       B::make_A(Y, sA + lane * B::NA);
     }
     __syncthreads();
-    for (int j = 0; j < n; ++j) {
-      const int64_t e = __builtin_amdgcn_readlane(my_e, j);
-      const int64_t snd = __builtin_amdgcn_readlane(my_src, j);
-      const int64_t slot = __builtin_amdgcn_readlane(my_slot, j);
-      double dyl[V::D_SH];
+    T xa[B::NXR][1], sa[B::NPATH][1], xb[B::NXR][1], sb[B::NPATH][1];
+    auto load = [&](int j, T (&xv)[B::NXR][1], T (&sv)[B::NPATH][1]) {
+      const int je = j + sub;
+      const bool on = act && je < n;
+      const SubRow<T> xr = sub_row(a.x, a.xn, __shfl(my_src, je, kWave), x_rows<V>(a) * C, q, on, C, a.wide);
+      const SubRow<T> sr = sub_row(a.s, a.sn, __shfl(my_e, je, kWave), p_rows<V>(a) * C, q, on, C, a.wide);
 #pragma unroll
-      for (int i = 0; i < V::D_SH; ++i) dyl[i] = 0.0;
-      if (act) {
-        const RowBuf64 xb = row_buf64(o.x + snd * x_rows<V>(a) * C, (int64_t)V::D_IN * C * 8, q, C);
-        const RowBuf64 sb = row_buf64(o.s + e * p_rows<V>(a) * C, (int64_t)V::NP * C * 8, q, C);
-        double xv[B::NXR][1], sv[B::NPATH][1], t[B::NXR][1], Yv[V::D_SH];
+      for (int i = 0; i < B::NXR; ++i) sld(xr, B::XROW[i], xv[i]);
 #pragma unroll
-        for (int i = 0; i < B::NXR; ++i) bld64(xb, B::XROW[i], xv[i]), t[i][0] = 0.0;
+      for (int i = 0; i < B::NPATH; ++i) sld<kNT>(sr, B::PATH[i], sv[i]);
+    };
+    auto compute = [&](int j, const T (&xv)[B::NXR][1], const T (&sv)[B::NPATH][1]) {
+      const int je = j + sub;
+      const bool on = act && je < n;
+      T dy[16];
 #pragma unroll
-        for (int i = 0; i < B::NPATH; ++i) bld64(sb, B::PATH[i], sv[i]);
+      for (int i = 0; i < 16; ++i) dy[i] = T(0);
+      const int e = __shfl(my_e, je, kWave), slot = __shfl(my_slot, je, kWave);
+      if (on) {
+        T t[B::NXR][1], Yv[V::D_SH], dyl[V::D_SH];
 #pragma unroll
-        for (int i = 0; i < V::D_SH; ++i) Yv[i] = sY[j * V::D_SH + i];
-        const RowBuf64 dsb = row_buf64(o.ds + e * p_rows<V>(a) * C, (int64_t)V::NP * C * 8, q, C);
-        auto st = [&](int pl, const double (&v)[1]) { bst64(dsb, B::PATH[pl], v); };
-        B::template edge<false, 1>(sA + j * B::NA, Yv, xv, sv, dmv, t, dyl, st);
-        const RowBuf64 Tb = row_buf64(o.T + slot * x_rows<V>(a) * C, (int64_t)V::D_IN * C * 8, q, C);
+        for (int i = 0; i < B::NXR; ++i) t[i][0] = T(0);
 #pragma unroll
-        for (int i = 0; i < B::NXR; ++i) bst64(Tb, B::XROW[i], t[i]);
+        for (int i = 0; i < V::D_SH; ++i) Yv[i] = sY[je * V::D_SH + i], dyl[i] = T(0);
+        const SubRow<T> dsr = sub_row(a.ds, a.dsn, e, p_rows<V>(a) * C, q, true, C, a.wide);
+        T old[ACC ? B::NPATH : 1][1];
+        if constexpr (ACC) {
+#pragma unroll
+          for (int i = 0; i < B::NPATH; ++i) sld(dsr, B::PATH[i], old[i]);
+        }
+        auto st = [&](int pl, const T (&v)[1]) {
+          if constexpr (ACC) {
+            const T o[1] = {old[pl][0] + v[0]};
+            sst<kST>(dsr, B::PATH[pl], o);
+          } else {
+            sst<kST>(dsr, B::PATH[pl], v);
+          }
+        };
+        B::template edge<E3_BWD_ALOAD_PIN != 0, 1>(sA + je * B::NA, Yv, xv, sv, dmv, t, dyl, st);
+        const SubRow<T> tr = sub_row(a.P, a.tn, slot, x_rows<V>(a) * C, q, true, C, a.wide);
+#pragma unroll
+        for (int i = 0; i < B::NXR; ++i) sst<E3_T_STORE_AUX>(tr, B::XROW[i], t[i]);
+#pragma unroll
+        for (int i = 0; i < V::D_SH; ++i) dy[i] = dyl[i];
       }
-#pragma unroll
-      for (int i = 0; i < V::D_SH; ++i) {
-        const double tot = wave_sum64(dyl[i]);
-        if (lane == 0) o.DY[(dy_group<V, G>(a, eb + j) * a.nslab + sl) * 16 + i] = tot;
+      sub_reduce16_store(dy, lane, lgl, a.DY + (dy_group<V, G>(a, eb + je) * a.nslab + sl) * 16, je < n);
+    };
+    load(0, xa, sa);
+    for (int j = 0; j < nr; j += 2 * S) {
+      if (j + S < nr) load(j + S, xb, sb);
+      compute(j, xa, sa);
+      if (j + S < nr) {
+        if (j + 2 * S < nr) load(j + 2 * S, xa, sa);
+        compute(j + S, xb, sb);
       }
     }
     __syncthreads();
   }
 }
 
-template <class V, int G>
-__device__ __forceinline__ void bwd64_dispatch(const ConvArgs& a, const Conv64Out& o, int b, int g, int sl,
-                                               double* sA, double* sY) {
+template <class V, int G, class T, bool ACC>
+__device__ __forceinline__ void sub_bwd_dispatch(const SubArgs<T>& a, int b, int g, int sl, T* sA, T* sY) {
   if constexpr (G < V::NBG) {
     if (g == G)
-      bwd64_task<V, G>(a, o, b, sl, sA, sY);
+      sub_bwd_task<V, G, T, ACC>(a, b, sl, sA, sY);
     else
-      bwd64_dispatch<V, G + 1>(a, o, b, g, sl, sA, sY);
+      sub_bwd_dispatch<V, G + 1, T, ACC>(a, b, g, sl, sA, sY);
   }
 }
 
-template <class V>
-__global__ __launch_bounds__(kWave, 1) void k_conv_bwd64(ConvArgs a, Conv64Out o) {
-  __shared__ __align__(32) double smem[kBatch64 * (V::MAX_NA_B + V::D_SH)];
+// dynamic LDS: fb * (V::MAX_NA_B + V::D_SH) values
+template <class V, class T, bool ACC>
+__global__ __launch_bounds__(kWave, sub_min_waves(sizeof(T))) void k_conv_bwd_sub(SubArgs<T> a) {
+  extern __shared__ __align__(32) unsigned char sub_lds[];
   int b, g, sl;
-  if (!task_of<V::NBG>(a, b, g, sl)) return;
-  bwd64_dispatch<V, 0>(a, o, b, g, sl, smem, smem + kBatch64 * V::MAX_NA_B);
+  if (!sub_task_of<V::NBG>(a, b, g, sl)) return;
+  T* sA = reinterpret_cast<T*>(sub_lds);
+  sub_bwd_dispatch<V, 0, T, ACC>(a, b, g, sl, sA, sA + a.fb * V::MAX_NA_B);
 }
 
 // dvec of each live edge from its harmonic cotangent (summed over groups).
@@ -2390,15 +2603,79 @@ ConvArgs base_args(const e3_plan* p, const e3_graph* g) {
   return a;
 }
 
+// ---- sub-wave sweeps
+// The float32 sweeps of layouts with C <= 32 run on sub-waves when every
+// tensor fits a 32-bit lane offset; the float64 sweeps always run that kernel,
+// with whole waves for C > 32 or larger tensors.
+inline bool sub_fits(const e3_graph* g, int64_t xr, int64_t pr, int64_t C, int64_t elem) {
+  const int64_t rows = std::max(std::max(g->n_nodes, g->n_live) * xr, g->n_edges * pr);
+  return rows * C * elem <= (int64_t)kSubMaxBytes;
+}
+
+// xr, pr, orr, ng, g0: of the whole layout (as in KindCall); V: the layout or
+// the single-block kind whose rows are swept.
+template <class V, class T>
+SubArgs<T> sub_args(const e3_plan* p, const e3_graph* g, int xr, int pr, int orr, int ng, int g0) {
+  SubArgs<T> a{};
+  a.rowptr = g->rowptr_r, a.eid = g->eid_r, a.src = g->src_r, a.r2s = g->r2s;
+  a.n_nodes = (int)g->n_nodes;
+  a.chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
+  a.C = p->lay.C;
+  a.nslab = (a.C + kWave - 1) / kWave;
+  const int64_t row = (int64_t)a.C * sizeof(T);
+  a.wide = sub_fits(g, xr, pr, a.C, sizeof(T)) ? 0 : -1;
+  a.lgl = a.wide || a.C > 32 ? 6 : a.C > 16 ? 5 : a.C > 8 ? 4 : 3;
+  a.fb = a.lgl >= 5 ? 16 : 32;
+  auto bytes = [&](int64_t n, int64_t stride, int64_t rows) {
+    return (unsigned)(a.wide ? rows * row : n > 0 ? ((n - 1) * stride + rows) * row : 0);
+  };
+  a.xn = bytes(g->n_nodes, xr, V::D_IN), a.sn = bytes(g->n_edges, pr, V::NP), a.tn = bytes(g->n_live, xr, V::D_IN);
+  a.dsn = a.sn;
+  a.xr = xr, a.pr = pr, a.orr = orr, a.ng = ng, a.g0 = g0;
+  return a;
+}
+
+template <class V, class T>
+e3_status launch_fwd_sub(const SubArgs<T>& a, const char* name, hipStream_t st) {
+  TimedLaunch t_(name, st);
+  hipLaunchKernelGGL((k_conv_fwd_sub<V, T>), dim3((unsigned)(kXcd * a.chunk * V::NFG * a.nslab)), dim3(kWave),
+                     (size_t)a.fb * V::MAX_NA_F * sizeof(T), st, a);
+  E3_HIP(hipGetLastError());
+  return E3_OK;
+}
+
+// accum: ds += the result (float32 only)
+template <class V, class T>
+e3_status launch_bwd_sub(const SubArgs<T>& a, bool accum, const char* name, hipStream_t st) {
+  TimedLaunch t_(name, st);
+  const dim3 grid((unsigned)(kXcd * a.chunk * V::NBG * a.nslab));
+  const size_t lds = (size_t)a.fb * (V::MAX_NA_B + V::D_SH) * sizeof(T);
+  if constexpr (sizeof(T) == 4) {
+    if (accum) {
+      hipLaunchKernelGGL((k_conv_bwd_sub<V, T, true>), grid, dim3(kWave), lds, st, a);
+      E3_HIP(hipGetLastError());
+      return E3_OK;
+    }
+  }
+  hipLaunchKernelGGL((k_conv_bwd_sub<V, T, false>), grid, dim3(kWave), lds, st, a);
+  E3_HIP(hipGetLastError());
+  return E3_OK;
+}
+
 // One forward convolution.  y: caller's harmonics or null (from vec);
 // accum: m += instead of m =.
 template <class V, int CPL>
 e3_status run_fwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* y,
                   const float* s, float* m, int accum, hipStream_t st) {
+  if (g->n_nodes == 0) return E3_OK;
+  if (p->lay.C <= 32 && sub_fits(g, V::D_IN, V::NP, p->lay.C, sizeof(float))) {
+    auto a = sub_args<V, float>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
+    a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
+    return launch_fwd_sub<V>(a, "conv_fwd", st);
+  }
   ConvArgs a = base_args(p, g);
   a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
   a.nslab = p->nslab_f;
-  if (g->n_nodes == 0) return E3_OK;
   const unsigned grid = (unsigned)(kXcd * a.chunk * V::NFG * a.nslab);
   {
     TimedLaunch t_("conv_fwd", st);
@@ -2440,10 +2717,11 @@ e3_status run_fwd3(const e3_plan* p, const e3_graph* g, const float* x, const fl
 }
 
 // The sender segment sum: dx[node] = sum of its `width` floats (doubles) per
-// slot of T.  Slots of up to kDxShort units, the reach of 256 threads, run
-// k_conv_bwd_dx_short; longer ones fill most of the eight units per lane of
-// k_conv_bwd_dx (5.7-5.9 TB/s at 288, 384 and 512 units).
-constexpr int kDxShort = 256;
+// slot of T.  Slots of up to kDxShort units run k_conv_bwd_dx_short; longer
+// ones fill most of the eight units per lane of k_conv_bwd_dx (158,000 slots:
+// 83 against 69 us at 144 units, 89 against 83 us at 180, 109 against 115 us
+// at 256).
+constexpr int kDxShort = 192;
 
 template <class T>
 void dx_sum(const T* P, T* dx, const e3_graph* g, int width, int accum, hipStream_t st) {
@@ -2479,7 +2757,14 @@ e3_status run_bwd(const e3_plan* p, const e3_graph* g, const float* x, const flo
   a.ds_row = ds ? (int64_t)V::NP * a.C * 4 : 0;
   a.t_row = dx ? (int64_t)V::D_IN * a.C * 4 : 0;
   a.nslab = p->nslab_b;
-  if (g->n_live > 0) {
+  if (g->n_live > 0 && a.C <= 32 && sub_fits(g, V::D_IN, V::NP, a.C, sizeof(float))) {
+    auto b = sub_args<V, float>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
+    b.x = x, b.vec = vec, b.y = y, b.s = s, b.dm = dm, b.ds = a.ds, b.P = a.T, b.DY = a.DY;
+    if (!ds) b.dsn = 0;
+    if (!dx) b.tn = 0;
+    const e3_status r = launch_bwd_sub<V>(b, a.accum, "conv_bwd_edges", st);
+    if (r != E3_OK) return r;
+  } else if (g->n_live > 0) {
     const unsigned grid = (unsigned)(kXcd * a.chunk * V::NBG * a.nslab);
     TimedLaunch t_("conv_bwd_edges", st);
     if (p->cpl_b == 1) {
@@ -2784,13 +3069,9 @@ template <class V>
 e3_status run_fwd64(const e3_plan* p, const e3_graph* g, const double* x, const double* vec, const double* s,
                     double* m, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  ConvArgs a = base_args(p, g);
-  a.nslab = nslab64(p);
-  const unsigned grid = (unsigned)(kXcd * a.chunk * V::NFG * a.nslab);
-  TimedLaunch t_("conv_fwd_f64", st);
-  hipLaunchKernelGGL((k_conv_fwd64<V>), dim3(grid), dim3(kWave), 0, st, a, x, vec, s, m);
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  auto a = sub_args<V, double>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
+  a.x = x, a.vec = vec, a.s = s, a.m = m;
+  return launch_fwd_sub<V>(a, "conv_fwd_f64", st);
 }
 
 template <class V>
@@ -2798,24 +3079,21 @@ e3_status run_bwd64(const e3_plan* p, const e3_graph* g, const double* x, const 
                     const double* dm, double* dx, double* dvec, double* ds, void* ws, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
   const Ws w = bwd_ws64<V>(p, g);
-  ConvArgs a = base_args(p, g);
-  a.nslab = nslab64(p);
-  Conv64Out o{x, vec, s, dm, ds, reinterpret_cast<double*>(ws),
-              reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + w.t_bytes)};
+  auto a = sub_args<V, double>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
+  a.x = x, a.vec = vec, a.s = s, a.dm = dm, a.ds = ds, a.P = reinterpret_cast<double*>(ws);
+  a.DY = reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + w.t_bytes);
   if (g->n_live > 0) {
-    const unsigned grid = (unsigned)(kXcd * a.chunk * V::NBG * a.nslab);
-    TimedLaunch t_("conv_bwd_edges_f64", st);
-    hipLaunchKernelGGL((k_conv_bwd64<V>), dim3(grid), dim3(kWave), 0, st, a, o);
-    E3_HIP(hipGetLastError());
+    const e3_status r = launch_bwd_sub<V>(a, false, "conv_bwd_edges_f64", st);
+    if (r != E3_OK) return r;
   }
   {
     TimedLaunch t_("conv_bwd_dx_f64", st);
-    dx_sum(o.T, dx, g, V::D_IN * a.C, 0, st);
+    dx_sum(a.P, dx, g, V::D_IN * a.C, 0, st);
     E3_HIP(hipGetLastError());
   }
   if (g->n_live > 0) {
     TimedLaunch t_("conv_bwd_dvec_f64", st);
-    hipLaunchKernelGGL((k_conv_bwd_dvec64<V>), dim3(blocks_for(g->n_live, 256)), dim3(256), 0, st, vec, o.DY,
+    hipLaunchKernelGGL((k_conv_bwd_dvec64<V>), dim3(blocks_for(g->n_live, 256)), dim3(256), 0, st, vec, a.DY,
                        g->eid_r, dvec, g->n_live, a.nslab);
     E3_HIP(hipGetLastError());
   }
@@ -2835,6 +3113,11 @@ template <class V>
 e3_status kind_fwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* y,
                    const float* s, float* m, int accum, const KindCall& kc, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
+  if (p->lay.C <= 32 && sub_fits(g, kc.xr, kc.pr, p->lay.C, sizeof(float))) {
+    auto a = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+    a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
+    return launch_fwd_sub<V>(a, "kind_fwd", st);
+  }
   ConvArgs a = base_args(p, g);
   a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
   a.xr = kc.xr, a.pr = kc.pr, a.orr = kc.orr;
@@ -2856,6 +3139,13 @@ e3_status kind_bwd(const e3_plan* p, const e3_graph* g, const float* x, const fl
                    const float* s, const float* dm, float* T, int64_t t_row, float* DY, float* ds, int64_t ds_row,
                    int accum_ds, const KindCall& kc, hipStream_t st) {
   if (g->n_live == 0) return E3_OK;
+  if (p->lay.C <= 32 && sub_fits(g, kc.xr, kc.pr, p->lay.C, sizeof(float))) {
+    auto a = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+    a.x = x, a.vec = vec, a.y = y, a.s = s, a.dm = dm, a.ds = ds, a.P = T, a.DY = DY;
+    if (!ds_row) a.dsn = 0;
+    if (!t_row) a.tn = 0;
+    return launch_bwd_sub<V>(a, accum_ds, "kind_bwd", st);
+  }
   ConvArgs a = base_args(p, g);
   a.x = x, a.vec = vec, a.y = y, a.s = s, a.dm = dm, a.accum = accum_ds;
   a.T = T, a.t_row = t_row, a.DY = DY, a.ds = ds, a.ds_row = ds_row;
@@ -2908,29 +3198,18 @@ template <class V>
 e3_status kind_fwd64(const e3_plan* p, const e3_graph* g, const double* x, const double* vec, const double* s,
                      double* m, const KindCall& kc, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  ConvArgs a = base_args(p, g);
-  a.nslab = nslab64(p);
-  a.xr = kc.xr, a.pr = kc.pr, a.orr = kc.orr;
-  const unsigned grid = (unsigned)(kXcd * a.chunk * V::NFG * a.nslab);
-  TimedLaunch t_("kind_fwd_f64", st);
-  hipLaunchKernelGGL((k_conv_fwd64<V>), dim3(grid), dim3(kWave), 0, st, a, x, vec, s, m);
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  auto a = sub_args<V, double>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+  a.x = x, a.vec = vec, a.s = s, a.m = m;
+  return launch_fwd_sub<V>(a, "kind_fwd_f64", st);
 }
 
 template <class V>
 e3_status kind_bwd64(const e3_plan* p, const e3_graph* g, const double* x, const double* vec, const double* s,
                      const double* dm, double* T, double* DY, double* ds, const KindCall& kc, hipStream_t st) {
   if (g->n_live == 0) return E3_OK;
-  ConvArgs a = base_args(p, g);
-  a.nslab = nslab64(p);
-  a.xr = kc.xr, a.pr = kc.pr, a.orr = kc.orr, a.ng = kc.ng, a.g0 = kc.g0;
-  Conv64Out o{x, vec, s, dm, ds, T, DY};
-  const unsigned grid = (unsigned)(kXcd * a.chunk * V::NBG * a.nslab);
-  TimedLaunch t_("kind_bwd_f64", st);
-  hipLaunchKernelGGL((k_conv_bwd64<V>), dim3(grid), dim3(kWave), 0, st, a, o);
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  auto a = sub_args<V, double>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+  a.x = x, a.vec = vec, a.s = s, a.dm = dm, a.ds = ds, a.P = T, a.DY = DY;
+  return launch_bwd_sub<V>(a, false, "kind_bwd_f64", st);
 }
 
 template <class V>

@@ -79,3 +79,46 @@ def _check_conv(e3, irreps, lsh, lout, f64, pad=-1, natural=False, composed=Fals
 ])
 def test_segment_sum_widths(e3, irreps, lsh, lout, f64):
     _check_conv(e3, irreps, lsh, lout, f64)
+
+
+# float32: 8, 16, 32 lanes per edge up to C = 32, then whole waves; float64:
+# the same, and 64 lanes per edge above, in one slab and in two
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("C", [4, 8, 12, 16, 20, 32, 36, 64, 72])
+@pytest.mark.parametrize("blocks,lsh,lout,natural,composed", [
+    ("0e+1o", 2, 2, False, False), ("0e+1o+2e+3o", 3, 3, True, False), ("1o+0e+3o+2e", 3, 3, False, False),
+    ("2e+0o+1e", 3, 2, False, True),
+])
+def test_narrow_sweeps(e3, blocks, lsh, lout, natural, composed, C, f64):
+    irreps = "+".join(f"{C}x{b}" for b in blocks.split("+"))
+    _check_conv(e3, irreps, lsh, lout, f64, pad=-1, natural=natural, composed=composed)
+    _check_conv(e3, irreps, lsh, lout, f64, pad=24, natural=natural, composed=composed)
+
+
+def test_narrow_beyond_lane_offsets(e3):
+    """32 channels with weights past 4 GiB: the float32 and float64 sweeps fall
+    back to whole waves; they agree to float32 rounding, and with the sub-wave
+    sweeps on a graph of the first edges."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n, E, C = 20_000, 930_000, 32
+    plan = e3.Plan("32x0e+32x1o+32x2e+32x3o", 3, 3)
+    print("[case] beyond lane offsets", E * plan.P * C * 4, flush=True)
+    assert E * plan.P * C * 4 > 0xF0000000
+    snd, rcv = (torch.randint(0, n, (E,), generator=g, device="cuda", dtype=torch.int32) for _ in range(2))
+    f = [torch.randn(sh, generator=g, device="cuda") for sh in
+         ((n, plan.D_in, C), (E, 3), (E, plan.P, C), (n, plan.D_out, C))]
+    x, vec, s, dm = f
+    G = e3.Graph(snd, rcv, n)
+    m, (dx, dvec, ds) = e3.conv_fwd(plan, G, x, vec, s), e3.conv_bwd(plan, G, x, vec, s, dm)
+    x64, vec64, s64, dm64 = (t.double() for t in f)
+    m64 = e3.conv_fwd_f64(plan, G, x64, vec64, s64)
+    dx64, dvec64, ds64 = e3.conv_bwd_f64(plan, G, x64, vec64, s64, dm64)
+    for a, b in ((m, m64), (dx, dx64), (dvec, dvec64), (ds, ds64)):
+        assert float((a - b).norm() / b.norm()) < TOL
+    # ds and dvec are per edge: the first edges alone give the same values
+    k = 5000
+    Gk = e3.Graph(snd[:k].contiguous(), rcv[:k].contiguous(), n)
+    _, dvec_k, ds_k = e3.conv_bwd(plan, Gk, x, vec[:k].contiguous(), s[:k].contiguous(), dm)
+    assert float((ds_k - ds64[:k]).norm() / ds64[:k].norm()) < TOL
+    assert float((dvec_k - dvec64[:k]).norm() / dvec64[:k].norm()) < TOL
