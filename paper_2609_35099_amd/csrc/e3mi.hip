@@ -407,20 +407,41 @@ __global__ __launch_bounds__(256) void k_lin_dw_sum(const float* __restrict__ dW
 // ------------------------------------------------------------ generic records
 // Tensor product with caller-supplied records (App. E.2's unfolded form):
 //   out[r, o, q] = sum over the records of segment o of v A[r, a, q] B[r, b, (q)]
-// A wave takes RB rows of one 64-channel slab.  The operand rows are staged in
-// LDS as [a][row][lane] (so one address serves the RB rows of a record), the
-// records and segment offsets are read-only for the launch and come through
-// the scalar cache, and each record feeds RB fused multiply-adds.  The
-// backward is the same kernel on permuted record tables (eq. tp-bwd); with RED
-// the outputs are summed over the channels (a shared y's cotangent): per-slab
-// partials in fixed lane order, then k_tpg_sum.
+// Rows and channels are independent, so a wave takes RB x 64 consecutive
+// (row, channel) pairs, whatever C is (64-channel slabs of a row left lanes
+// idle at any other C, and shared cache lines between waves of different XCDs
+// at C = 100).  The operands are staged in LDS as [a][u][lane] (pair 64 u +
+// lane, so one address serves the RB pairs of a lane); each record feeds RB
+// fused multiply-adds.  The backward is the same kernel on permuted record
+// tables (eq. tp-bwd).  With RED the outputs are summed over the channels (a
+// shared y's cotangent): a wave takes whole rows, or one piece of a row longer
+// than RB x 64 (its partials then added by k_tpg_sum), and adds in a fixed
+// order.
+//
+// What bounds it is latency and instruction issue, not the LDS reads (38% of
+// their rate), so nothing in the chain waits alone: the float32 operands go
+// straight to LDS with every load in flight at once; a chunk of 64 records is
+// one coalesced load, a record per lane, handed out by v_readlane (scalar loads
+// would share the LDS reads' wait counter); the operands of the next kTpgAhead
+// records are read while the current ones are used, and a group of records in
+// which no segment ends takes no branches.  Per kernel, with 9 + 9 operand rows
+// and 137 records (30,011 rows, C = 100): 189 -> 117 us (2.8 TB/s); 16 + 16
+// rows, 611 records (20,000 rows, C = 64) 303 -> 218 us; 9 + 4 rows, 59 records
+// (40,000 rows, C = 12) 46 -> 16 us; 16 records (50,000 rows, C = 128), at 4.9
+// TB/s before, 62 us either way.  kTpgAhead = 4: 120 and 237 us.
+constexpr int kTpgAhead = 8;
+
+// A segment's last record carries kTpgEnd; a segment without records has one
+// with kTpgEmpty, which stores zeros.  Tables are padded to a multiple of
+// kTpgAhead with records that belong to no segment.
+constexpr unsigned kTpgEnd = 1u << 30, kTpgEmpty = 1u << 31;
 struct TpgRec {
-  int a, b;
+  unsigned ab;  // a | b << 10 | flags (operand rows: at most 256 fit the staging)
   float v;
-  int pad;
 };
 struct TpgRec64 {
-  int a, b;
+  unsigned ab;
+  unsigned pad;
   double v;
 };
 template <class T>
@@ -428,100 +449,184 @@ struct TpgArgs {
   const T* A;
   const T* B;
   T* out;
-  T* part;  // RED: [rows][nslab][dout]
-  const int* seg;
+  T* part;  // RED: [rows][pieces][dout] (dy itself when pieces == 1)
   const typename std::conditional<sizeof(T) == 8, TpgRec64, TpgRec>::type* recs;
+  int nrec;
   int64_t rows;
-  int C, nslab, dA, dB, dout;
+  int C, dA, dB, dout;
+  int pieces;  // RED: tiles of one row (1: `rpt` whole rows per tile)
+  int rpt;
 };
 
+__device__ __forceinline__ float lane_of(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_of(double v, int l) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)x, l);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(x >> 32), l);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 
 template <class T>
-__device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, int off) {
+__device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, int off, int soff) {
   if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
   else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
 }
 
 template <class T, bool BSH, bool RED, int RB>
 __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
-  using Rec = typename std::conditional<sizeof(T) == 8, TpgRec64, TpgRec>::type;
-  const ConstPtr<Rec> recs = (ConstPtr<Rec>)a.recs;
-  const ConstPtr<int> seg = (ConstPtr<int>)a.seg;
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  T* lds = reinterpret_cast<T*>(lds_raw);
-  int sl;
-  int64_t tile;
-  if (!tile_of<false>(a.rows, RB, a.nslab, tile, sl)) return;
-  const int64_t r0 = tile * RB;
-  const int nr = a.rows - r0 < RB ? (int)(a.rows - r0) : RB;
-  const int lane = threadIdx.x, q = sl * kWave + lane;
-  const bool act = q < a.C;
-  T* sA = lds;                                                        // [dA][RB][64]
-  T* sB = sA + a.dA * RB * kWave;                                     // BSH: [dB][RB], else [dB][RB][64]
-  T* sP = sB + (BSH ? ((a.dB * RB + 3) & ~3) : a.dB * RB * kWave);    // RED: [dout][RB][64]
-  // Operand loads through descriptors bounded by the block's rows: rows past
-  // the end read zero; lanes past C are zeroed (their sums enter RED's total).
-  const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<T*>(a.A) + r0 * a.dA * a.C, (short)0, (int)((int64_t)nr * a.dA * a.C * sizeof(T)), 0x00020000);
-  const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<T*>(a.B) + r0 * a.dB * (BSH ? 1 : a.C), (short)0,
-      (int)((int64_t)nr * a.dB * (BSH ? 1 : a.C) * sizeof(T)), 0x00020000);
-#pragma unroll 8
-  for (int i = 0; i < a.dA * RB; ++i) {
-    const int ai = i / RB, u = i % RB;
-    const T v = buf_ld<T>(ar, (int)(((u * a.dA + ai) * a.C + q) * sizeof(T)));
-    sA[i * kWave + lane] = act ? v : T(0);
-  }
-  if constexpr (BSH) {
-    for (int i = lane; i < a.dB * RB; i += kWave) {
-      const int bi = i / RB, u = i % RB;
-      sB[i] = buf_ld<T>(br, (int)((u * a.dB + bi) * sizeof(T)));
+  T* sA = reinterpret_cast<T*>(lds_raw);     // [dA][RB][64]
+  T* sB = sA + a.dA * RB * kWave;            // [dB][RB][64]
+  T* sP = sB + a.dB * RB * kWave;            // RED: [dout][RB][64]
+  const int lane = threadIdx.x, C = a.C;
+  constexpr int kPairs = RB * kWave;
+  // first row and channel of the tile, and its number of pairs
+  const int64_t tile = blockIdx.x;
+  int64_t r0;
+  int c0, np;
+  if constexpr (RED) {
+    if (a.pieces == 1) {
+      r0 = tile * a.rpt, c0 = 0;
+      np = (int)(a.rows - r0 < a.rpt ? a.rows - r0 : a.rpt) * C;
+    } else {
+      r0 = tile / a.pieces, c0 = (int)(tile % a.pieces) * kPairs;
+      np = imin(kPairs, C - c0);
     }
   } else {
-#pragma unroll 8
-    for (int i = 0; i < a.dB * RB; ++i) {
-      const int bi = i / RB, u = i % RB;
-      const T v = buf_ld<T>(br, (int)(((u * a.dB + bi) * a.C + q) * sizeof(T)));
-      sB[i * kWave + lane] = act ? v : T(0);
-    }
+    const int64_t p0 = tile * kPairs, left = a.rows * C - p0;
+    r0 = p0 / C, c0 = (int)(p0 - r0 * C);
+    np = left < kPairs ? (int)left : kPairs;
   }
-  __syncthreads();
-  int k = seg[0];
-  for (int o = 0; o < a.dout; ++o) {
-    const int k1 = seg[o + 1];
-    T acc[RB];
+  // the lane's pairs: row r0 + dr, channel q; operand offsets from row r0
+  unsigned offA[RB], offB[RB];
+  T* po[RB];
 #pragma unroll
-    for (int u = 0; u < RB; ++u) acc[u] = T(0);
-#pragma unroll 2
-    for (; k < k1; ++k) {
-      const int ra = recs[k].a, rbi = recs[k].b;
-      const T rv = T(recs[k].v);
-      const T* pa = sA + ra * RB * kWave + lane;
+  for (int u = 0; u < RB; ++u) {
+    const int i = u * kWave + lane, at = c0 + i, dr = at / C, q = at - dr * C;
+    const bool on = i < np;
+    offA[u] = on ? (unsigned)(dr * a.dA * C + q) * (unsigned)sizeof(T) : kSubOff;
+    offB[u] = on ? (unsigned)(BSH ? dr * a.dB : dr * a.dB * C + q) * (unsigned)sizeof(T) : kSubOff;
+    po[u] = a.out + ((r0 + dr) * a.dout * C + q);
+  }
+  auto rsrc = [&](const T* p, int64_t row) {
+    const int64_t n = (a.rows - r0) * row * (int64_t)sizeof(T);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p) + r0 * row, (short)0,
+                                             (int)(unsigned)(n < (int64_t)kSubOff ? n : (int64_t)kSubOff), 0x00020000);
+  };
+  auto stage = [&](__amdgpu_buffer_rsrc_t r, T* dst, int d, const unsigned (&off)[RB], int stride) {
+    if constexpr (sizeof(T) == 4) {
+      for (int ai = 0; ai < d; ++ai)
 #pragma unroll
-      for (int u = 0; u < RB; ++u) {
-        const T bv = BSH ? sB[rbi * RB + u] : sB[(rbi * RB + u) * kWave + lane];
-        acc[u] = fma(rv * pa[u * kWave], bv, acc[u]);
+        for (int u = 0; u < RB; ++u)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              r, (__attribute__((address_space(3))) void*)(dst + (ai * RB + u) * kWave), 4, (int)off[u],
+              ai * stride * 4, 0, 0);
+    } else {
+      constexpr int N = 16 / RB;  // operand rows in flight
+      for (int a0 = 0; a0 < d; a0 += N) {
+        T v[N][RB];
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+#pragma unroll
+          for (int u = 0; u < RB; ++u)
+            v[k][u] = buf_ld<T>(r, a0 + k < d ? (int)off[u] : (int)kSubOff, (a0 + k) * stride * (int)sizeof(T));
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+          if (a0 + k < d)
+#pragma unroll
+            for (int u = 0; u < RB; ++u) dst[((a0 + k) * RB + u) * kWave + lane] = v[k][u];
       }
     }
-    if constexpr (RED) {
+  };
+  stage(rsrc(a.A, (int64_t)a.dA * C), sA, a.dA, offA, C);
+  stage(rsrc(a.B, (int64_t)a.dB * (BSH ? 1 : C)), sB, a.dB, offB, BSH ? 1 : C);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads to LDS
+  __syncthreads();
+  int o = 0;
+  T acc[RB];
 #pragma unroll
-      for (int u = 0; u < RB; ++u) sP[(o * RB + u) * kWave + lane] = acc[u];
-    } else if (act) {
+  for (int u = 0; u < RB; ++u) acc[u] = T(0);
+  for (int k0 = 0; k0 < a.nrec; k0 += kWave) {
+    const int nk = imin(kWave, a.nrec - k0);  // a multiple of kTpgAhead
+    const auto mine = a.recs[k0 + imin(lane, nk - 1)];
+    const T my_v = T(mine.v);
+    // per lane: LDS offsets of its record's operands; per chunk: the flag bits
+    const int my_a = (int)(mine.ab & 0x3ffu) * (RB * kWave);
+    const int my_b = (int)(mine.ab >> 10 & 0x3ffu) * (RB * kWave);
+    const uint64_t ends = __ballot((mine.ab & (kTpgEnd | kTpgEmpty)) != 0), empties = __ballot((mine.ab & kTpgEmpty) != 0);
+    T pa[2][kTpgAhead][RB], pb[2][kTpgAhead][RB];
+    auto fetch = [&](int k, T (&va)[kTpgAhead][RB], T (&vb)[kTpgAhead][RB]) {
 #pragma unroll
-      for (int u = 0; u < RB; ++u)
-        if (u < nr) a.out[((r0 + u) * a.dout + o) * a.C + q] = acc[u];
+      for (int j = 0; j < kTpgAhead; ++j) {
+        const T* qa = sA + __builtin_amdgcn_readlane(my_a, k + j) + lane;
+        const T* qb = sB + __builtin_amdgcn_readlane(my_b, k + j) + lane;
+#pragma unroll
+        for (int u = 0; u < RB; ++u) va[j][u] = qa[u * kWave], vb[j][u] = qb[u * kWave];
+      }
+    };
+    auto use = [&](int k, const T (&va)[kTpgAhead][RB], const T (&vb)[kTpgAhead][RB]) {
+      const unsigned end = (unsigned)(ends >> k) & ((1u << kTpgAhead) - 1), empty = (unsigned)(empties >> k);
+      if (end == 0) {  // most groups: no segment ends inside
+#pragma unroll
+        for (int j = 0; j < kTpgAhead; ++j) {
+          const T rv = lane_of(my_v, k + j);
+#pragma unroll
+          for (int u = 0; u < RB; ++u) acc[u] = fma(rv * va[j][u], vb[j][u], acc[u]);
+        }
+        return;
+      }
+#pragma unroll
+      for (int j = 0; j < kTpgAhead; ++j) {
+        const T rv = lane_of(my_v, k + j);
+#pragma unroll
+        for (int u = 0; u < RB; ++u) acc[u] = fma(rv * va[j][u], vb[j][u], acc[u]);
+        if (end >> j & 1) {
+          if (empty >> j & 1) {
+#pragma unroll
+            for (int u = 0; u < RB; ++u) acc[u] = T(0);
+          }
+          if constexpr (RED) {
+#pragma unroll
+            for (int u = 0; u < RB; ++u) sP[(o * RB + u) * kWave + lane] = acc[u];
+          } else {
+            const int64_t at = (int64_t)o * C;
+#pragma unroll
+            for (int u = 0; u < RB; ++u)
+              if (u * kWave + lane < np) po[u][at] = acc[u];
+          }
+#pragma unroll
+          for (int u = 0; u < RB; ++u) acc[u] = T(0);
+          ++o;
+        }
+      }
+    };
+    fetch(0, pa[0], pb[0]);
+    for (int k = 0; k < nk; k += 2 * kTpgAhead) {
+      if (k + kTpgAhead < nk) fetch(k + kTpgAhead, pa[1], pb[1]);
+      use(k, pa[0], pb[0]);
+      if (k + kTpgAhead < nk) {
+        if (k + 2 * kTpgAhead < nk) fetch(k + 2 * kTpgAhead, pa[0], pb[0]);
+        use(k + kTpgAhead, pa[1], pb[1]);
+      }
     }
   }
   if constexpr (RED) {
     __syncthreads();
-    for (int i = lane; i < a.dout * RB; i += kWave) {
-      const int o = i / RB, u = i % RB;
-      if (u >= nr) continue;
+    const int w = a.pieces == 1 ? C : np, nrow = np / w;  // channels and rows of the tile
+    for (int i = lane; i < a.dout * nrow; i += kWave) {
+      const int ou = i / nrow, r = i - ou * nrow;
+      const T* p = sP + ou * kPairs + r * w;
       T t = T(0);
-      for (int l = 0; l < kWave; ++l) t += sP[i * kWave + l];
-      a.part[((r0 + u) * a.nslab + sl) * a.dout + o] = t;
+      // lane i starts at channel i (mod w), so that the lanes read different banks
+      for (int l = 0, c = i % w; l < w; ++l) {
+        t += p[c];
+        c = c + 1 == w ? 0 : c + 1;
+      }
+      a.part[((r0 + r) * a.pieces + (a.pieces == 1 ? 0 : tile % a.pieces)) * a.dout + ou] = t;
     }
   }
 }
@@ -1693,10 +1798,10 @@ struct e3_tpg {
   int d_x = 0, d_y = 0, d_z = 0, ypc = 0;
   // record tables: forward (out z, A x, B y), dx (out x, A dz, B y), dy (out y, A x, B dz)
   struct Table {
-    std::vector<int> seg;
+    int d_out = 0;
     std::vector<TpgRec> recs;
     std::vector<TpgRec64> recs64;
-    size_t off_seg = 0, off_recs = 0, off_recs64 = 0;
+    size_t off_recs = 0, off_recs64 = 0;
   } t[3];
   char* dev = nullptr;  // device copy of the tables (uploaded by e3_tpg_create)
   int device = -1;      // the device that holds it
@@ -1709,13 +1814,21 @@ e3_tpg::Table tpg_table(int d_out, const std::vector<std::array<int, 3>>& key, c
   for (size_t i = 0; i < ord.size(); ++i) ord[i] = i;
   std::stable_sort(ord.begin(), ord.end(), [&](size_t u, size_t v) { return key[u] < key[v]; });
   e3_tpg::Table T;
-  T.seg.assign(d_out + 1, 0);
-  for (size_t i : ord) {
-    T.recs.push_back(TpgRec{key[i][1], key[i][2], (float)val[i], 0});
-    T.recs64.push_back(TpgRec64{key[i][1], key[i][2], val[i]});
-    ++T.seg[key[i][0] + 1];
+  T.d_out = d_out;
+  auto push = [&](unsigned ab, double v) {
+    T.recs.push_back(TpgRec{ab, (float)v});
+    T.recs64.push_back(TpgRec64{ab, 0, v});
+  };
+  size_t k = 0;
+  for (int o = 0; o < d_out; ++o) {
+    if (k == ord.size() || key[ord[k]][0] != o) push(kTpgEmpty, 0.0);
+    for (; k < ord.size() && key[ord[k]][0] == o; ++k) {
+      const size_t i = ord[k];
+      const bool last = k + 1 == ord.size() || key[ord[k + 1]][0] != o;
+      push((unsigned)key[i][1] | (unsigned)key[i][2] << 10 | (last ? kTpgEnd : 0u), val[i]);
+    }
   }
-  for (int o = 0; o < d_out; ++o) T.seg[o + 1] += T.seg[o];
+  while (T.recs.size() % kTpgAhead) push(0, 0.0);
   return T;
 }
 
@@ -1724,8 +1837,6 @@ e3_tpg::Table tpg_table(int d_out, const std::vector<std::array<int, 3>>& key, c
 e3_status tpg_upload(e3_tpg* G) {
   size_t off = 0;
   for (auto& T : G->t) {
-    T.off_seg = off;
-    off = align256(off + T.seg.size() * sizeof(int));
     T.off_recs = off;
     off = align256(off + T.recs.size() * sizeof(TpgRec) + 1);
     T.off_recs64 = off;
@@ -1733,7 +1844,6 @@ e3_status tpg_upload(e3_tpg* G) {
   }
   std::vector<char> host(off, 0);
   for (auto& T : G->t) {
-    std::memcpy(host.data() + T.off_seg, T.seg.data(), T.seg.size() * sizeof(int));
     if (!T.recs.empty()) std::memcpy(host.data() + T.off_recs, T.recs.data(), T.recs.size() * sizeof(TpgRec));
     if (!T.recs64.empty())
       std::memcpy(host.data() + T.off_recs64, T.recs64.data(), T.recs64.size() * sizeof(TpgRec64));
@@ -1751,12 +1861,24 @@ e3_status tpg_upload(e3_tpg* G) {
   return E3_OK;
 }
 
-size_t tpg_lds(int dA, int dB, int dout, bool bsh, bool red, size_t elem = sizeof(float), int rb = 1) {
+// Staging of one wave with rb pairs per lane (all operands per pair).
+size_t tpg_lds(int dA, int dB, int dout, bool red, size_t elem, int rb) {
+  return ((size_t)dA + dB + (red ? dout : 0)) * rb * kWave * elem;
+}
+constexpr size_t kTpgMaxLds = 64 * 1024;
+// Pairs per lane: the most of 4, 2, 1 whose staging leaves ten waves per CU.
+// More waves hide more latency, more pairs share a record's overhead: 118, 121
+// and 139 us with 2, 4 and 1 at 18 operand rows (30,011 rows, C = 100), 241,
+// 292 and 281 us at 32 (20,000 rows, C = 64).
+constexpr size_t kTpgWant = 16 * 1024;
+
+// What a call accepts: one row's operands of 64 channels (a shared B once)
+// within the limit, and its operand block of up to four rows within 2 GiB.
+size_t tpg_row_lds(int dA, int dB, int dout, bool bsh, bool red, size_t elem, int rb = 1) {
   return ((size_t)dA * rb * kWave + (bsh ? (((size_t)dB * rb + 3) & ~3) : (size_t)dB * rb * kWave) +
           (red ? (size_t)dout * rb * kWave : 0)) *
          elem;
 }
-constexpr size_t kTpgMaxLds = 64 * 1024;
 
 template <class T>
 e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, int dB, bool bsh, T* out, T* part,
@@ -1764,30 +1886,33 @@ e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, in
   const e3_tpg::Table& Tb = G->t[which];
   TpgArgs<T> a{};
   a.A = A, a.B = B, a.out = out, a.part = part;
-  a.seg = reinterpret_cast<const int*>(G->dev + Tb.off_seg);
   a.recs = reinterpret_cast<decltype(a.recs)>(G->dev + (sizeof(T) == 8 ? Tb.off_recs64 : Tb.off_recs));
-  a.rows = rows, a.C = C, a.nslab = (C + kWave - 1) / kWave, a.dA = dA, a.dB = dB;
-  a.dout = (int)Tb.seg.size() - 1;
-  // rows per wave: the most of 4, 2, 1 whose staging fits the LDS limit
+  a.nrec = (int)Tb.recs.size();
+  a.rows = rows, a.C = C, a.dA = dA, a.dB = dB;
+  a.dout = Tb.d_out;
+  int rows_per = 4;
+  while (rows_per > 1 && tpg_row_lds(dA, dB, a.dout, bsh, red, sizeof(T), rows_per) > kTpgMaxLds) rows_per /= 2;
+  if (tpg_row_lds(dA, dB, a.dout, bsh, red, sizeof(T), rows_per) > kTpgMaxLds) return E3_ERR_UNSUPPORTED;
+  if ((int64_t)rows_per * std::max(dA, dB) * C * (int64_t)sizeof(T) > 0x7fffffff) return E3_ERR_INVALID_ARG;
+  // pairs per lane
   int rb = 4;
-  while (rb > 1 && tpg_lds(dA, dB, a.dout, bsh, red, sizeof(T), rb) > kTpgMaxLds) rb /= 2;
-  const size_t lds = tpg_lds(dA, dB, a.dout, bsh, red, sizeof(T), rb);
-  if (lds > kTpgMaxLds) return E3_ERR_UNSUPPORTED;
-  // operand blocks are addressed with 32-bit byte offsets
-  if ((int64_t)rb * std::max(dA, dB) * C * (int64_t)sizeof(T) > 0x7fffffff) return E3_ERR_INVALID_ARG;
-  const int64_t grid = tile_grid(false, rows, rb, a.nslab);
+  while (rb > 1 && tpg_lds(dA, dB, a.dout, red, sizeof(T), rb) > kTpgWant) rb /= 2;
+  const size_t lds = tpg_lds(dA, dB, a.dout, red, sizeof(T), rb);
+  const int pairs = rb * kWave;
+  a.pieces = red ? (C + pairs - 1) / pairs : 1;
+  a.rpt = red && C <= pairs ? pairs / C : 1;
+  const int64_t grid = !red ? (rows * C + pairs - 1) / pairs : a.pieces > 1 ? rows * a.pieces : (rows + a.rpt - 1) / a.rpt;
   if (grid > 0x7fffffff) return E3_ERR_INVALID_ARG;
+  if (red && a.pieces == 1) a.part = out;
   TimedLaunch t_(name, st);
   auto go = [&](auto RBc) {
     constexpr int R = decltype(RBc)::value;
-    if (bsh && red)
-      hipLaunchKernelGGL((k_tpg<T, true, true, R>), dim3((unsigned)grid), dim3(kWave), lds, st, a);
-    else if (bsh)
-      hipLaunchKernelGGL((k_tpg<T, true, false, R>), dim3((unsigned)grid), dim3(kWave), lds, st, a);
-    else if (red)
-      hipLaunchKernelGGL((k_tpg<T, false, true, R>), dim3((unsigned)grid), dim3(kWave), lds, st, a);
-    else
-      hipLaunchKernelGGL((k_tpg<T, false, false, R>), dim3((unsigned)grid), dim3(kWave), lds, st, a);
+    auto* k = bsh ? (red ? k_tpg<T, true, true, R> : k_tpg<T, true, false, R>)
+                  : (red ? k_tpg<T, false, true, R> : k_tpg<T, false, false, R>);
+    // over 64 KiB only in float64 with a shared B of many rows
+    if (lds > kTpgMaxLds)
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kWave), lds, st, a);
   };
   if (rb == 4)
     go(std::integral_constant<int, 4>{});
@@ -1796,6 +1921,11 @@ e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, in
   else
     go(std::integral_constant<int, 1>{});
   E3_HIP(hipGetLastError());
+  if (red && a.pieces > 1) {
+    hipLaunchKernelGGL(k_tpg_sum<T>, dim3(blocks_for(rows * a.dout, 256)), dim3(256), 0, st, part, out, rows, a.pieces,
+                       a.dout);
+    E3_HIP(hipGetLastError());
+  }
   return E3_OK;
 }
 }  // namespace
@@ -1812,8 +1942,9 @@ e3_status e3_tpg_create(int d_x, int d_y, int d_z, int64_t nnz, const int32_t* i
     if (i0[k] < 0 || i0[k] >= d_z || i1[k] < 0 || i1[k] >= d_x || i2[k] < 0 || i2[k] >= d_y)
       return E3_ERR_INDEX_OUT_OF_RANGE;
   const bool bsh = !y_per_channel;
-  if (tpg_lds(d_x, d_y, d_z, bsh, false) > kTpgMaxLds || tpg_lds(d_z, d_y, d_x, bsh, false) > kTpgMaxLds ||
-      tpg_lds(d_x, d_z, d_y, false, bsh) > kTpgMaxLds) {
+  const size_t f = sizeof(float);
+  if (tpg_row_lds(d_x, d_y, d_z, bsh, false, f) > kTpgMaxLds || tpg_row_lds(d_z, d_y, d_x, bsh, false, f) > kTpgMaxLds ||
+      tpg_row_lds(d_x, d_z, d_y, false, bsh, f) > kTpgMaxLds) {
     g_last_error = "record tensor product: operand rows do not fit the 64 KiB staging limit";
     return E3_ERR_UNSUPPORTED;
   }
@@ -1881,18 +2012,8 @@ e3_status tpg_bwd(e3_tpg* G, const T* x, const T* y, const T* dz, T* dx, T* dy, 
                       f64 ? "tpg_bwd_dx_f64" : "tpg_bwd_dx", st)) != E3_OK)
     return s;
   // dy = tensor_product(C^{i2}_{i1 i0}, x, dz), summed over the channels when y is shared
-  if (G->ypc)
-    return tpg_run<T>(G, 2, x, G->d_x, dz, G->d_z, false, dy, nullptr, false, rows, C,
-                      f64 ? "tpg_bwd_dy_f64" : "tpg_bwd_dy", st);
-  T* part = reinterpret_cast<T*>(ws);
-  if ((s = tpg_run<T>(G, 2, x, G->d_x, dz, G->d_z, false, nullptr, part, true, rows, C,
-                      f64 ? "tpg_bwd_dy_f64" : "tpg_bwd_dy", st)) != E3_OK)
-    return s;
-  TimedLaunch t_(f64 ? "tpg_bwd_dy_sum_f64" : "tpg_bwd_dy_sum", st);
-  hipLaunchKernelGGL(k_tpg_sum<T>, dim3(blocks_for(rows * G->d_y, 256)), dim3(256), 0, st, part, dy, rows,
-                     (C + kWave - 1) / kWave, G->d_y);
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  return tpg_run<T>(G, 2, x, G->d_x, dz, G->d_z, false, dy, reinterpret_cast<T*>(ws), !G->ypc, rows, C,
+                    f64 ? "tpg_bwd_dy_f64" : "tpg_bwd_dy", st);
 }
 }  // namespace
 

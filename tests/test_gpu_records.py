@@ -1,0 +1,77 @@
+"""The caller-record tensor product at the edges of its record walk and row
+tiles: record counts around a chunk of 64 and the look-ahead, output rows
+without records (first, last, in between), row and channel remainders, both
+kinds of y, both precisions, against a float64 sum record by record.
+
+Bars: each output row sums at most 140 terms; rel-L2 1e-6 in float32 (about 16
+roundings of 6e-8) and 1e-14 in float64.
+"""
+import numpy as np
+import pytest
+
+from gpu_util import rel_l2, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def e3():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2609_35099_amd import e3mi
+    e3mi.lib()
+    return e3mi
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("ypc", [False, True])
+@pytest.mark.parametrize("nnz,dims,rows,C", [
+    (0, (2, 3, 4), 5, 7), (1, (1, 1, 1), 1, 1), (3, (4, 2, 5), 2, 63), (63, (5, 4, 7), 3, 64),
+    (64, (5, 4, 7), 4, 65), (65, (9, 9, 9), 5, 100), (67, (9, 9, 9), 9, 12), (137, (9, 4, 16), 13, 130),
+    (260, (40, 3, 30), 6, 20), (90, (60, 50, 8), 3, 10),
+])
+def test_record_walk_edges(e3, nnz, dims, rows, C, ypc, f64):
+    rng = np.random.default_rng(nnz * 7 + rows)
+    dx_, dy_, dz_ = dims
+    # output rows 0, dz - 1 and every fourth one get no record
+    outs = [o for o in range(dz_) if o % 4 != 0 and o != dz_ - 1] or [0]
+    i0 = rng.choice(outs, nnz).astype(np.int32)
+    i1, i2 = rng.integers(0, dx_, nnz).astype(np.int32), rng.integers(0, dy_, nnz).astype(np.int32)
+    val = rng.standard_normal(nnz)
+    dt = np.float64 if f64 else np.float32
+    x = rng.standard_normal((rows, dx_, C)).astype(dt)
+    y = rng.standard_normal((rows, dy_, C) if ypc else (rows, dy_)).astype(dt)
+    dz = rng.standard_normal((rows, dz_, C)).astype(dt)
+    print("[case]", nnz, dims, rows, C, ypc, f64, flush=True)
+    tp = e3.RecordTP(dx_, dy_, dz_, i0, i1, i2, val, y_per_channel=ypc)
+    z = tp.forward(to_dev(x), to_dev(y))
+    gx, gy = tp.backward(to_dev(x), to_dev(y), to_dev(dz))
+    x, y, dz = x.astype(np.float64), y.astype(np.float64), dz.astype(np.float64)
+    yc = y if ypc else np.repeat(y[..., None], C, 2)
+    rz, rx, ry = np.zeros((rows, dz_, C)), np.zeros_like(x), np.zeros_like(yc)
+    v = val if f64 else val.astype(np.float32).astype(np.float64)
+    for a, b, c, w in zip(i0, i1, i2, v):
+        rz[:, a] += w * x[:, b] * yc[:, c]
+        rx[:, b] += w * dz[:, a] * yc[:, c]
+        ry[:, c] += w * dz[:, a] * x[:, b]
+    ry = ry if ypc else ry.sum(2)
+    tol = 1e-14 if f64 else 1e-6
+    for got, ref in ((z, rz), (gx, rx), (gy, ry)):
+        assert rel_l2(to_np(got), ref) < tol
+    empty = [o for o in range(dz_) if o not in set(i0.tolist())]
+    assert not to_np(z)[:, empty].any()
+
+
+def test_wide_shared_operands_f64(e3):
+    """float64 operands of 200 rows with a shared y: more than 64 KiB staged per wave."""
+    rng = np.random.default_rng(5)
+    nnz, dx_, dy_, dz_, rows, C = 300, 100, 100, 8, 7, 70
+    i0, i1, i2 = (rng.integers(0, d, nnz).astype(np.int32) for d in (dz_, dx_, dy_))
+    val, x, y = rng.standard_normal(nnz), rng.standard_normal((rows, dx_, C)), rng.standard_normal((rows, dy_))
+    print("[case] wide shared operands", flush=True)
+    z = e3.RecordTP(dx_, dy_, dz_, i0, i1, i2, val, y_per_channel=False).forward(to_dev(x), to_dev(y))
+    ref = np.zeros((rows, dz_, C))
+    for a, b, c, w in zip(i0, i1, i2, val):
+        ref[:, a] += w * x[:, b] * y[:, c, None]
+    assert rel_l2(to_np(z), ref) < 1e-14
