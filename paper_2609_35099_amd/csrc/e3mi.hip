@@ -30,42 +30,15 @@ Timing g_timing;
 
 namespace {
 // ------------------------------------------------------------ linear mixing
-// Dense per-irrep channel mixing on the matrix cores (v_mfma_f32_16x16x4f32,
-// fp32 in and out).  A destination block of 2l+1 rows per node receives, for
-// each of its sources, src[n, src_row + m, k] B[k, col] summed over k and the
-// sources, B[k, col] = W[w_off + k ldk + col ldc].  The forward has one job per
-// output block (its sources: the input blocks of the same degree and parity);
-// dx has one job per input block (its sources: the output blocks it feeds,
-// with W read transposed).
-//
-// One wave per (job, tile of 32 rows, slab of 64 columns).  Operand layout of
-// the 16x16x4 instruction: A[i][kk] from lane i + 16 kk, B[kk][j] from lane
-// j + 16 kk, D[4 (l / 16) + r][l % 16] in register r of lane l.  Lane l loads
-// one float4 of its row (row l % 16 of a 16-row subtile) at columns
-// k0 + 4 (l / 16) .. +3; instruction c then uses component c, so the four kk
-// of instruction c are k0 + 4 kk + c, and B is read at the same k.  No
-// transpose of the rows is needed.
+// Dense per-irrep channel mixing on the matrix cores (float32 in and out; the
+// kernels are in linear_split.h).  A destination block of 2l+1 rows per node
+// receives, for each of its sources, src[n, src_row + m, k] B[k, col] summed
+// over k and the sources.  The forward has one job per output block (its
+// sources: the input blocks of the same degree and parity; B = W); dx has one
+// job per input block (its sources: the output blocks it feeds; B = W
+// transposed).
 constexpr int kLinMaxJobs = 64;
 constexpr int kLinChunks = 64;  // row chunks of the dW reduction (fixed: deterministic)
-#ifndef E3_LIN_RT
-#define E3_LIN_RT 4
-#endif
-constexpr int kLinRT = E3_LIN_RT;  // 16-row subtiles per wave in the gather-GEMM
-#ifndef E3_LIN_V4
-#define E3_LIN_V4 1
-#endif
-// Row fetches of the dW kernel in flight while one fetch runs (1 or 2; two
-// measured 1.29 -> 1.23 ms).
-#ifndef E3_LIN_DW_AHEAD
-#define E3_LIN_DW_AHEAD 2
-#endif
-// 1: the gather-GEMM requests the W operands of the next k step with its A
-// rows, instead of at the start of the step that uses them (forward 1.147 ->
-// 1.110 ms, dx 1.39 -> 1.356 ms; the A rows two steps ahead as well measured
-// no better for the forward and 6% slower for dx).
-#ifndef E3_LIN_BPF
-#define E3_LIN_BPF 1
-#endif
 
 struct LinJob {
   int R, dst_row, src_first, nsrc;
@@ -86,170 +59,12 @@ struct LinArgs {
   const LinJob* jobs;
   const LinSrc* srcs;
   int64_t n;
-  int D_src, C_src, D_dst, C_dst, ldk, ldc, njobs, slabs;
+  int D_src, C_src, D_dst, C_dst, njobs, slabs;
   int first[kLinMaxJobs + 1];
 };
 
-// V4 (unit column stride, 16-byte aligned W, C_dst a multiple of 4): lane l
-// owns the four consecutive columns col0 + 4 (l % 16) .. +3, so one float4 of
-// a W row gives B of all four column blocks, and the results leave as float4s.
-template <int RT, bool V4>  // RT subtiles of 16 rows per wave
-__global__ __launch_bounds__(kWave) void k_lin_gemm(LinArgs a) {
-  const int unit = blockIdx.x;
-  int lo = 0, hi = a.njobs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.first[mid] <= unit) lo = mid; else hi = mid - 1;
-  }
-  const LinJob jb = a.jobs[lo];
-  const int u = unit - a.first[lo];
-  const int col0 = (u % a.slabs) * kWave;
-  const int64_t r0 = (int64_t)(u / a.slabs) * (16 * RT);
-  const int64_t NR = a.n * jb.R;
-  const int lane = threadIdx.x, g = lane >> 4, li = lane & 15;
-  f4v acc[RT][4];
-#pragma unroll
-  for (int s = 0; s < RT; ++s)
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) acc[s][cb] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-  int64_t abase[RT];
-  bool aval[RT];
-#pragma unroll
-  for (int s = 0; s < RT; ++s) {
-    const int64_t r = r0 + 16 * s + li;
-    aval[s] = r < NR;
-    const int64_t nd = aval[s] ? r / jb.R : 0, m = aval[s] ? r % jb.R : 0;
-    abase[s] = (nd * a.D_src + m) * a.C_src + 4 * g;
-  }
-  if constexpr (V4) {
-    // Rows past NR and columns past C_dst load in-bounds data of other rows or
-    // read zero; the instruction keeps rows and columns apart and those results
-    // are not stored, so no masking is needed.  The A rows of the next
-    // (source, k-step) load while this one runs.
-    const int colv = col0 + 4 * li;
-    const bool cv = colv < a.C_dst;
-    const ConstPtr<LinSrc> srcs = (ConstPtr<LinSrc>)a.srcs;
-    const int ksteps = a.C_src / 16, nsteps = jb.nsrc * ksteps;
-    const int bvoff = ((4 * g) * a.ldk + colv) * 4;
-    auto load_a = [&](int i, f4v(&v)[RT]) {
-      const int t = i / ksteps;
-      const float* sp = a.src + (int64_t)srcs[jb.src_first + t].row * a.C_src + (i - t * ksteps) * 16;
-#pragma unroll
-      for (int s = 0; s < RT; ++s) v[s] = *reinterpret_cast<const f4v*>(sp + abase[s]);
-    };
-    auto load_b = [&](int i, f4v(&bq)[4]) {
-      const int t = i / ksteps, k0 = (i - t * ksteps) * 16;
-      const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<float*>(a.W + srcs[jb.src_first + t].w_off), (short)0, a.C_src * a.C_dst * 4, 0x00020000);
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        bq[c] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(wr, bvoff, (k0 + c) * a.ldk * 4, 0));
-    };
-    auto mfmas = [&](const f4v(&av)[RT], const f4v(&bq)[4]) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-          for (int s = 0; s < RT; ++s)
-            acc[s][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][c], bq[c][cb], acc[s][cb], 0, 0, 0);
-    };
-    if constexpr (E3_LIN_BPF) {
-      // one (source, k-step): the W and A operands of step i + 1 (clamped, so
-      // the loads are unconditional and the waits count exactly; loads
-      // complete in issue order) are requested, then the 64 instructions run
-      // on the operands of step i, requested one step earlier
-      auto step = [&](int i, const f4v(&av)[RT], const f4v(&bv)[4], f4v(&an)[RT], f4v(&bn)[4]) {
-        const int ni = i + 1 < nsteps ? i + 1 : i;
-        load_b(ni, bn);
-        load_a(ni, an);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(av, bv);
-      };
-      f4v a0[RT], a1[RT], b0[4], b1[4];
-      if (nsteps > 0) load_b(0, b0), load_a(0, a0);
-      for (int i = 0; i < nsteps; i += 2) {
-        step(i, a0, b0, a1, b1);
-        if (i + 1 < nsteps) step(i + 1, a1, b1, a0, b0);
-      }
-    } else {
-      // one (source, k-step): W (cache-resident) first, then the A rows of step
-      // i + 1, then the 64 instructions
-      auto step = [&](int i, const f4v(&av)[RT], f4v(&an)[RT]) {
-        f4v bq[4];
-        load_b(i, bq);
-        __builtin_amdgcn_sched_barrier(0);
-        load_a(i + 1 < nsteps ? i + 1 : i, an);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(av, bq);
-      };
-      f4v a0[RT], a1[RT];
-      if (nsteps > 0) load_a(0, a0);
-      for (int i = 0; i < nsteps; i += 2) {
-        step(i, a0, a1);
-        if (i + 1 < nsteps) step(i + 1, a1, a0);
-      }
-    }
-    // register r of acc[s][cb] in lane l: row 16 s + 4 (l / 16) + r, column col0 + 4 (l % 16) + cb
-    if (!cv) return;
-#pragma unroll
-    for (int s = 0; s < RT; ++s)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = r0 + 16 * s + 4 * g + r;
-        if (row >= NR) continue;
-        const int64_t nd = row / jb.R, m = row % jb.R;
-        float* dp = a.dst + (nd * a.D_dst + jb.dst_row + m) * a.C_dst;
-        *reinterpret_cast<f4v*>(dp + colv) = f4v{acc[s][0][r], acc[s][1][r], acc[s][2][r], acc[s][3][r]};
-      }
-    return;
-  }
-  // B[k][col] = W[w_off + k ldk + col ldc]: per-lane part in the vector offset,
-  // the k step and column block in the (uniform) scalar offset; columns past
-  // C_dst read zero through the range check of a per-source descriptor.
-  const int col = col0 + li;
-  const int bvoff = ((4 * g) * a.ldk + col * a.ldc) * 4;
-  const int ncols_valid = a.C_dst - col0;  // uniform
-  for (int t = 0; t < jb.nsrc; ++t) {
-    const LinSrc sr = a.srcs[jb.src_first + t];
-    const float* sp = a.src + (int64_t)sr.row * a.C_src;
-    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(a.W + sr.w_off), (short)0, a.C_src * a.C_dst * 4, 0x00020000);
-    for (int k0 = 0; k0 < a.C_src; k0 += 16) {
-      f4v av[RT];
-#pragma unroll
-      for (int s = 0; s < RT; ++s)
-        av[s] = aval[s] ? *reinterpret_cast<const f4v*>(sp + abase[s] + k0) : f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-          float bv = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(wr, bvoff, ((k0 + c) * a.ldk + 16 * cb * a.ldc) * 4, 0));
-          if (16 * cb + li >= ncols_valid) bv = 0.0f;
-#pragma unroll
-          for (int s = 0; s < RT; ++s)
-            acc[s][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][c], bv, acc[s][cb], 0, 0, 0);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < RT; ++s)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = r0 + 16 * s + 4 * g + r;
-      if (row >= NR) continue;
-      const int64_t nd = row / jb.R, m = row % jb.R;
-      float* dp = a.dst + (nd * a.D_dst + jb.dst_row + m) * a.C_dst;
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-        if (16 * cb + li < ncols_valid) dp[col0 + 16 * cb + li] = acc[s][cb][r];
-    }
-}
-
 // Wt[pair][j][k] = W[w_off(pair) + k C_out + j]: each dW-sized slice
-// transposed, so that dx reads B along rows.
+// transposed, for a dx whose W is not 16-byte aligned.
 __global__ __launch_bounds__(256) void k_lin_transpose(const float* __restrict__ W, const LinPair* __restrict__ pairs,
                                                         float* __restrict__ Wt, int npairs, int C_in, int C_out) {
   const int64_t per = (int64_t)C_in * C_out;
@@ -261,12 +76,6 @@ __global__ __launch_bounds__(256) void k_lin_transpose(const float* __restrict__
   Wt[i] = W[pairs[p].w_off + (int64_t)k * C_out + j];
 }
 
-// dW partials: one wave per (pair, row chunk, 64 x 64 tile of W).  Per four
-// rows, lane l loads one float4 of x (columns k-tile + 4 (l % 16) .. +3) and
-// one of dout (j-tile + 4 (l % 16) .. +3) of row + l / 16; instruction (a, b)
-// takes component a as A and b as B (the 16x16x4 reduction index kk is the
-// row), so D[a][b][i][j] accumulates x^T dout at k = k-tile + 4 i + a,
-// j = j-tile + 4 j + b.
 struct LinDwArgs {
   const float* x;
   const float* dout;
@@ -275,121 +84,6 @@ struct LinDwArgs {
   int64_t n;
   int D_in, C_in, D_out, C_out, ktiles, jtiles;
 };
-
-__global__ __launch_bounds__(kWave) void k_lin_dw(LinDwArgs a) {
-  const int per = kLinChunks * a.ktiles * a.jtiles;
-  const int p = blockIdx.x / per, u = blockIdx.x % per;
-  const int chunk = u / (a.ktiles * a.jtiles), kt = (u / a.jtiles) % a.ktiles, jt = u % a.jtiles;
-  const LinPair pr = a.pairs[p];
-  const int64_t NR = a.n * pr.R;
-  const int64_t rpc = ((NR + kLinChunks - 1) / kLinChunks + 15) / 16 * 16;  // rows per chunk, a multiple of 16
-  const int64_t rb = chunk * rpc < NR ? chunk * rpc : NR, re = rb + rpc < NR ? rb + rpc : NR;
-  const int lane = threadIdx.x, g = lane >> 4, li = lane & 15;
-  f4v acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-  const int kc = kt * 64 + 4 * li, jc = jt * 64 + 4 * li;  // multiples of 4; C_in, C_out are of 16
-  const bool kv = kc < a.C_in, jv = jc < a.C_out;
-  // Lane rows rb + g, rb + g + 4, ...: the (node, m) position steps by four
-  // rows without a division.  Columns past C_in / C_out read column 0; their
-  // results are not stored.
-  const int R = pr.R, dq = 4 / R, dr = 4 % R;
-  int64_t row = rb + g;
-  int m = (int)(row % R);
-  int64_t ox = ((row / R) * a.D_in + pr.src_row + m) * a.C_in + (kv ? kc : 0);
-  int64_t od = ((row / R) * a.D_out + pr.dst_row + m) * a.C_out + (jv ? jc : 0);
-  const int64_t sx = ((int64_t)dq * a.D_in + dr) * a.C_in, wx = (int64_t)(a.D_in - R) * a.C_in;
-  const int64_t sd = ((int64_t)dq * a.D_out + dr) * a.C_out, wd = (int64_t)(a.D_out - R) * a.C_out;
-  auto advance = [&]() {
-    const bool w = m + dr >= R;
-    row += 4;
-    m += w ? dr - R : dr;
-    ox += w ? sx + wx : sx;
-    od += w ? sd + wd : sd;
-  };
-  auto group = [&](const f4v& xa, const f4v& db) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[i], db[j], acc[i][j], 0, 0, 0);
-  };
-  // Whole fetches of 16 rows (chunks are sized in multiples of 16 rows, so
-  // only the last chunk has a tail): no masking, the next fetch in flight.
-  // Every fetch is unconditional so that the waits count exactly; the one
-  // past the last whole fetch reads row rb again and is not used.
-  constexpr int S = 4;
-  const int64_t nf = (re - rb) / (4 * S), rfull = rb + nf * 4 * S;
-  const int64_t ox0 = ((rb / R) * a.D_in + pr.src_row + rb % R) * a.C_in + (kv ? kc : 0);
-  const int64_t od0 = ((rb / R) * a.D_out + pr.dst_row + rb % R) * a.C_out + (jv ? jc : 0);
-  auto fetch = [&](f4v(&xs)[S], f4v(&ds)[S]) {
-#pragma unroll
-    for (int q = 0; q < S; ++q) {
-      const bool ok = row < rfull;
-      xs[q] = *reinterpret_cast<const f4v*>(a.x + (ok ? ox : ox0));
-      ds[q] = *reinterpret_cast<const f4v*>(a.dout + (ok ? od : od0));
-      advance();
-    }
-  };
-  if (nf > 0 && E3_LIN_DW_AHEAD == 2) {
-    // two fetches in flight while one runs
-    f4v xA[S], dA[S], xB[S], dB[S], xC[S], dC[S];
-    fetch(xA, dA);
-    fetch(xB, dB);
-    for (int64_t f = 0; f < nf; ++f) {
-      fetch(xC, dC);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < S; ++q) group(xA[q], dA[q]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < S; ++q) xA[q] = xB[q], dA[q] = dB[q], xB[q] = xC[q], dB[q] = dC[q];
-    }
-    // the state ran two fetches ahead: step back to the first row after the whole fetches
-    row = rb + g + nf * 4 * S;
-    m = (int)(row % R);
-    ox = ((row / R) * a.D_in + pr.src_row + m) * a.C_in + (kv ? kc : 0);
-    od = ((row / R) * a.D_out + pr.dst_row + m) * a.C_out + (jv ? jc : 0);
-  } else if (nf > 0) {
-    f4v xA[S], dA[S], xB[S], dB[S];
-    fetch(xA, dA);
-    for (int64_t f = 0; f < nf; ++f) {
-      fetch(xB, dB);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < S; ++q) group(xA[q], dA[q]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < S; ++q) xA[q] = xB[q], dA[q] = dB[q];
-    }
-    // the state ran one fetch ahead: step back to the first row after the whole fetches
-    row = rb + g + nf * 4 * S;
-    m = (int)(row % R);
-    ox = ((row / R) * a.D_in + pr.src_row + m) * a.C_in + (kv ? kc : 0);
-    od = ((row / R) * a.D_out + pr.dst_row + m) * a.C_out + (jv ? jc : 0);
-  }
-  // the last chunk's tail: four-row groups, rows past re read as zero
-  for (int64_t r = rb + nf * 4 * S; r < re; r += 4) {
-    const bool ok = row < re;
-    const f4v xa = ok ? *reinterpret_cast<const f4v*>(a.x + ox) : f4v{0.0f, 0.0f, 0.0f, 0.0f};
-    const f4v db = ok ? *reinterpret_cast<const f4v*>(a.dout + od) : f4v{0.0f, 0.0f, 0.0f, 0.0f};
-    group(xa, db);
-    advance();
-  }
-  // register r of acc[a][b] in lane l: k = k-tile + 4 (4 (l / 16) + r) + a, j = j-tile + 4 (l % 16) + b
-  float* out = a.dWp + ((int64_t)p * kLinChunks + chunk) * a.C_in * a.C_out;
-  if (!jv) return;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = kt * 64 + 4 * (4 * g + r) + i;
-      if (k >= a.C_in) continue;
-      f4v v{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
-      *reinterpret_cast<f4v*>(out + (int64_t)k * a.C_out + jc) = v;
-    }
-}
 
 // dW[w_off(p) + e] = sum over the row chunks of pair p, in chunk order.
 __global__ __launch_bounds__(256) void k_lin_dw_sum(const float* __restrict__ dWp, const LinPair* __restrict__ pairs,
@@ -403,6 +97,9 @@ __global__ __launch_bounds__(256) void k_lin_dw_sum(const float* __restrict__ dW
   dW[pairs[p].w_off + e] = s;
 }
 
+}  // namespace
+#include "linear_split.h"
+namespace {
 
 // ------------------------------------------------------------ generic records
 // Tensor product with caller-supplied records (App. E.2's unfolded form):
@@ -1616,27 +1313,32 @@ e3_status check_device(int device, const char* what) {
   return E3_OK;
 }
 
+// Tile width of an operand of C columns: the one of 64 and 128 with fewer padded ones.
+int lin_tile(int C) { return (C + 63) / 64 % 2 ? 64 : 128; }
+constexpr int kLinRows = 128;  // rows of a gather-GEMM tile
+
+// wt: W is read transposed ([col][k], 16-byte aligned).
 e3_status lin_gemm(const std::vector<LinJob>& jobs, const LinJob* djobs, const LinSrc* dsrcs, const float* src,
-                   const float* W, float* dst, int64_t n, int D_src, int C_src, int D_dst, int C_dst, int ldk, int ldc,
+                   const float* W, bool wt, float* dst, int64_t n, int D_src, int C_src, int D_dst, int C_dst,
                    const char* name, hipStream_t st) {
+  const int bn = lin_tile(C_dst);
   LinArgs a{};
   a.src = src, a.W = W, a.dst = dst, a.jobs = djobs, a.srcs = dsrcs, a.n = n;
-  a.D_src = D_src, a.C_src = C_src, a.D_dst = D_dst, a.C_dst = C_dst, a.ldk = ldk, a.ldc = ldc;
+  a.D_src = D_src, a.C_src = C_src, a.D_dst = D_dst, a.C_dst = C_dst;
   a.njobs = (int)jobs.size();
-  a.slabs = (C_dst + kWave - 1) / kWave;
+  a.slabs = (C_dst + bn - 1) / bn;
   int64_t u = 0;
   for (size_t j = 0; j < jobs.size(); ++j) {
     a.first[j] = (int)u;
-    u += (n * jobs[j].R + 16 * kLinRT - 1) / (16 * kLinRT) * a.slabs;
+    u += (n * jobs[j].R + kLinRows - 1) / kLinRows * a.slabs;
   }
   a.first[jobs.size()] = (int)u;
   if (u == 0) return E3_OK;
   if (u > 0x7fffffff) return E3_ERR_INVALID_ARG;
+  auto* k = wt ? (bn == 128 ? k_lin_gemm<kLinRows, 128, true> : k_lin_gemm<kLinRows, 64, true>)
+               : (bn == 128 ? k_lin_gemm<kLinRows, 128, false> : k_lin_gemm<kLinRows, 64, false>);
   TimedLaunch t_(name, st);
-  if (ldc == 1 && C_dst % 4 == 0 && aligned16(W) && E3_LIN_V4)
-    hipLaunchKernelGGL((k_lin_gemm<kLinRT, true>), dim3((unsigned)u), dim3(kWave), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_lin_gemm<kLinRT, false>), dim3((unsigned)u), dim3(kWave), 0, st, a);
+  hipLaunchKernelGGL(k, dim3((unsigned)u), dim3(kSpThreads), 0, st, a);
   E3_HIP(hipGetLastError());
   return E3_OK;
 }
@@ -1734,8 +1436,8 @@ e3_status e3_linear_fwd(e3_linear* L, const float* x, const float* W, float* out
   e3_status s = check_device(L->device, "linear mixing handle");
   if (s != E3_OK) return s;
   return lin_gemm(L->fj, reinterpret_cast<const LinJob*>(L->dev + L->off_fj),
-                  reinterpret_cast<const LinSrc*>(L->dev + L->off_fs), x, W, out, n, L->d_in, L->c_in, L->d_out,
-                  L->c_out, L->c_out, 1, "linear_fwd", st);
+                  reinterpret_cast<const LinSrc*>(L->dev + L->off_fs), x, W, false, out, n, L->d_in, L->c_in,
+                  L->d_out, L->c_out, "linear_fwd", st);
 }
 
 e3_status e3_linear_workspace_size(const e3_linear* L, size_t* bwd_bytes) {
@@ -1758,15 +1460,16 @@ e3_status e3_linear_bwd(e3_linear* L, const float* x, const float* W, const floa
   if (n > 0) {
     // slices of Wt sit at the same offsets as those of W (pair order)
     float* Wt = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + lin_ws_dwp(L));
-    if (!L->pairs.empty()) {
+    const bool wt = aligned16(W);
+    if (!L->pairs.empty() && !wt) {
       TimedLaunch t_("linear_bwd_transpose", st);
       hipLaunchKernelGGL(k_lin_transpose, dim3(blocks_for(L->nw, 256)), dim3(256), 0, st, W, dp, Wt,
                          (int)L->pairs.size(), L->c_in, L->c_out);
       E3_HIP(hipGetLastError());
     }
     s = lin_gemm(L->bj, reinterpret_cast<const LinJob*>(L->dev + L->off_bj),
-                 reinterpret_cast<const LinSrc*>(L->dev + L->off_bs), dout, Wt, dx, n, L->d_out, L->c_out, L->d_in,
-                 L->c_in, L->c_in, 1, "linear_bwd_dx", st);
+                 reinterpret_cast<const LinSrc*>(L->dev + L->off_bs), dout, wt ? W : Wt, wt, dx, n, L->d_out,
+                 L->c_out, L->d_in, L->c_in, "linear_bwd_dx", st);
     if (s != E3_OK) return s;
   }
   if (L->pairs.empty()) return E3_OK;
@@ -1774,11 +1477,14 @@ e3_status e3_linear_bwd(e3_linear* L, const float* x, const float* W, const floa
   LinDwArgs a{};
   a.x = x, a.dout = dout, a.dWp = dWp, a.pairs = dp, a.n = n;
   a.D_in = L->d_in, a.C_in = L->c_in, a.D_out = L->d_out, a.C_out = L->c_out;
-  a.ktiles = (L->c_in + 63) / 64, a.jtiles = (L->c_out + 63) / 64;
+  const int km = lin_tile(L->c_in), jm = lin_tile(L->c_out);
+  a.ktiles = (L->c_in + km - 1) / km, a.jtiles = (L->c_out + jm - 1) / jm;
   {
+    auto* k = km == 128 ? (jm == 128 ? k_lin_dw<128, 128> : k_lin_dw<128, 64>)
+                        : (jm == 128 ? k_lin_dw<64, 128> : k_lin_dw<64, 64>);
     TimedLaunch t_("linear_bwd_dw", st);
     const int64_t units = (int64_t)L->pairs.size() * kLinChunks * a.ktiles * a.jtiles;
-    hipLaunchKernelGGL(k_lin_dw, dim3((unsigned)units), dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL(k, dim3((unsigned)units), dim3(kSpThreads), 0, st, a);
     E3_HIP(hipGetLastError());
   }
   {

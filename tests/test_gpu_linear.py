@@ -1,0 +1,115 @@
+"""The linear mixing's tiles and operand splitting at their edges, against
+float64: row remainders of the 128-row tile, channel counts on either side of
+the 64- and 128-wide tiles, odd counts of 16-wide reduction halves, several
+blocks per type, W off 16-byte alignment; operands over the whole float32
+range; infinities and NaNs where float32 has them.
+
+Bar: relative L2 1e-6 per output (sums of at most 1,500 terms, about 16
+roundings of 6e-8; the splitting itself adds under 2^-25).
+"""
+import numpy as np
+import pytest
+
+from gpu_util import rel_l2, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def e3():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2609_35099_amd import e3mi
+    e3mi.lib()
+    return e3mi
+
+
+def _blocks(irreps):
+    out, row = [], 0
+    for tok in irreps.split("+"):
+        l = int(tok[:-1])
+        out.append((tok, row, 2 * l + 1))
+        row += 2 * l + 1
+    return out, row
+
+
+def _reference(ins, outs, ci, co, x, W, d):
+    """out, dx, dW in float64."""
+    (bi, di), (bo, do) = _blocks(ins), _blocks(outs)
+    out, dx, dW, o = np.zeros((len(x), do, co)), np.zeros((len(x), di, ci)), [], 0
+    for to, ro, n in bo:
+        for ti, ri, _ in bi:
+            if ti == to:
+                w = W[o:o + ci * co].reshape(ci, co)
+                xi, dd = x[:, ri:ri + n], d[:, ro:ro + n]
+                out[:, ro:ro + n] += xi @ w
+                dx[:, ri:ri + n] += dd @ w.T
+                dW.append((xi.reshape(-1, ci).T @ dd.reshape(-1, co)).reshape(-1))
+                o += ci * co
+    return out, dx, np.concatenate(dW) if dW else np.zeros(0)
+
+
+def _run(e3, ins, outs, ci, co, x, W, d, shift=0):
+    import torch
+    L = e3.Linear("+".join(f"{ci}x{t}" for t in ins.split("+")), "+".join(f"{co}x{t}" for t in outs.split("+")))
+    buf = torch.empty(len(W) + 4, device="cuda")
+    Wd = buf[shift:shift + len(W)]
+    Wd.copy_(torch.from_numpy(W))
+    xd, dd = torch.from_numpy(x).cuda(), torch.from_numpy(d).cuda()
+    print("[case]", ins, outs, ci, co, len(x), shift, flush=True)
+    return [to_np(t) for t in (L.forward(xd, Wd), *L.backward(xd, Wd, dd))]
+
+
+def _inputs(ins, outs, ci, co, n, seed=1):
+    rng = np.random.default_rng(seed)
+    (bi, di), (bo, do) = _blocks(ins), _blocks(outs)
+    nw = sum(ti[0] == to[0] for ti in bi for to in bo) * ci * co
+    return [rng.standard_normal(s).astype(np.float32) for s in ((n, di, ci), (nw,), (n, do, co))]
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("ins,outs,ci,co,n", [
+    ("0e", "0e", 16, 16, 1), ("0e+1o", "1o+0e", 16, 48, 43), ("1o+1o+0e", "1o+0e", 48, 64, 128),
+    ("0e", "0e", 64, 80, 129), ("0e+1o+2e+0e", "0e+2e+1o+1o", 80, 128, 77), ("3o+1o", "1o+3o", 128, 144, 300),
+    ("1o+1o+1o", "1o", 112, 192, 127), ("0e+1e", "0e+1o", 256, 16, 1000), ("2e+70e", "70e+2e", 16, 32, 11),
+    ("0e+0e", "0e+0e", 96, 96, 9000),
+])
+def test_linear_tiles(e3, ins, outs, ci, co, n, shift):
+    x, W, d = _inputs(ins, outs, ci, co, n)
+    got = _run(e3, ins, outs, ci, co, x, W, d, shift)
+    for g, r in zip(got, _reference(ins, outs, ci, co, *(a.astype(np.float64) for a in (x, W, d)))):
+        assert rel_l2(g, r) < 1e-6
+
+
+@pytest.mark.parametrize("sx,sw", [(1e-37, 1.0), (1.0, 1e-37), (1e-30, 1e20), (1e-19, 1e-19), (1e26, 1e-3),
+                                   (1e33, 1e-20), (1e-12, 1e33), (1e36, 1.0)])
+def test_linear_magnitudes(e3, sx, sw):
+    """Operands from the subnormals to the largest floats (the last ones take the float32 instruction)."""
+    ins = outs = "0e+1o"
+    x, W, d = _inputs(ins, outs, 128, 64, 150)
+    x, W = (np.clip(x, -3, 3) * np.float32(sx)).astype(np.float32), (np.clip(W, -3, 3) * np.float32(sw)).astype(np.float32)
+    got = _run(e3, ins, outs, 128, 64, x, W, d)
+    for g, r in zip(got, _reference(ins, outs, 128, 64, *(a.astype(np.float64) for a in (x, W, d)))):
+        assert np.isfinite(r).all() and np.abs(r).max() < 3e38
+        top = np.abs(r).max()
+        assert rel_l2(g.astype(np.float64) / top, r / top) < 1e-6
+
+
+def test_linear_infinities_and_nans(e3):
+    ins = outs = "0e+1o"
+    x, W, d = _inputs(ins, outs, 64, 128, 400)
+    x[5, 0, 7], x[9, 2, 3], x[300, 0, 1], x[300, 0, 2] = np.inf, np.nan, np.inf, -np.inf
+    x[11, 1, 0], d[20, 3, 5] = 3.4e38, -np.inf
+    W = (W / 8).astype(np.float32)
+    W[9] = 0.0
+    got = _run(e3, ins, outs, 64, 128, x, W, d)
+    with np.errstate(all="ignore"):
+        ref = _reference(ins, outs, 64, 128, *(a.astype(np.float64) for a in (x, W, d)))
+    for g, r in zip(got, ref):
+        r = np.where(np.abs(r) > np.finfo(np.float32).max, np.sign(r) * np.inf, r)
+        assert (np.isnan(g) == np.isnan(r)).all()
+        inf = np.isinf(r)
+        assert (np.isinf(g) == inf).all() and (np.sign(g[inf]) == np.sign(r[inf])).all()
+        ok = np.isfinite(r) & (np.abs(r) < 1e30)
+        assert rel_l2(g[ok], r[ok]) < 1e-6
