@@ -367,13 +367,36 @@ __global__ void k_graph_keys(const int32_t* __restrict__ snd, const int32_t* __r
 //   + (same-digit elements of lower lanes of its wave),
 // so equal digits keep their input order and every pass is stable.  Integer
 // counts only: the result does not depend on scheduling.
-constexpr int kSortBlock = 256, kSortRounds = 16, kSortTile = kSortBlock * kSortRounds;
+//
+// The receiver and the sender sort run in the same launches (blockIdx.y).  A
+// tile has 4 rounds up to kSortLarge elements, where its rounds are a serial
+// chain in a launch that does not fill the chip, and 16 beyond, where shorter
+// tiles would lengthen the scan.
+constexpr int kSortBlock = 256;
+constexpr int64_t kSortLarge = 4 << 20;
+inline int64_t sort_tiles(int64_t n) {
+  const int64_t tile = (int64_t)kSortBlock * (n <= kSortLarge ? 4 : 16);
+  return (n + tile - 1) / tile;
+}
 constexpr int kSortWaves = kSortBlock / kWave;
 static_assert(kSortBlock == 256, "one thread per digit");
 
-__global__ __launch_bounds__(kSortBlock) void k_sort_hist(const uint32_t* __restrict__ keys, int64_t n, int shift,
-                                                          int64_t n_tiles, int32_t* __restrict__ count) {
+// One pass of the two sorts; iin == nullptr: the ids are the element indices.
+// count: 256 x tiles tile counts, then 256 digit totals.
+struct SortPass {
+  const uint32_t* kin[2];
+  const int32_t* iin[2];
+  uint32_t* kout[2];
+  int32_t* iout[2];
+  int32_t* count[2];
+};
+
+template <int ROUNDS>
+__global__ __launch_bounds__(kSortBlock) void k_sort_hist(SortPass a, int64_t n, int shift, int64_t n_tiles) {
+  constexpr int kSortRounds = ROUNDS, kSortTile = kSortBlock * ROUNDS;
   __shared__ int hist[256];
+  const uint32_t* __restrict__ keys = a.kin[blockIdx.y];
+  int32_t* __restrict__ count = a.count[blockIdx.y];
   const int tid = threadIdx.x;
   hist[tid] = 0;
   __syncthreads();
@@ -407,9 +430,9 @@ __device__ __forceinline__ int32_t block_incl_scan(int32_t v, int32_t (&buf)[2][
 
 // Per digit (one block each): exclusive scan of its tiles' counts in place
 // (row d of count) and the digit's total.
-__global__ __launch_bounds__(kSortBlock) void k_sort_scan(int32_t* __restrict__ count, int64_t n_tiles,
-                                                          int32_t* __restrict__ total) {
+__global__ __launch_bounds__(kSortBlock) void k_sort_scan(SortPass a, int64_t n_tiles) {
   __shared__ int32_t buf[2][kSortBlock];
+  int32_t *count = a.count[blockIdx.y], *total = count + 256 * n_tiles;
   const int tid = threadIdx.x;
   int32_t* row = count + (int64_t)blockIdx.x * n_tiles;
   int32_t carry = 0;
@@ -424,15 +447,18 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_scan(int32_t* __restrict__ 
   if (tid == 0) total[blockIdx.x] = carry;
 }
 
-// ids_in == nullptr: the ids are the element indices.  Positions outside
-// [0, n) cannot arise from consistent offsets; they are refused (bad = 1)
-// rather than written.
-__global__ __launch_bounds__(kSortBlock) void k_sort_scatter(const uint32_t* __restrict__ keys_in,
-                                                             const int32_t* __restrict__ ids_in, int64_t n, int shift,
-                                                             int64_t n_tiles, const int32_t* __restrict__ off,
-                                                             const int32_t* __restrict__ total,
-                                                             uint32_t* __restrict__ keys_out,
-                                                             int32_t* __restrict__ ids_out, int* __restrict__ bad) {
+// Positions outside [0, n) cannot arise from consistent offsets; they are
+// refused (bad = 1) rather than written.
+template <int ROUNDS>
+__global__ __launch_bounds__(kSortBlock) void k_sort_scatter(SortPass a, int64_t n, int shift, int64_t n_tiles,
+                                                             int* __restrict__ bad) {
+  constexpr int kSortRounds = ROUNDS, kSortTile = kSortBlock * ROUNDS;
+  const uint32_t* __restrict__ keys_in = a.kin[blockIdx.y];
+  const int32_t* __restrict__ ids_in = a.iin[blockIdx.y];
+  const int32_t* __restrict__ off = a.count[blockIdx.y];
+  const int32_t* __restrict__ total = off + 256 * n_tiles;
+  uint32_t* __restrict__ keys_out = a.kout[blockIdx.y];
+  int32_t* __restrict__ ids_out = a.iout[blockIdx.y];
   __shared__ int running[256];
   __shared__ int cnt[kSortWaves][256];
   __shared__ int32_t buf[2][kSortBlock];
@@ -484,11 +510,14 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_scatter(const uint32_t* __r
   }
 }
 
-// rowptr[b] = first position with key >= b (binary search; keys sorted).
-__global__ void k_graph_rowptr(const uint32_t* __restrict__ keys, int64_t n_edges, int32_t n_nodes,
-                               int32_t* __restrict__ rowptr) {
+// rowptr[b] = first position with key >= b (binary search; keys sorted), for
+// both sorts; the receiver one also reports the live edges, rowptr[n_nodes].
+__global__ void k_graph_rowptr(const uint32_t* __restrict__ keys_r, const uint32_t* __restrict__ keys_s,
+                               int64_t n_edges, int32_t n_nodes, int32_t* __restrict__ rowptr_r,
+                               int32_t* __restrict__ rowptr_s, int* __restrict__ n_live) {
   const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (b > n_nodes) return;
+  const uint32_t* keys = blockIdx.y ? keys_s : keys_r;
   int64_t lo = 0, hi = n_edges;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
@@ -497,22 +526,25 @@ __global__ void k_graph_rowptr(const uint32_t* __restrict__ keys, int64_t n_edge
     else
       hi = mid;
   }
-  rowptr[b] = (int32_t)lo;
+  (blockIdx.y ? rowptr_s : rowptr_r)[b] = (int32_t)lo;
+  if (blockIdx.y == 0 && b == n_nodes) *n_live = (int)lo;
 }
 
+// flag: index out of range, inconsistent offsets (the ids are then not
+// followed), live edges.
 __global__ void k_graph_finish(const int32_t* __restrict__ snd, const int32_t* __restrict__ eid_r,
-                               const int32_t* __restrict__ eid_s, int64_t n_live, int32_t* __restrict__ src_r,
-                               int32_t* __restrict__ pos_s) {
+                               const int32_t* __restrict__ eid_s, const int* __restrict__ flag,
+                               int32_t* __restrict__ src_r, int32_t* __restrict__ pos_s) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_live) return;
+  if (flag[1] || i >= flag[2]) return;
   src_r[i] = snd[eid_r[i]];
   pos_s[eid_s[i]] = (int32_t)i;
 }
 
-__global__ void k_graph_r2s(const int32_t* __restrict__ eid_r, const int32_t* __restrict__ pos_s, int64_t n_live,
-                            int32_t* __restrict__ r2s) {
+__global__ void k_graph_r2s(const int32_t* __restrict__ eid_r, const int32_t* __restrict__ pos_s,
+                            const int* __restrict__ flag, int32_t* __restrict__ r2s) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_live) return;
+  if (flag[1] || i >= flag[2]) return;
   r2s[i] = pos_s[eid_r[i]];
 }
 
@@ -725,27 +757,29 @@ e3_status e3_sh_host(int lmax, const double* u, double* y, int64_t n) {
 }
 
 namespace {
-// Stable sort of keys[0, n) < 2^nbits with their element indices as ids:
-// ceil(nbits / 8) passes ping-ponging between (tk, ti) and the outputs, so that
-// the last lands in (keys_out, ids_out).  count holds 256 * (tiles + 1) ints
-// (the tile counts, then the digit totals).
-hipError_t sort_pairs(const uint32_t* keys, int64_t n, int nbits, uint32_t* keys_out, int32_t* ids_out,
-                      uint32_t* tk, int32_t* ti, int32_t* count, int* bad, hipStream_t st) {
-  const int64_t tiles = (n + kSortTile - 1) / kSortTile;
+// Both sorts of the graph build: ceil(nbits / 8) passes ping-ponging between
+// (tk, ti) and the outputs, so that the last lands in (keys_out, ids_out).
+struct SortBufs {
+  uint32_t *keys, *keys_out, *tk;
+  int32_t *ids_out, *ti, *count;  // count: 256 * (sort_tiles(n) + 1)
+};
+hipError_t sort_pairs(const SortBufs (&s)[2], int64_t n, int nbits, int* bad, hipStream_t st) {
+  const int64_t tiles = sort_tiles(n);
   const int passes = (nbits + 7) / 8;
-  const uint32_t* kin = keys;
-  const int32_t* iin = nullptr;
+  SortPass a{};
+  for (int k = 0; k < 2; ++k) a.kin[k] = s[k].keys, a.iin[k] = nullptr, a.count[k] = s[k].count;
   for (int p = 0; p < passes; ++p) {
     const bool to_out = ((passes - 1 - p) % 2) == 0;
-    uint32_t* kout = to_out ? keys_out : tk;
-    int32_t* iout = to_out ? ids_out : ti;
-    hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, kin, n, 8 * p, tiles, count);
-    hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(kSortBlock), 0, st, count, tiles, count + 256 * tiles);
-    hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)tiles), dim3(kSortBlock), 0, st, kin, iin, n, 8 * p, tiles,
-                       count, count + 256 * tiles, kout, iout, bad);
+    for (int k = 0; k < 2; ++k)
+      a.kout[k] = to_out ? s[k].keys_out : s[k].tk, a.iout[k] = to_out ? s[k].ids_out : s[k].ti;
+    const dim3 grid((unsigned)tiles, 2), block(kSortBlock);
+    const bool few = n <= kSortLarge;
+    hipLaunchKernelGGL(few ? k_sort_hist<4> : k_sort_hist<16>, grid, block, 0, st, a, n, 8 * p, tiles);
+    hipLaunchKernelGGL(k_sort_scan, dim3(256, 2), block, 0, st, a, tiles);
+    hipLaunchKernelGGL(few ? k_sort_scatter<4> : k_sort_scatter<16>, grid, block, 0, st, a, n, 8 * p, tiles, bad);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    kin = kout, iin = iout;
+    for (int k = 0; k < 2; ++k) a.kin[k] = a.kout[k], a.iin[k] = a.iout[k];
   }
   return hipSuccess;
 }
@@ -767,94 +801,71 @@ e3_status e3_graph_create(const int32_t* sender, const int32_t* receiver, int64_
     e3_graph_destroy(g);
     return s;
   };
-  auto alloc = [&](void** p, size_t bytes) -> bool {
-    if (hipMalloc(p, std::max<size_t>(bytes, 4)) != hipSuccess) {
-      g_last_error = "hipMalloc failed in e3_graph_create";
-      return false;
-    }
-    return true;
-  };
-  if (!alloc((void**)&g->rowptr_r, (N + 1) * 4) || !alloc((void**)&g->rowptr_s, (N + 1) * 4) ||
-      !alloc((void**)&g->eid_r, E * 4) || !alloc((void**)&g->eid_s, E * 4) || !alloc((void**)&g->src_r, E * 4) ||
-      !alloc((void**)&g->r2s, E * 4) || !alloc((void**)&g->pos_s, E * 4))
-    return fail(E3_ERR_ALLOC);
-  uint32_t *key_r = nullptr, *key_s = nullptr, *key_sorted = nullptr, *tk = nullptr;
-  int32_t *ti = nullptr, *count = nullptr;
-  int* flag = nullptr;
-  auto cleanup = [&]() {
-    (void)hipFree(key_r), (void)hipFree(key_s), (void)hipFree(key_sorted), (void)hipFree(tk), (void)hipFree(ti),
-        (void)hipFree(count), (void)hipFree(flag);
-  };
-  const int64_t tiles = (E + kSortTile - 1) / kSortTile;
-  if (!alloc((void**)&key_r, E * 4) || !alloc((void**)&key_s, E * 4) || !alloc((void**)&key_sorted, E * 4) ||
-      !alloc((void**)&tk, E * 4) || !alloc((void**)&ti, E * 4) || !alloc((void**)&count, 256 * (tiles + 1) * 4) ||
-      !alloc((void**)&flag, 2 * sizeof(int))) {
-    cleanup();
-    return fail(E3_ERR_ALLOC);
+  // One allocation for the graph's arrays and one for the sorts' temporaries:
+  // 14 of them, their frees and a second wait took most of a small graph's
+  // build (1,503 atoms, 87,000 edges: build and destruction together about 205 ->
+  // 105 us, with the sorts' shorter tiles and shared launches).  The arrays that
+  // are written last serve the sorts first.
+  const size_t nb = align256((size_t)(N + 1) * 4), eb = align256(std::max<size_t>((size_t)E * 4, 4));
+  const int64_t tiles = sort_tiles(E);
+  const size_t cb = align256((size_t)256 * (tiles + 1) * 4);
+  char* tmp = nullptr;
+  if (hipMalloc(&g->mem, 2 * nb + 5 * eb) != hipSuccess || hipMalloc((void**)&tmp, 5 * eb + 2 * cb + 256) != hipSuccess) {
+    g_last_error = "hipMalloc failed in e3_graph_create";
+    return fail(E3_ERR_ALLOC);  // tmp is the last to be allocated
   }
+  auto take = [](char*& at, size_t bytes) {
+    char* p = at;
+    at += bytes;
+    return reinterpret_cast<int32_t*>(p);
+  };
+  char* at = static_cast<char*>(g->mem);
+  g->rowptr_r = take(at, nb), g->rowptr_s = take(at, nb);
+  g->eid_r = take(at, eb), g->eid_s = take(at, eb), g->src_r = take(at, eb), g->r2s = take(at, eb);
+  g->pos_s = take(at, eb);
+  at = tmp;
+  auto key = [&]() { return reinterpret_cast<uint32_t*>(take(at, eb)); };
+  SortBufs sb[2];
+  sb[0] = {key(), key(), reinterpret_cast<uint32_t*>(g->src_r), g->eid_r, g->r2s, nullptr};
+  sb[1] = {key(), key(), key(), g->eid_s, g->pos_s, nullptr};
+  sb[0].count = take(at, cb), sb[1].count = take(at, cb);
+  int* flag = take(at, 256);  // index out of range, inconsistent offsets, live edges
   // keys are receivers (senders) in [0, N), padding edges N
   int end_bit = 1;
   while (end_bit < 32 && ((int64_t)1 << end_bit) <= N) ++end_bit;
-  hipError_t herr = hipSuccess;
-  herr = hipMemsetAsync(flag, 0, 2 * sizeof(int), st);
+  hipError_t herr = hipMemsetAsync(flag, 0, 3 * sizeof(int), st);
   if (herr == hipSuccess && E > 0) {
     hipLaunchKernelGGL(k_graph_keys, dim3(blocks_for(E, 256)), dim3(256), 0, st, sender, receiver, E, (int32_t)N,
-                       pad_node, key_r, key_s, flag);
+                       pad_node, sb[0].keys, sb[1].keys, flag);
     herr = hipGetLastError();
-    if (herr == hipSuccess)
-      herr = sort_pairs(key_r, E, end_bit, key_sorted, g->eid_r, tk, ti, count, flag + 1, st);
+    if (herr == hipSuccess) herr = sort_pairs(sb, E, end_bit, flag + 1, st);
     if (herr == hipSuccess) {
-      hipLaunchKernelGGL(k_graph_rowptr, dim3(blocks_for(N + 1, 256)), dim3(256), 0, st, key_sorted, E, (int32_t)N,
-                         g->rowptr_r);
-      herr = hipGetLastError();
-    }
-    if (herr == hipSuccess)
-      herr = sort_pairs(key_s, E, end_bit, key_sorted, g->eid_s, tk, ti, count, flag + 1, st);
-    if (herr == hipSuccess) {
-      hipLaunchKernelGGL(k_graph_rowptr, dim3(blocks_for(N + 1, 256)), dim3(256), 0, st, key_sorted, E, (int32_t)N,
-                         g->rowptr_s);
+      hipLaunchKernelGGL(k_graph_rowptr, dim3(blocks_for(N + 1, 256), 2), dim3(256), 0, st, sb[0].keys_out,
+                         sb[1].keys_out, E, (int32_t)N, g->rowptr_r, g->rowptr_s, flag + 2);
+      hipLaunchKernelGGL(k_graph_finish, dim3(blocks_for(E, 256)), dim3(256), 0, st, sender, g->eid_r, g->eid_s,
+                         flag, g->src_r, g->pos_s);
+      hipLaunchKernelGGL(k_graph_r2s, dim3(blocks_for(E, 256)), dim3(256), 0, st, g->eid_r, g->pos_s, flag,
+                         g->r2s);
       herr = hipGetLastError();
     }
   } else if (herr == hipSuccess) {
-    herr = hipMemsetAsync(g->rowptr_r, 0, (N + 1) * 4, st);
-    if (herr == hipSuccess) herr = hipMemsetAsync(g->rowptr_s, 0, (N + 1) * 4, st);
+    herr = hipMemsetAsync(g->rowptr_r, 0, 2 * nb, st);
   }
   int host[3] = {0, 0, 0};
-  if (herr == hipSuccess) herr = hipMemcpyAsync(&host[0], flag, 2 * sizeof(int), hipMemcpyDeviceToHost, st);
-  if (herr == hipSuccess) herr = hipMemcpyAsync(&host[2], g->rowptr_r + N, sizeof(int), hipMemcpyDeviceToHost, st);
+  if (herr == hipSuccess) herr = hipMemcpyAsync(host, flag, 3 * sizeof(int), hipMemcpyDeviceToHost, st);
   if (herr == hipSuccess) herr = hipStreamSynchronize(st);
+  (void)hipFree(tmp);
   if (herr != hipSuccess) {
     g_last_error = std::string("e3_graph_create: ") + hipGetErrorString(herr);
-    cleanup();
     return fail(E3_ERR_HIP);
   }
-  if (host[0]) {
-    cleanup();
-    return fail(E3_ERR_INDEX_OUT_OF_RANGE);
-  }
+  if (host[0]) return fail(E3_ERR_INDEX_OUT_OF_RANGE);
   if (host[1]) {
     g_last_error = "e3_graph_create: inconsistent sort offsets";
-    cleanup();
     return fail(E3_ERR_HIP);
   }
   g->n_live = host[2];
   g->n_pad = E - g->n_live;
-  if (g->n_live > 0) {
-    hipLaunchKernelGGL(k_graph_finish, dim3(blocks_for(g->n_live, 256)), dim3(256), 0, st, sender, g->eid_r, g->eid_s,
-                       g->n_live, g->src_r, g->pos_s);
-    herr = hipGetLastError();
-    if (herr == hipSuccess) {
-      hipLaunchKernelGGL(k_graph_r2s, dim3(blocks_for(g->n_live, 256)), dim3(256), 0, st, g->eid_r, g->pos_s,
-                         g->n_live, g->r2s);
-      herr = hipGetLastError();
-    }
-    if (herr == hipSuccess) herr = hipStreamSynchronize(st);  // temporaries are freed below
-  }
-  cleanup();
-  if (herr != hipSuccess) {
-    g_last_error = std::string("e3_graph_create: ") + hipGetErrorString(herr);
-    return fail(E3_ERR_HIP);
-  }
   *out = g;
   return E3_OK;
 }
@@ -877,8 +888,7 @@ e3_status e3_graph_export(const e3_graph* g, int32_t* perm_r, int32_t* rowptr_r,
 
 e3_status e3_graph_destroy(e3_graph* g) {
   if (!g) return E3_OK;
-  (void)hipFree(g->rowptr_r), (void)hipFree(g->eid_r), (void)hipFree(g->src_r), (void)hipFree(g->r2s);
-  (void)hipFree(g->rowptr_s), (void)hipFree(g->eid_s), (void)hipFree(g->pos_s);
+  (void)hipFree(g->mem);
   delete g;
   return E3_OK;
 }

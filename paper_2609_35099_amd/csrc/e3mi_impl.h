@@ -2435,6 +2435,7 @@ struct e3_plan {
 struct e3_graph {
   int64_t n_nodes = 0, n_edges = 0, n_live = 0, n_pad = 0;
   int32_t pad = -1;
+  void* mem = nullptr;          // the one allocation behind the arrays below
   int32_t* rowptr_r = nullptr;  // [N+1]
   int32_t* eid_r = nullptr;     // [E] (live first, then padding edges by id)
   int32_t* src_r = nullptr;     // [n_live]
