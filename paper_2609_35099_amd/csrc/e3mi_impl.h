@@ -664,6 +664,8 @@ struct ConvArgs {
   int chunk;  // receivers per XCD
   int C;
   int nslab;  // channel slabs of 64 lanes x CPL channels
+  int c0;     // plain sweeps: first channel of the launch's first slab
+  int nsd;    // backward sweep: slabs of a harmonic-partial slot (all launches')
   const float* y;  // harmonics [E, D_sh] given by the caller, or null: from vec
   int accum;       // add to m (forward) / ds (backward) instead of overwriting it
   // backward: bytes of one ds / T row, or 0 when that output is not wanted (the
@@ -721,7 +723,8 @@ __device__ __forceinline__ void fwd_task(const ConvArgs& a, int b, int sl, float
   using F = typename V::template FG<G>;
   const int lane = threadIdx.x;
   int ch0, lanes;
-  slab_of<CPL>(a.C, sl, ch0, lanes);
+  slab_of<CPL>(a.C - a.c0, sl, ch0, lanes);
+  ch0 += a.c0;
   const bool act = lane < lanes;
   const int C = a.C, q = ch0 + lane * CPL;
   const int e0 = uniform(a.rowptr[b]), e1 = uniform(a.rowptr[b + 1]);
@@ -923,7 +926,7 @@ __global__ __launch_bounds__(2 * kWave, E3_FWD_MIN_WAVES) void k_conv_fwd3(ConvA
 template <class V>
 size_t fwd3_lds_bytes(const ConvArgs& a) { return (size_t)2 * a.fb * V::MAX_NA_F * sizeof(float); }
 
-template <class V, int G, int CPL, bool ACC>
+template <class V, int G, int CPL, bool ACC, bool CACHED>
 __device__ __forceinline__ void bwd_task(const ConvArgs& a, int b, int sl, float* sA, float* sY) {
   using B = typename V::template BG<G>;
   const int lane = threadIdx.x;
@@ -971,7 +974,7 @@ __device__ __forceinline__ void bwd_task(const ConvArgs& a, int b, int sl, float
       const int64_t e = __builtin_amdgcn_readlane(my_e, j);
       const RowBuf sb_ = row_buf(a.s + e * p_rows<V>(a) * C, (int64_t)V::NP * C * 4, q, C);
 #pragma unroll
-      for (int i = 0; i < B::NPATH; ++i) bld<CPL, kNT>(sb_, B::PATH[i], sv[i]);
+      for (int i = 0; i < B::NPATH; ++i) bld<CPL, CACHED ? 0 : kNT>(sb_, B::PATH[i], sv[i]);
     };
     auto compute = [&](int j, const float (&xv)[B::NXR][CPL], const float (&sv)[B::NPATH][CPL]) {
       const int64_t e = __builtin_amdgcn_readlane(my_e, j);
@@ -1008,11 +1011,11 @@ __device__ __forceinline__ void bwd_task(const ConvArgs& a, int b, int sl, float
               float o[CPL];
 #pragma unroll
               for (int c = 0; c < CPL; ++c) o[c] = old[pl][c] + v[c];
-              bst<CPL, kST>(dsb, B::PATH[pl], o);
+              bst<CPL, CACHED ? 0 : kST>(dsb, B::PATH[pl], o);
               return;
             }
           }
-          bst<CPL, kST>(dsb, B::PATH[pl], v);
+          bst<CPL, CACHED ? 0 : kST>(dsb, B::PATH[pl], v);
         };
         float dyl[V::D_SH];
 #pragma unroll
@@ -1023,11 +1026,11 @@ __device__ __forceinline__ void bwd_task(const ConvArgs& a, int b, int sl, float
         {
           const RowBuf Tb = row_buf(a.T + slot * x_rows<V>(a) * C, a.t_row, q, C);
 #pragma unroll
-          for (int i = 0; i < B::NXR; ++i) bst<CPL, E3_T_STORE_AUX>(Tb, B::XROW[i], t[i]);
+          for (int i = 0; i < B::NXR; ++i) bst<CPL, CACHED ? 0 : E3_T_STORE_AUX>(Tb, B::XROW[i], t[i]);
         }
       }
       const float tot = wave_reduce16(dy, lane);
-      if ((lane & 3) == 0) a.DY[(dy_group<V, G>(a, eb + j) * a.nslab + sl) * 16 + (lane >> 2)] = tot;
+      if ((lane & 3) == 0) a.DY[(dy_group<V, G>(a, eb + j) * a.nsd + sl) * 16 + (lane >> 2)] = tot;
     };
     load_x(0, xa);
     if (E3_BWD_DB_S) load_s(0, sa);
@@ -1051,24 +1054,30 @@ __device__ __forceinline__ void bwd_task(const ConvArgs& a, int b, int sl, float
   }
 }
 
-template <class V, int G, int CPL, bool ACC>
+template <class V, int G, int CPL, bool ACC, bool CACHED>
 __device__ __forceinline__ void bwd_dispatch(const ConvArgs& a, int b, int g, int sl, float* sA, float* sY) {
   if constexpr (G < V::NBG) {
     if (g == G)
-      bwd_task<V, G, CPL, ACC>(a, b, sl, sA, sY);
+      bwd_task<V, G, CPL, ACC, CACHED>(a, b, sl, sA, sY);
     else
-      bwd_dispatch<V, G + 1, CPL, ACC>(a, b, g, sl, sA, sY);
+      bwd_dispatch<V, G + 1, CPL, ACC, CACHED>(a, b, g, sl, sA, sY);
   }
 }
 
 // ACC: ds += the result (the double backward's sums) instead of ds = result.
-template <class V, int CPL, bool ACC>
+// CACHED: s, ds and T without the non-temporal bit, for several slabs of rows
+// that are not whole 64-byte pieces: there two waves each move a part of one,
+// which non-temporal accesses move twice (C = 100, l <= 2, 3,000 nodes 1170 ->
+// 937 us; C = 68, l <= 3, 3,000 nodes 1666 -> 1423; C = 132, 1,500 nodes 1037 ->
+// 766; C = 72 170 -> 151).  On whole pieces the bit is the faster one (C = 64 534
+// against 544 us, C = 80 382 against 420, C = 96 2032 against 2178).
+template <class V, int CPL, bool ACC, bool CACHED>
 __global__ __launch_bounds__(kWave, E3_BWD_MIN_WAVES) void k_conv_bwd_edges(ConvArgs a) {
   __shared__ f4v smem[(kEdgeBatch * (V::MAX_NA_B + V::D_SH) + 3) / 4];
   int b, g, sl;
   if (!task_of<V::NBG>(a, b, g, sl)) return;
   float* sA = reinterpret_cast<float*>(smem);
-  bwd_dispatch<V, 0, CPL, ACC>(a, b, g, sl, sA, sA + kEdgeBatch * V::MAX_NA_B);
+  bwd_dispatch<V, 0, CPL, ACC, CACHED>(a, b, g, sl, sA, sA + kEdgeBatch * V::MAX_NA_B);
 }
 
 // The double backward's three backward sweeps in one (generated BG::edge3):
@@ -1539,6 +1548,7 @@ struct SubArgs {
   T *m, *ds, *P, *DY;
   const int *rowptr, *eid, *src, *r2s;
   int n_nodes, chunk, C, nslab;
+  int c0, sl0, nsd;  // first channel and slab of the launch; slabs of a harmonic-partial slot
   int lgl;    // log2 of the lanes per edge, 3..6 (6: one edge per wave)
   int wide;   // -1: one edge per wave, descriptors based at the edge's rows; else 0
   int fb;     // edges per staged batch, a multiple of the edges per step
@@ -1659,7 +1669,7 @@ template <class V, int G, class T>
 __device__ __forceinline__ void sub_fwd_task(const SubArgs<T>& a, int b, int sl, T* sA) {
   using F = typename V::template FG<G>;
   const int lane = threadIdx.x, lgl = a.lgl, S = kWave >> lgl, sub = lane >> lgl;
-  const int C = a.C, q = sl * kWave + (lane & ((1 << lgl) - 1));
+  const int C = a.C, q = a.c0 + sl * kWave + (lane & ((1 << lgl) - 1));
   const bool act = q < C;
   const int e0 = uniform(a.rowptr[b]), e1 = uniform(a.rowptr[b + 1]);
   T acc[F::NROW][1];
@@ -1768,7 +1778,7 @@ template <class V, int G, class T, bool ACC>
 __device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl, T* sA, T* sY) {
   using B = typename V::template BG<G>;
   const int lane = threadIdx.x, lgl = a.lgl, S = kWave >> lgl, sub = lane >> lgl;
-  const int C = a.C, q = sl * kWave + (lane & ((1 << lgl) - 1));
+  const int C = a.C, q = a.c0 + sl * kWave + (lane & ((1 << lgl) - 1));
   const bool act = q < C;
   const int e0 = uniform(a.rowptr[b]), e1 = uniform(a.rowptr[b + 1]);
   if (e0 == e1) return;
@@ -1845,7 +1855,7 @@ __device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl,
 #pragma unroll
         for (int i = 0; i < V::D_SH; ++i) dy[i] = dyl[i];
       }
-      sub_reduce16_store(dy, lane, lgl, a.DY + (dy_group<V, G>(a, eb + je) * a.nslab + sl) * 16, je < n);
+      sub_reduce16_store(dy, lane, lgl, a.DY + (dy_group<V, G>(a, eb + je) * a.nsd + a.sl0 + sl) * 16, je < n);
     };
     load(0, xa, sa);
     for (int j = 0; j < nr; j += 2 * S) {
@@ -2613,6 +2623,28 @@ inline bool sub_fits(const e3_graph* g, int64_t xr, int64_t pr, int64_t C, int64
   return rows * C * elem <= (int64_t)kSubMaxBytes;
 }
 
+// Lanes per edge for w channels.
+template <class T>
+void sub_width(SubArgs<T>& a, int w) {
+  a.lgl = w > 32 ? 6 : w > 16 ? 5 : w > 8 ? 4 : 3;
+  a.fb = a.lgl >= 5 ? 16 : 32;
+}
+
+// The channels of a float32 sweep whose last slab would leave half of its lanes
+// or more idle, in two launches: the whole slabs, then the last w channels on
+// sub-waves (w <= 32) or, in the forward, on one slab of 64 with one channel
+// per lane.  Forward, slabs of 128, C > 128 (1,500 nodes, l <= 3): 348 -> 300 us
+// at C = 160, 358 -> 292 us at 132, 360 -> 338 us at 192; no better at 65 to 96
+// or from 224 on.  Backward, slabs of 64, w = 32: 2295 -> 2050 us at C = 96
+// (5,001 nodes), 727 -> 716 us at 160; other w gained nothing.  Graphs of fewer waves than kSplitWaves keep one
+// launch: they do not fill the chip, and two launches are two latencies.
+constexpr int64_t kSplitWaves = 4096;
+inline int split_of(const e3_plan* p, const e3_graph* g, int64_t waves, int xr, int pr, bool fwd) {
+  const int C = p->lay.C, r = C % (fwd ? 2 * kWave : kWave);
+  if (waves < kSplitWaves || (fwd ? C <= 2 * kWave || r > kWave : C <= kWave || r != 32)) return 0;
+  return r <= 32 && !sub_fits(g, xr, pr, C, sizeof(float)) ? 0 : r;
+}
+
 // xr, pr, orr, ng, g0: of the whole layout (as in KindCall); V: the layout or
 // the single-block kind whose rows are swept.
 template <class V, class T>
@@ -2622,11 +2654,10 @@ SubArgs<T> sub_args(const e3_plan* p, const e3_graph* g, int xr, int pr, int orr
   a.n_nodes = (int)g->n_nodes;
   a.chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
   a.C = p->lay.C;
-  a.nslab = (a.C + kWave - 1) / kWave;
+  a.nslab = a.nsd = (a.C + kWave - 1) / kWave;
   const int64_t row = (int64_t)a.C * sizeof(T);
   a.wide = sub_fits(g, xr, pr, a.C, sizeof(T)) ? 0 : -1;
-  a.lgl = a.wide || a.C > 32 ? 6 : a.C > 16 ? 5 : a.C > 8 ? 4 : 3;
-  a.fb = a.lgl >= 5 ? 16 : 32;
+  sub_width(a, a.wide ? kWave : a.C);
   auto bytes = [&](int64_t n, int64_t stride, int64_t rows) {
     return (unsigned)(a.wide ? rows * row : n > 0 ? ((n - 1) * stride + rows) * row : 0);
   };
@@ -2663,30 +2694,87 @@ e3_status launch_bwd_sub(const SubArgs<T>& a, bool accum, const char* name, hipS
   return E3_OK;
 }
 
+// The float32 forward sweep of a layout or of a kind inside one.
+template <class V, bool ACCT>
+e3_status launch_fwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const KindCall& kc, const char* name,
+                     hipStream_t st) {
+  auto sub = [&](int c0, int w) {
+    auto b = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+    b.x = a.x, b.vec = a.vec, b.y = a.y, b.s = a.s, b.m = a.m, b.accum = a.accum;
+    b.c0 = c0, b.nslab = 1;
+    sub_width(b, w);
+    return launch_fwd_sub<V>(b, name, st);
+  };
+  const int C = a.C;
+  if (C <= 32 && sub_fits(g, kc.xr, kc.pr, C, sizeof(float))) return sub(0, C);
+  auto main = [&](int c0, int cpl, int nslab) -> e3_status {
+    a.c0 = c0, a.nslab = nslab;
+    const dim3 grid((unsigned)(kXcd * a.chunk * V::NFG * nslab)), block(kWave);
+    TimedLaunch t_(name, st);
+    if (ACCT && a.accum) {
+      if (cpl == 1)
+        hipLaunchKernelGGL((k_conv_fwd<V, 1, ACCT>), grid, block, 0, st, a);
+      else
+        hipLaunchKernelGGL((k_conv_fwd<V, E3_FWD_CPL, ACCT>), grid, block, 0, st, a);
+    } else if (cpl == 1) {
+      hipLaunchKernelGGL((k_conv_fwd<V, 1, false>), grid, block, 0, st, a);
+    } else {
+      hipLaunchKernelGGL((k_conv_fwd<V, E3_FWD_CPL, false>), grid, block, 0, st, a);
+    }
+    E3_HIP(hipGetLastError());
+    return E3_OK;
+  };
+  const int cpl = p->cpl_f, slab = kWave * cpl;
+  const int w = split_of(p, g, g->n_nodes * V::NFG * p->nslab_f, kc.xr, kc.pr, true);
+  const e3_status r = main(0, cpl, (C - w + slab - 1) / slab);
+  if (r != E3_OK || w == 0) return r;
+  return w <= 32 ? sub(C - w, w) : main(C - w, 1, 1);
+}
+
+// The float32 backward edge sweep of a layout or of a kind inside one: a.ds /
+// a.T rows are stored where a.ds_row / a.t_row are not 0.
+template <class V, bool ACCT>
+e3_status launch_bwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const KindCall& kc, const char* name,
+                     hipStream_t st) {
+  auto sub = [&](int c0, int w) {
+    auto b = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+    b.x = a.x, b.vec = a.vec, b.y = a.y, b.s = a.s, b.dm = a.dm, b.ds = a.ds, b.P = a.T, b.DY = a.DY;
+    if (!a.ds_row) b.dsn = 0;
+    if (!a.t_row) b.tn = 0;
+    b.c0 = c0, b.sl0 = c0 / kWave, b.nslab = 1, b.nsd = p->nslab_b;
+    sub_width(b, w);
+    return launch_bwd_sub<V>(b, a.accum, name, st);
+  };
+  static_assert(E3_BWD_CPL == 1, "the launches below count slabs of 64 channels");
+  const int C = a.C;
+  if (C <= 32 && sub_fits(g, kc.xr, kc.pr, C, sizeof(float))) return sub(0, C);
+  const int w = split_of(p, g, g->n_nodes * V::NBG * p->nslab_b, kc.xr, kc.pr, false);
+  a.nsd = p->nslab_b, a.nslab = (C - w + kWave - 1) / kWave;
+  // several slabs of rows that are not whole 64-byte pieces (see k_conv_bwd_edges)
+  const bool cached = C > kWave && C % 16 != 0;
+  {
+    const dim3 grid((unsigned)(kXcd * a.chunk * V::NBG * a.nslab)), block(kWave);
+    TimedLaunch t_(name, st);
+    if (ACCT && a.accum)
+      hipLaunchKernelGGL((k_conv_bwd_edges<V, 1, ACCT, false>), grid, block, 0, st, a);
+    else if (cached)
+      hipLaunchKernelGGL((k_conv_bwd_edges<V, 1, false, true>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((k_conv_bwd_edges<V, 1, false, false>), grid, block, 0, st, a);
+    E3_HIP(hipGetLastError());
+  }
+  return w ? sub(C - w, w) : E3_OK;
+}
+
 // One forward convolution.  y: caller's harmonics or null (from vec);
 // accum: m += instead of m =.
 template <class V, int CPL>
 e3_status run_fwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* y,
                   const float* s, float* m, int accum, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  if (p->lay.C <= 32 && sub_fits(g, V::D_IN, V::NP, p->lay.C, sizeof(float))) {
-    auto a = sub_args<V, float>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
-    a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
-    return launch_fwd_sub<V>(a, "conv_fwd", st);
-  }
   ConvArgs a = base_args(p, g);
   a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
-  a.nslab = p->nslab_f;
-  const unsigned grid = (unsigned)(kXcd * a.chunk * V::NFG * a.nslab);
-  {
-    TimedLaunch t_("conv_fwd", st);
-    if (accum)
-      hipLaunchKernelGGL((k_conv_fwd<V, CPL, true>), dim3(grid), dim3(kWave), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_conv_fwd<V, CPL, false>), dim3(grid), dim3(kWave), 0, st, a);
-  }
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  return launch_fwd<V, true>(p, g, a, KindCall{V::D_IN, V::NP, V::D_OUT, V::NBG, 0}, "conv_fwd", st);
 }
 
 // Slabs of the three-term forward: one channel per lane; the waves of two
@@ -2757,29 +2845,10 @@ e3_status run_bwd(const e3_plan* p, const e3_graph* g, const float* x, const flo
   a.ds = ds ? ds : a.DY;
   a.ds_row = ds ? (int64_t)V::NP * a.C * 4 : 0;
   a.t_row = dx ? (int64_t)V::D_IN * a.C * 4 : 0;
-  a.nslab = p->nslab_b;
-  if (g->n_live > 0 && a.C <= 32 && sub_fits(g, V::D_IN, V::NP, a.C, sizeof(float))) {
-    auto b = sub_args<V, float>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
-    b.x = x, b.vec = vec, b.y = y, b.s = s, b.dm = dm, b.ds = a.ds, b.P = a.T, b.DY = a.DY;
-    if (!ds) b.dsn = 0;
-    if (!dx) b.tn = 0;
-    const e3_status r = launch_bwd_sub<V>(b, a.accum, "conv_bwd_edges", st);
+  if (g->n_live > 0) {
+    const e3_status r =
+        launch_bwd<V, true>(p, g, a, KindCall{V::D_IN, V::NP, V::D_OUT, V::NBG, 0}, "conv_bwd_edges", st);
     if (r != E3_OK) return r;
-  } else if (g->n_live > 0) {
-    const unsigned grid = (unsigned)(kXcd * a.chunk * V::NBG * a.nslab);
-    TimedLaunch t_("conv_bwd_edges", st);
-    if (p->cpl_b == 1) {
-      if (a.accum)
-        hipLaunchKernelGGL((k_conv_bwd_edges<V, 1, true>), dim3(grid), dim3(kWave), 0, st, a);
-      else
-        hipLaunchKernelGGL((k_conv_bwd_edges<V, 1, false>), dim3(grid), dim3(kWave), 0, st, a);
-    } else {
-      if (a.accum)
-        hipLaunchKernelGGL((k_conv_bwd_edges<V, E3_BWD_CPL, true>), dim3(grid), dim3(kWave), 0, st, a);
-      else
-        hipLaunchKernelGGL((k_conv_bwd_edges<V, E3_BWD_CPL, false>), dim3(grid), dim3(kWave), 0, st, a);
-    }
-    E3_HIP(hipGetLastError());
   }
   if (dx) {
     TimedLaunch t_("conv_bwd_dx", st);
@@ -3114,25 +3183,10 @@ template <class V>
 e3_status kind_fwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* y,
                    const float* s, float* m, int accum, const KindCall& kc, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  if (p->lay.C <= 32 && sub_fits(g, kc.xr, kc.pr, p->lay.C, sizeof(float))) {
-    auto a = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
-    a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
-    return launch_fwd_sub<V>(a, "kind_fwd", st);
-  }
   ConvArgs a = base_args(p, g);
   a.x = x, a.vec = vec, a.y = y, a.s = s, a.m = m, a.accum = accum;
   a.xr = kc.xr, a.pr = kc.pr, a.orr = kc.orr;
-  a.nslab = p->nslab_f;
-  const unsigned grid = (unsigned)(kXcd * a.chunk * V::NFG * a.nslab);
-  {
-    TimedLaunch t_("kind_fwd", st);
-    if (p->cpl_f == 1)
-      hipLaunchKernelGGL((k_conv_fwd<V, 1, false>), dim3(grid), dim3(kWave), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_conv_fwd<V, E3_FWD_CPL, false>), dim3(grid), dim3(kWave), 0, st, a);
-  }
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  return launch_fwd<V, false>(p, g, a, kc, "kind_fwd", st);
 }
 
 template <class V>
@@ -3140,25 +3194,11 @@ e3_status kind_bwd(const e3_plan* p, const e3_graph* g, const float* x, const fl
                    const float* s, const float* dm, float* T, int64_t t_row, float* DY, float* ds, int64_t ds_row,
                    int accum_ds, const KindCall& kc, hipStream_t st) {
   if (g->n_live == 0) return E3_OK;
-  if (p->lay.C <= 32 && sub_fits(g, kc.xr, kc.pr, p->lay.C, sizeof(float))) {
-    auto a = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
-    a.x = x, a.vec = vec, a.y = y, a.s = s, a.dm = dm, a.ds = ds, a.P = T, a.DY = DY;
-    if (!ds_row) a.dsn = 0;
-    if (!t_row) a.tn = 0;
-    return launch_bwd_sub<V>(a, accum_ds, "kind_bwd", st);
-  }
   ConvArgs a = base_args(p, g);
   a.x = x, a.vec = vec, a.y = y, a.s = s, a.dm = dm, a.accum = accum_ds;
   a.T = T, a.t_row = t_row, a.DY = DY, a.ds = ds, a.ds_row = ds_row;
   a.xr = kc.xr, a.pr = kc.pr, a.orr = kc.orr, a.ng = kc.ng, a.g0 = kc.g0;
-  a.nslab = p->nslab_b;
-  const unsigned grid = (unsigned)(kXcd * a.chunk * V::NBG * a.nslab);
-  {
-    TimedLaunch t_("kind_bwd", st);
-    hipLaunchKernelGGL((k_conv_bwd_edges<V, 1, false>), dim3(grid), dim3(kWave), 0, st, a);
-  }
-  E3_HIP(hipGetLastError());
-  return E3_OK;
+  return launch_bwd<V, false>(p, g, a, kc, "kind_bwd", st);
 }
 
 template <class V>

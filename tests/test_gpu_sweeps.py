@@ -122,3 +122,29 @@ def test_narrow_beyond_lane_offsets(e3):
     _, dvec_k, ds_k = e3.conv_bwd(plan, Gk, x, vec[:k].contiguous(), s[:k].contiguous(), dm)
     assert float((ds_k - ds64[:k]).norm() / ds64[:k].norm()) < TOL
     assert float((dvec_k - dvec64[:k]).norm() / dvec64[:k].norm()) < TOL
+
+
+# last slabs of 32 channels on sub-waves (backward; forward past 128), of up to
+# 64 on one channel per lane (forward), and rows that are not whole 64-byte
+# pieces; graphs on either side of the size where the channels are split
+@pytest.mark.parametrize("n,deg", [(40, 9), (3000, 3)])
+@pytest.mark.parametrize("C,composed", [(68, False), (80, False), (96, False), (96, True), (132, False), (132, True),
+                                        (160, False), (188, False), (192, True), (200, False)])
+def test_ragged_slabs(e3, C, composed, n, deg):
+    rng = np.random.default_rng(C)
+    irreps = f"{C}x0e+{C}x1o"
+    lay = oirreps.layout(irreps, 2, 2)
+    plan = e3.Plan(irreps, 2, 2, composed=composed)
+    E = n * deg
+    snd, rcv = (rng.integers(0, n, E).astype(np.int32) for _ in range(2))
+    vec = rng.standard_normal((E, 3)).astype(np.float32)
+    x, s, dm = (rng.standard_normal(sh).astype(np.float32) for sh in
+                ((n, lay.d_in, C), (E, lay.n_paths, C), (n, lay.d_out, C)))
+    print("[case] ragged", C, plan.kernels, n, flush=True)
+    G = e3.Graph(to_dev(snd), to_dev(rcv), n)
+    dev = [to_dev(a) for a in (x, vec, s)]
+    got = (e3.conv_fwd(plan, G, *dev), *e3.conv_bwd(plan, G, *dev, to_dev(dm)))
+    ref = oconv.conv_bwd(lay, x, vec, s, dm, snd, rcv, n)
+    refs = (oconv.conv_fwd(lay, x, vec, s, snd, rcv, n), ref["dx"], ref["dvec"], ref["ds"])
+    for a, b in zip(got, refs):
+        assert rel_l2(to_np(a), b.numpy()) < TOL
