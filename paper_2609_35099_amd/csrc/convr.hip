@@ -971,9 +971,19 @@ e3_status comp_bwd(const e3_plan* p, const e3_graph* g, int64_t rows, const floa
   if (dx) {
     for (const auto& z : p->pathless)
       if ((r = comp_zero_rows(T, g->n_live, D_in * C, z.first * C, z.second * C, st)) != E3_OK) return r;
-    TimedLaunch t_("conv_bwd_dx", st);
-    dx_sum(T, dx, g, (int)(D_in * C), (accum & kAccDx) != 0, st);
+    bool done;
+    switch (p->lay.lmax_sh) {
+      case 0: done = launch_finish<0>(p, g, T, dx, vec, DY, dvec, ds, nparts, st); break;
+      case 1: done = launch_finish<1>(p, g, T, dx, vec, DY, dvec, ds, nparts, st); break;
+      case 2: done = launch_finish<2>(p, g, T, dx, vec, DY, dvec, ds, nparts, st); break;
+      default: done = launch_finish<3>(p, g, T, dx, vec, DY, dvec, ds, nparts, st); break;
+    }
+    if (!done) {
+      TimedLaunch t_("conv_bwd_dx", st);
+      dx_sum(T, dx, g, (int)(D_in * C), (accum & kAccDx) != 0, st);
+    }
     E3_HIP(hipGetLastError());
+    if (done) return E3_OK;
   }
   (void)P;
   return finish_bwd(p, g, g->n_live, vec, DY, dvec, dy, ds, nparts, accum, st);

@@ -1267,13 +1267,13 @@ __global__ __launch_bounds__(kWave) void k_conv_bwd_dx(const T* __restrict__ P, 
 constexpr int kDxThreads = 256;
 
 template <class T>
-__global__ __launch_bounds__(kDxThreads) void k_conv_bwd_dx_short(const T* __restrict__ P, T* __restrict__ dx,
-                                                                  const int* __restrict__ rowptr_s, int n_nodes,
-                                                                  int chunk, int units, int accum) {
+__device__ __forceinline__ void dx_short_block(const T* __restrict__ P, T* __restrict__ dx,
+                                               const int* __restrict__ rowptr_s, int n_nodes, int chunk, int units,
+                                               int accum, int block) {
   constexpr int W = 16 / sizeof(T);
   typedef T Vt __attribute__((ext_vector_type(W)));
   __shared__ Vt part[kDxThreads];
-  const int node = (blockIdx.x % kXcd) * chunk + blockIdx.x / kXcd;
+  const int node = (block % kXcd) * chunk + block / kXcd;
   if (node >= n_nodes) return;
   const int S = kDxThreads / units, tid = threadIdx.x;
   const int sub = tid / units, u = tid - sub * units;
@@ -1291,6 +1291,13 @@ __global__ __launch_bounds__(kDxThreads) void k_conv_bwd_dx_short(const T* __res
   Vt* o = reinterpret_cast<Vt*>(dx) + (int64_t)node * units + u;
   if (accum) acc += *o;  // old + this sum, so that accumulating equals adding a separate result
   __builtin_nontemporal_store(acc, o);
+}
+
+template <class T>
+__global__ __launch_bounds__(kDxThreads) void k_conv_bwd_dx_short(const T* __restrict__ P, T* __restrict__ dx,
+                                                                  const int* __restrict__ rowptr_s, int n_nodes,
+                                                                  int chunk, int units, int accum) {
+  dx_short_block(P, dx, rowptr_s, n_nodes, chunk, units, accum, (int)blockIdx.x);
 }
 
 // dvec of each live edge from its harmonic cotangent (summed over groups).
@@ -1327,6 +1334,55 @@ __global__ __launch_bounds__(256) void k_zero_pad(const int* __restrict__ pad_ei
     for (int64_t k = threadIdx.x; k < w0; k += blockDim.x) p0[e * w0 + k] = 0.0f;
   if (p1)
     for (int64_t k = threadIdx.x; k < w1; k += blockDim.x) p1[e * w1 + k] = 0.0f;
+}
+
+// What follows a backward edge sweep with short slots, in one launch: the
+// segment sum (a block per node), then dvec (256 live edges per block), then
+// the zero rows of padding edges (a block each).  The three are independent,
+// and on a small graph a launch costs more than the work of any of them
+// (1,503 atoms, 7,900 padding edges: 32 + 7 + 11 us in three, 42 in one; 64-atom
+// cluster 6 + 6 us in two, 6 in one).
+// With long slots, bound by their bytes, one launch measured no faster.
+struct FinishArgs {
+  const float *P, *vec, *DY;
+  float *dx, *dvec, *ds;
+  const int *rowptr_s, *eid;
+  int n_nodes, chunk, units, nparts;
+  int64_t n_live, n_pad, ds_width;
+  int64_t dx_blocks, dvec_blocks;
+};
+
+template <int L>
+__global__ __launch_bounds__(kDxThreads) void k_conv_bwd_finish(FinishArgs a) {
+  int64_t b = blockIdx.x;
+  if (b < a.dx_blocks) {
+    dx_short_block(a.P, a.dx, a.rowptr_s, a.n_nodes, a.chunk, a.units, 0, (int)b);
+    return;
+  }
+  b -= a.dx_blocks;
+  if (b < a.dvec_blocks) {
+    constexpr int DSH = (L + 1) * (L + 1);
+    const int64_t pos = b * kDxThreads + threadIdx.x;
+    if (pos >= a.n_live) return;
+    const int64_t e = a.eid[pos];
+    float dY[DSH];
+#pragma unroll
+    for (int i = 0; i < DSH; ++i) dY[i] = 0.0f;
+    for (int g = 0; g < a.nparts; ++g)
+#pragma unroll
+      for (int i = 0; i < DSH; ++i) dY[i] += a.DY[(pos * a.nparts + g) * 16 + i];
+    float ux, uy, uz, inv, gx, gy, gz, ox, oy, oz;
+    unit_of(a.vec, e, ux, uy, uz, inv);
+    sh_grad_of<L>(ux, uy, uz, dY, gx, gy, gz);
+    project(ux, uy, uz, inv, gx, gy, gz, ox, oy, oz);
+    a.dvec[3 * e] = ox, a.dvec[3 * e + 1] = oy, a.dvec[3 * e + 2] = oz;
+    return;
+  }
+  b -= a.dvec_blocks;
+  if (b >= a.n_pad) return;
+  const int64_t e = a.eid[a.n_live + b];
+  for (int64_t k = threadIdx.x; k < a.ds_width; k += kDxThreads) a.ds[e * a.ds_width + k] = 0.0f;
+  if (threadIdx.x < 3) a.dvec[3 * e + threadIdx.x] = 0.0f;
 }
 
 // dy of each live edge: the sum of its per-(group, slab) partials, in order.
@@ -2825,6 +2881,25 @@ void dx_sum(const T* P, T* dx, const e3_graph* g, int width, int accum, hipStrea
                      (int)g->n_nodes, chunk, units, nsl, accum);
 }
 
+// The segment sum, dvec and the padding rows after a sweep in one launch
+// (k_conv_bwd_finish); false when the slots are too long for it.
+template <int L>
+bool launch_finish(const e3_plan* p, const e3_graph* g, const float* P, float* dx, const float* vec, const float* DY,
+                   float* dvec, float* ds, int nparts, hipStream_t st) {
+  FinishArgs a{P, vec, DY, dx, dvec, ds, g->rowptr_s, g->eid_r, (int)g->n_nodes};
+  a.units = p->lay.d_in * p->lay.C / 4;
+  if (a.units > kDxShort || !dx || !dvec || !ds || g->n_live == 0) return false;
+  a.chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
+  a.nparts = nparts, a.n_live = g->n_live, a.n_pad = g->n_pad;
+  a.ds_width = (int64_t)p->lay.paths.size() * p->lay.C;
+  a.dx_blocks = (int64_t)kXcd * a.chunk, a.dvec_blocks = (g->n_live + kDxThreads - 1) / kDxThreads;
+  const int64_t blocks = a.dx_blocks + a.dvec_blocks + a.n_pad;
+  if (blocks > 0x7fffffff) return false;
+  TimedLaunch t_("conv_bwd_finish", st);
+  hipLaunchKernelGGL(k_conv_bwd_finish<L>, dim3((unsigned)blocks), dim3(kDxThreads), 0, st, a);
+  return true;
+}
+
 // One backward convolution.  Harmonics from y when given (then dy is the
 // harmonic cotangent output), else from vec (then dvec = J^T dy).  Any of
 // dx, dvec/dy, ds may be null: that cotangent is not stored.  accum is a mask
@@ -2849,6 +2924,11 @@ e3_status run_bwd(const e3_plan* p, const e3_graph* g, const float* x, const flo
     const e3_status r =
         launch_bwd<V, true>(p, g, a, KindCall{V::D_IN, V::NP, V::D_OUT, V::NBG, 0}, "conv_bwd_edges", st);
     if (r != E3_OK) return r;
+  }
+  // (dvec comes with harmonics from vec, which no accumulating call has)
+  if (launch_finish<V::LSH>(p, g, a.T, dx, vec, a.DY, dvec, ds, V::NBG * p->nslab_b, st)) {
+    E3_HIP(hipGetLastError());
+    return E3_OK;
   }
   if (dx) {
     TimedLaunch t_("conv_bwd_dx", st);
