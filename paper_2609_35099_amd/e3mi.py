@@ -121,31 +121,35 @@ def _check(status: int, where: str):
 
 
 # ---------------------------------------------------------------- tensors
+_modules = None   # torch and the dtypes by name, looked up once
+
+
 def _torch():
-    import torch
-    return torch
+    global _modules
+    if _modules is None:
+        import torch
+        _modules = torch, {"float32": torch.float32, "float64": torch.float64, "int32": torch.int32}
+    return _modules[0]
 
 
 def _ptr(t, name, shape=None, dtype="float32"):
     torch = _torch()
-    want = {"float32": torch.float32, "float64": torch.float64, "int32": torch.int32}[dtype]
+    want = _modules[1][dtype]
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
-    if t.dtype != want:
+    if t.dtype is not want:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return ct.c_void_p(t.data_ptr()) if t.numel() else ct.c_void_p(0)
+    return t.data_ptr() if t.numel() else None
 
 
 def _stream(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ct.c_void_p(s.cuda_stream)
+    return (_torch().cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _on_stream(fn):
@@ -330,7 +334,7 @@ def tp_bwd(plan: Plan, x, y, w, dz, dx=None, dy=None, dw=None, ws=None, stream=N
     _check(lib().e3_tp_bwd(plan.handle, _ptr(x, "x", (R, plan.D_in, plan.C)), _ptr(y, "y", (R, plan.D_sh)),
                            _ptr(w, "w", (R, plan.P, plan.C)), _ptr(dz, "dz", (R, plan.D_out, plan.C)),
                            _ptr(dx, "dx", (R, plan.D_in, plan.C)), _ptr(dy, "dy", (R, plan.D_sh)),
-                           _ptr(dw, "dw", (R, plan.P, plan.C)), ct.c_void_p(ws.data_ptr()), ws.numel(), R,
+                           _ptr(dw, "dw", (R, plan.P, plan.C)), ws.data_ptr(), ws.numel(), R,
                            _stream(stream)), "e3_tp_bwd")
     return dx, dy, dw
 
@@ -369,7 +373,7 @@ def conv_bwd(plan: Plan, graph: Graph, x, vec, s, dm, dx=None, dvec=None, ds=Non
                              _ptr(vec, "vec", (E, 3)), _ptr(s, "s", (E, plan.P, plan.C)),
                              _ptr(dm, "dm", (N, plan.D_out, plan.C)), _ptr(dx, "dx", (N, plan.D_in, plan.C)),
                              _ptr(dvec, "dvec", (E, 3)), _ptr(ds, "ds", (E, plan.P, plan.C)),
-                             ct.c_void_p(ws.data_ptr()), ws.numel(), _stream(stream)), "e3_conv_bwd")
+                             ws.data_ptr(), ws.numel(), _stream(stream)), "e3_conv_bwd")
     return dx, dvec, ds
 
 
@@ -401,7 +405,7 @@ def tp_bwd_f64(plan: Plan, x, y, w, dz, stream=None):
     _check(lib().e3_tp_bwd_f64(plan.handle, _ptr(x, "x", (R, plan.D_in, plan.C), f), _ptr(y, "y", (R, plan.D_sh), f),
                                _ptr(w, "w", (R, plan.P, plan.C), f), _ptr(dz, "dz", (R, plan.D_out, plan.C), f),
                                _ptr(dx, "dx", (R, plan.D_in, plan.C), f), _ptr(dy, "dy", (R, plan.D_sh), f),
-                               _ptr(dw, "dw", (R, plan.P, plan.C), f), ct.c_void_p(ws.data_ptr()), ws.numel(), R,
+                               _ptr(dw, "dw", (R, plan.P, plan.C), f), ws.data_ptr(), ws.numel(), R,
                                _stream(stream)), "e3_tp_bwd_f64")
     return dx, dy, dw
 
@@ -429,7 +433,7 @@ def conv_bwd_f64(plan: Plan, graph: Graph, x, vec, s, dm, stream=None):
                                  _ptr(vec, "vec", (E, 3), f), _ptr(s, "s", (E, plan.P, plan.C), f),
                                  _ptr(dm, "dm", (N, plan.D_out, plan.C), f), _ptr(dx, "dx", (N, plan.D_in, plan.C), f),
                                  _ptr(dvec, "dvec", (E, 3), f), _ptr(ds, "ds", (E, plan.P, plan.C), f),
-                                 ct.c_void_p(ws.data_ptr()), ws.numel(), _stream(stream)), "e3_conv_bwd_f64")
+                                 ws.data_ptr(), ws.numel(), _stream(stream)), "e3_conv_bwd_f64")
     return dx, dvec, ds
 
 
@@ -482,7 +486,7 @@ def conv_bwd_y(plan: Plan, graph: Graph, x, y, s, dm, dx=None, dy=None, ds=None,
                                _ptr(y, "y", (E, plan.D_sh)), _ptr(s, "s", (E, plan.P, plan.C)),
                                _ptr(dm, "dm", (N, plan.D_out, plan.C)), _optr(dx, "dx", (N, plan.D_in, plan.C)),
                                _optr(dy, "dy", (E, plan.D_sh)), _optr(ds, "ds", (E, plan.P, plan.C)),
-                               1 if accumulate else 0, ct.c_void_p(ws.data_ptr()), ws.numel(), _stream(stream)),
+                               1 if accumulate else 0, ws.data_ptr(), ws.numel(), _stream(stream)),
            "e3_conv_bwd_y")
     return dx, dy, ds
 
@@ -502,7 +506,7 @@ def conv_bwd2(plan: Plan, graph: Graph, x, y, s, dm, ddx, ddy, dds, ws=None, str
                               _ptr(ddy, "ddy", (E, plan.D_sh)), _ptr(dds, "dds", (E, plan.P, plan.C)),
                               _ptr(gx, "gx", (N, plan.D_in, plan.C)), _ptr(gy, "gy", (E, plan.D_sh)),
                               _ptr(gs, "gs", (E, plan.P, plan.C)), _ptr(gdm, "gdm", (N, plan.D_out, plan.C)),
-                              ct.c_void_p(ws.data_ptr()), ws.numel(), _stream(stream)), "e3_conv_bwd2")
+                              ws.data_ptr(), ws.numel(), _stream(stream)), "e3_conv_bwd2")
     return gx, gy, gs, gdm
 
 
@@ -563,7 +567,7 @@ class RecordTP:
         _check(getattr(lib(), "e3_tpg_bwd" + sfx)(
             self.handle, _ptr(x, "x", (R, self.d_x, C), dt), _ptr(y, "y", self._yshape(R, C), dt),
             _ptr(dz, "dz", (R, self.d_z, C), dt), _ptr(dx, "dx", (R, self.d_x, C), dt),
-            _ptr(dy, "dy", self._yshape(R, C), dt), ct.c_void_p(ws.data_ptr()), ws.numel(), R, C,
+            _ptr(dy, "dy", self._yshape(R, C), dt), ws.data_ptr(), ws.numel(), R, C,
             _stream(stream)), "e3_tpg_bwd" + sfx)
         return dx, dy
 
@@ -615,7 +619,7 @@ class Linear:
         _check(lib().e3_linear_bwd(self.handle, _ptr(x, "x", (n, self.D_in, self.C_in)),
                                    _ptr(W, "W", (self.n_weights,)), _ptr(dout, "dout", (n, self.D_out, self.C_out)),
                                    _ptr(dx, "dx", (n, self.D_in, self.C_in)), _ptr(dW, "dW", (self.n_weights,)),
-                                   ct.c_void_p(ws.data_ptr()), ws.numel(), n, _stream(stream)), "e3_linear_bwd")
+                                   ws.data_ptr(), ws.numel(), n, _stream(stream)), "e3_linear_bwd")
         return dx, dW
 
 
@@ -657,7 +661,7 @@ def conv_bwd_radial(plan: Plan, graph: Graph, x, vec, h, W, dm, dx=None, dvec=No
                                     _ptr(W, "W", (K, plan.P, plan.C)), K,
                                     _ptr(dm, "dm", (N, plan.D_out, plan.C)), _ptr(dx, "dx", (N, plan.D_in, plan.C)),
                                     _ptr(dvec, "dvec", (E, 3)), _ptr(dh, "dh", (E, K)),
-                                    _ptr(dW, "dW", (K, plan.P, plan.C)), ct.c_void_p(ws.data_ptr()), ws.numel(),
+                                    _ptr(dW, "dW", (K, plan.P, plan.C)), ws.data_ptr(), ws.numel(),
                                     _stream(stream)), "e3_conv_bwd_radial")
     return dx, dvec, dh, dW
 
