@@ -489,7 +489,13 @@ struct TpStr {
 // ------------------------------------------------------------ tensor product
 constexpr int kTpRows = 8;  // rows whose pre-contraction is staged per LDS batch
 
-template <class V, int CPL>
+// Bound by its stream (a quarter reads).  CACHED: without the non-temporal bit,
+// for rows that are not whole 64-byte pieces, where a wave's neighbouring rows
+// share one: 716 -> 610, 534 -> 434, 234 -> 171 and 291 -> 241 us at C = 100, 68, 20
+// and 36 (50,000 to 100,000 rows).  Whole pieces (C = 32 345 against 353 us),
+// several slabs (C = 132 847 against 857) and the single-block kinds (C = 40 220
+// against 242) keep it.
+template <class V, int CPL, bool CACHED>
 __global__ __launch_bounds__(kWave) void k_tp(const float* __restrict__ x, const float* __restrict__ y,
                                               const float* __restrict__ w, float* __restrict__ z, int64_t rows,
                                               int C, int nslab, TpStr ts) {
@@ -520,10 +526,10 @@ __global__ __launch_bounds__(kWave) void k_tp(const float* __restrict__ x, const
     const RowBuf wb = row_buf(w + r * p_rows<V>(ts) * C, (int64_t)V::NP * C * 4, q, C);
     const RowBuf zb = row_buf(z + r * o_rows<V>(ts) * C, (int64_t)V::D_OUT * C * 4, q, C);
 #pragma unroll
-    for (int i = 0; i < T::NXR; ++i) bld<CPL, kNT>(xb, T::XROW[i], xv[i]);
+    for (int i = 0; i < T::NXR; ++i) bld<CPL, CACHED ? 0 : kNT>(xb, T::XROW[i], xv[i]);
 #pragma unroll
-    for (int i = 0; i < T::NPATH; ++i) bld<CPL, kNT>(wb, T::PATH[i], wv[i]);
-    auto st = [&](int row, const float (&v)[CPL]) { bst<CPL, kST>(zb, row, v); };
+    for (int i = 0; i < T::NPATH; ++i) bld<CPL, CACHED ? 0 : kNT>(wb, T::PATH[i], wv[i]);
+    auto st = [&](int row, const float (&v)[CPL]) { bst<CPL, CACHED ? 0 : kST>(zb, row, v); };
     T::template rows<CPL>(sA + j * T::NA, xv, wv, st);
   }
 }
@@ -3009,7 +3015,11 @@ e3_status run_tp(const e3_plan* p, const float* x, const float* y, const float* 
   {
     TimedLaunch t_("tp_fwd", st);
     const dim3 grid((unsigned)tile_grid(false, rows, kTpRows, p->nslab_f));
-    hipLaunchKernelGGL((k_tp<V, CPL>), grid, dim3(kWave), 0, st, x, y, w, z, rows, p->lay.C, p->nslab_f, TpStr{});
+    if (p->nslab_f == 1 && p->lay.C % 16 != 0)
+      hipLaunchKernelGGL((k_tp<V, CPL, true>), grid, dim3(kWave), 0, st, x, y, w, z, rows, p->lay.C, 1, TpStr{});
+    else
+      hipLaunchKernelGGL((k_tp<V, CPL, false>), grid, dim3(kWave), 0, st, x, y, w, z, rows, p->lay.C, p->nslab_f,
+                         TpStr{});
   }
   E3_HIP(hipGetLastError());
   return E3_OK;
@@ -3289,7 +3299,7 @@ e3_status kind_tp(const e3_plan* p, const float* x, const float* y, const float*
   {
     TimedLaunch t_("kind_tp", st);
     const dim3 grid((unsigned)tile_grid(false, rows, kTpRows, nslab));
-    hipLaunchKernelGGL((k_tp<V, 1>), grid, dim3(kWave), 0, st, x, y, w, z, rows, p->lay.C, nslab,
+    hipLaunchKernelGGL((k_tp<V, 1, false>), grid, dim3(kWave), 0, st, x, y, w, z, rows, p->lay.C, nslab,
                        TpStr{kc.xr, kc.pr, kc.orr});
   }
   E3_HIP(hipGetLastError());
