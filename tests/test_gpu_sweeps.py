@@ -11,6 +11,7 @@ import pytest
 
 from oracle import conv as oconv
 from oracle import irreps as oirreps
+from oracle import tp as otp
 
 from gpu_util import TOL, rel_l2, to_dev, to_np
 
@@ -148,3 +149,17 @@ def test_ragged_slabs(e3, C, composed, n, deg):
     refs = (oconv.conv_fwd(lay, x, vec, s, snd, rcv, n), ref["dx"], ref["dvec"], ref["ds"])
     for a, b in zip(got, refs):
         assert rel_l2(to_np(a), b.numpy()) < TOL
+
+
+# rows of whole 64-byte pieces and of others, on one slab and on two
+@pytest.mark.parametrize("C", [4, 16, 20, 36, 64, 68, 100, 128, 132])
+def test_tensor_product_row_pieces(e3, C):
+    rng = np.random.default_rng(C)
+    irreps, rows = f"{C}x0e+{C}x1o", 67
+    lay = oirreps.layout(irreps, 2, 2)
+    plan = e3.Plan(irreps, 2, 2)
+    x, y, w = (rng.standard_normal(sh).astype(np.float32) for sh in
+               ((rows, lay.d_in, C), (rows, 9), (rows, lay.n_paths, C)))
+    print("[case] tp", C, plan.kernels, flush=True)
+    z = to_np(e3.tp_fwd(plan, to_dev(x), to_dev(y), to_dev(w)))
+    assert rel_l2(z, otp.tp(lay, x, y, w).numpy()) < TOL
