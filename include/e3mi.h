@@ -329,8 +329,8 @@ e3_status e3_linear_bwd(e3_linear* lin, const float* x, const float* W, const fl
  * x [rows, d_x, C], y [rows, d_y, C] or [rows, d_y], z [rows, d_z, C]; any
  * C >= 1.  Records are copied at create (index errors: E3_ERR_INDEX_OUT_OF_RANGE);
  * operand rows must fit 64 KiB of staging per 64 channels (else
- * E3_ERR_UNSUPPORTED).  A wave stages up to four rows (as many as fit the
- * limit); an operand block of those rows, d C element bytes per row, must stay
+ * E3_ERR_UNSUPPORTED).  An operand block of four rows (or as many as fit the
+ * limit), d C element bytes per row, must stay
  * under 2 GiB (else E3_ERR_INVALID_ARG).  e3_tpg_create uploads the tables
  * to the device current at creation (it allocates and waits for the copy);
  * the compute calls then only launch kernels, and return E3_ERR_INVALID_ARG

@@ -1409,10 +1409,9 @@ __global__ __launch_bounds__(256) void k_conv_bwd_dy(const float* __restrict__ D
 // ------------------------------------------------------------ float64 builds
 // The tensor product and the convolution in float64, the precision the paper
 // measures its float32 kernels against (App. D, "Precision").  They run the
-// same generated per-edge code (generic in the scalar type) in simpler
-// skeletons than the float32 sweeps: one channel per lane, one 64-channel slab
-// per wave, rows through 8-byte buffer loads, harmonic cotangents summed
-// across the wave by a fixed butterfly.  Accuracy, not throughput, is their use.
+// same generated per-edge code (generic in the scalar type).  The convolution
+// shares the sub-wave sweeps with float32; the tensor product takes one channel
+// per lane and one 64-channel slab per wave, rows through 8-byte buffer loads.
 struct RowBuf64 {
   __amdgpu_buffer_rsrc_t r;
   int voff;      // lane's channel, bytes

@@ -30,6 +30,7 @@ def e3():
     (0, (2, 3, 4), 5, 7), (1, (1, 1, 1), 1, 1), (3, (4, 2, 5), 2, 63), (63, (5, 4, 7), 3, 64),
     (64, (5, 4, 7), 4, 65), (65, (9, 9, 9), 5, 100), (67, (9, 9, 9), 9, 12), (137, (9, 4, 16), 13, 130),
     (260, (40, 3, 30), 6, 20), (90, (60, 50, 8), 3, 10),
+    (137, (9, 16, 20), 5, 64), (90, (30, 7, 8), 3, 128), (70, (3, 4, 5), 7, 192), (65, (70, 9, 9), 2, 320),
 ])
 def test_record_walk_edges(e3, nnz, dims, rows, C, ypc, f64):
     rng = np.random.default_rng(nnz * 7 + rows)
