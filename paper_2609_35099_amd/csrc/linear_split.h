@@ -174,26 +174,33 @@ struct SpWave {
   }
 };
 
-// v / R by a multiplication, exact while v R < 2^32.
+// v / R and v % R by a multiplication and a correction: with mul = 2^32 / R
+// rounded up, the product's high half is at most one too large for any v < 2^31.
 struct SpDiv {
-  unsigned R, mul;  // mul = 0 for R = 1
+  int R;
+  unsigned mul;  // 0 for R = 1
   __device__ __forceinline__ explicit SpDiv(int R_) : R(R_), mul(0xffffffffu / R_ + 1) {}
-  __device__ __forceinline__ int operator()(unsigned v) const { return (int)(mul ? __umulhi(v, mul) : v); }
+  __device__ __forceinline__ int operator()(int v, int& rem) const {
+    const int q = mul ? (int)__umulhi((unsigned)v, mul) : v, m = v - q * R;
+    rem = m < 0 ? m + R : m;
+    return m < 0 ? q - 1 : q;
+  }
 };
 
 // Rows r0 + d of a tile as (node, component of R).
 struct SpRows {
   int64_t node0;
-  int m0, R, last;
+  int m0, last;
   SpDiv div;
-  __device__ __forceinline__ SpRows(int64_t r0, int64_t NR, int R_) : R(R_), div(R_) {
+  __device__ __forceinline__ SpRows(int64_t r0, int64_t NR, int R) : div(R) {
     node0 = r0 / R, m0 = (int)(r0 - node0 * R);
     last = NR - r0 < 1024 ? (int)(NR - r0) - 1 : 1023;  // rows past the end become the last one
   }
   // offset of row d's component row in units of rows of a tensor with D per node, from node0
   __device__ __forceinline__ int at(int d, int D) const {
-    const int v = m0 + imin(d, last), q = div(v);
-    return q * D + (v - q * R);
+    int m;
+    const int q = div(m0 + imin(d, last), m);
+    return q * D + m;
   }
 };
 
@@ -329,32 +336,31 @@ __global__ __launch_bounds__(kSpThreads, 2) void k_lin_dw(LinDwArgs a) {
   // Columns past C_in / C_out read the last one; their results are not stored.
   // A thread's N / 8 rows of a step are uniform per wave; rows past the end
   // load the last row and are cleared.
-  const int xoff = imin(kc0 + tid % RM, a.C_in - 1) * 4, doff = imin(jc0 + tid % BN, a.C_out - 1) * 4;
+  const unsigned xcol = imin(kc0 + tid % RM, a.C_in - 1), dcol = imin(jc0 + tid % BN, a.C_out - 1);
   float xv[RM / 8], dv[BN / 8];
   // Row offsets from the node of the step's first row, a row per lane (they
-  // repeat every 16 lanes), handed out by v_readlane.
+  // repeat every 16 lanes), handed out by v_readlane: in units of 16 channels,
+  // which stay below 2^31 for any layout (64 blocks of up to 1,999 rows, 4,096
+  // channels, 32 nodes), where bytes would not.
   const int64_t node0 = rb / R;
   const int m0 = (int)(rb - node0 * R), lane16 = tid & 15;
   const SpDiv div(R);
   auto load = [&](int st) {
     st = imin(st, nsteps - 1);  // unconditional loads: the waits count exactly
-    const unsigned r1 = m0 + 32 * st;
-    const int q1 = div(r1), m1 = (int)r1 - q1 * R;
+    int m1;
+    const int q1 = div(m0 + 32 * st, m1);
     const float* x0 = a.x + ((node0 + q1) * a.D_in + pr.src_row) * a.C_in;
     const float* d0 = a.dout + ((node0 + q1) * a.D_out + pr.dst_row) * a.C_out;
-    auto rows = [&](auto& v, const float* base, int D, int C, int voff, int k0) {
+    auto rows = [&](auto& v, const float* base, int D, int C, unsigned col, int k0) {
       constexpr int cnt = sizeof(v) / sizeof(v[0]);
-      const __amdgpu_buffer_rsrc_t rs =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, 0x7fffffff, 0x00020000);
-      const int r = m1 + imin(k0 + lane16, nrows - 1 - 32 * st), q = div(r);
-      const int off = (q * D + (r - q * R)) * C * 4;
+      int m;
+      const int q = div(m1 + imin(k0 + lane16, nrows - 1 - 32 * st), m);
+      const int off = (q * D + m) * (C / 16);
 #pragma unroll
-      for (int e = 0; e < cnt; ++e)
-        v[e] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, __builtin_amdgcn_readlane(off, e), 0));
+      for (int e = 0; e < cnt; ++e) v[e] = (base + ((uint64_t)(unsigned)__builtin_amdgcn_readlane(off, e) << 4))[col];
     };
-    rows(xv, x0, a.D_in, a.C_in, xoff, uniform(tid / RM) * (RM / 8));
-    rows(dv, d0, a.D_out, a.C_out, doff, uniform(tid / BN) * (BN / 8));
+    rows(xv, x0, a.D_in, a.C_in, xcol, uniform(tid / RM) * (RM / 8));
+    rows(dv, d0, a.D_out, a.C_out, dcol, uniform(tid / BN) * (BN / 8));
   };
   SpWave<RM, BN> w;
   if (nsteps > 0) load(0);

@@ -113,3 +113,43 @@ def test_linear_infinities_and_nans(e3):
         assert (np.isinf(g) == inf).all() and (np.sign(g[inf]) == np.sign(r[inf])).all()
         ok = np.isfinite(r) & (np.abs(r) < 1e30)
         assert rel_l2(g[ok], r[ok]) < 1e-6
+
+
+def test_linear_dw_row_offsets(e3):
+    """Node rows of 164 MB: a chunk's 16 scalar rows lie up to 2.4 GB apart."""
+    import torch
+    n, ci, co = 16, 4096, 16
+    g = torch.Generator(device="cuda").manual_seed(2)
+    L = e3.Linear("+".join([f"{ci}x0e"] + [f"{ci}x999e"] * 5), f"{co}x0e")
+    assert 15 * L.D_in * ci * 4 > 2**31
+    x = torch.zeros(n, L.D_in, ci, device="cuda")
+    x[:, 0] = torch.randn(n, ci, generator=g, device="cuda")
+    W, d = (torch.randn(s, generator=g, device="cuda") for s in ((ci * co,), (n, 1, co)))
+    print("[case] dW row offsets", L.D_in * ci * 4, flush=True)
+    _, dW = L.backward(x, W, d)
+    ref = x[:, 0].double().T.contiguous() @ d[:, 0].double()
+    assert rel_l2(to_np(dW), to_np(ref).reshape(-1)) < 1e-6
+
+
+def test_linear_dw_long_chunks(e3):
+    """Chunks of 2,488,750 rows of a block of 1,991 per node: row number times
+    block height passes 2^32, where a quotient by multiplication needs its
+    correction (at 2,174,171 for the first time)."""
+    import torch
+    n, C, R = 80_000, 16, 1991
+    g = torch.Generator(device="cuda").manual_seed(3)
+    L = e3.Linear(f"{C}x0e+{C}x995e", f"{C}x995e+{C}x0e")
+    x, d = (torch.randn(n, R + 1, C, generator=g, device="cuda") for _ in range(2))
+    W = torch.randn(L.n_weights, generator=g, device="cuda")
+    print("[case] dW long chunks", n * R // 64, flush=True)
+    _, dW = L.backward(x, W, d)
+    ref = torch.zeros(2, C, C, dtype=torch.float64, device="cuda")
+    for a in range(0, n, 4000):
+        xs, ds = x[a:a + 4000].double(), d[a:a + 4000].double()
+        ref[0] += xs[:, 1:].reshape(-1, C).T.contiguous() @ ds[:, :R].reshape(-1, C)
+        ref[1] += xs[:, 0].T.contiguous() @ ds[:, R]
+    # 78,000 sums of 32 rows per chunk, each addition rounding the partial by up
+    # to 6e-8: sqrt(78,000) of them at random leave up to 1.7e-5 of a result,
+    # whose size is that of its random sum; a step of wrong rows gives 1e-2
+    got = to_np(dW).reshape(2, C, C)
+    assert rel_l2(got[0], to_np(ref[0])) < 2e-5 and rel_l2(got[1], to_np(ref[1])) < 1e-6
