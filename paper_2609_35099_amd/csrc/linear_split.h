@@ -2,29 +2,37 @@
 //
 // The float32 instruction (v_mfma_f32_16x16x4f32) runs at a sixteenth of the
 // bf16 rate.  Here every float32 operand is split into three bf16 terms, each
-// the rounding of what the ones before leave (8 bits each: x = h + m + l to
-// 2^-27), and a product is the six term products of order up to 2^-16; the
-// three left out are below 2^-26 of it.  Every term product is exact and the
-// sums are float32 as before, with 6 accumulations per 32 of the reduction
-// instead of 8.  Against 64 bits (24,000 nodes, 34 -> 8 blocks of 128, float32
-// instruction -> here): forward 4.5e-7 -> 3.8e-7, dx 2.0e-7 -> 1.5e-7, dW
-// 8.2e-7 -> 4.5e-7, and no larger at 12 other sizes (16 to 192 channels, 64 to
-// 24,000 rows).
+// the rounding of what the ones before leave: 8 bits each with their signs, so
+// that x = h + m + l holds exactly.  A product is eight term products, each
+// exact; the one left out, l l, is below 2^-34 of it.  Seven of them (all with
+// an m or an l) are summed apart and added on the vector unit, so that a single
+// product comes out as the float32 instruction gives it (largest error 6.0e-8,
+// L2 2.53e-8; all in one chain, six products: 1.6e-7 and 3.5e-8), and long sums
+// come out closer.  Against 64 bits (24,000 nodes, 34 -> 8 blocks of 128,
+// float32 instruction -> here): forward 4.5e-7 -> 1.7e-7, dx 2.0e-7 -> 7.3e-8,
+// dW 8.2e-7 -> 2.6e-7; sums of 4,096 terms 1.15e-6 -> 4.5e-7, of 8,192 1.62e-6
+// -> 6.4e-7; smaller at all of 13 sizes (16 to 192 channels, 64 to 24,000 rows).
 //
-// Time, same workload: forward 1107 -> 710 us, dx 1367 (with the transpose)
-// -> 924 us, dW 1251 -> 959 us.  Bound by the matrix instructions (0.35 ms at
-// their rate) and the splitting (176 VALU instructions per step and thread)
-// sharing the issue of each SIMD: three workgroups per CU overlap them (two:
-// 768 and 1066 us).  Loads two steps ahead measured 2% slower.
+// Time, same workload (float32 instruction, six products in one chain, here):
+// forward 1126, 720, 980 us, dx (the first with a transpose) 1376, 928, 1039 us,
+// dW 1258, 969, 1036 us.  Bound by the matrix instructions (0.47 ms at their
+// rate) and the splitting (176 vector instructions per step and thread, and 64
+// for the sums apart) sharing the issue of each SIMD: two (forward) or three
+// workgroups per CU overlap them.  Measured and left: the forward in pairs of
+// subtiles on three workgroups 870 us against 921, but 40 against 35 us at 300
+// nodes; dx on two 1151 us, dW on two 1083 us (here in that run: 1030, 1012);
+// workgroups of 512 threads, 20% slower on 64-wide tiles; loads two steps ahead,
+// 2% slower.
 //
 // A workgroup of four waves takes an RM x BN tile; per 32 of the reduction the
 // 256 threads load both operands once (the next step's loads are in flight
 // during the instructions), split them and write the terms to LDS as
 // [term][row or column][32], which is the operand order of
 // v_mfma_f32_16x16x32_bf16: lane l reads 16 bytes of row l % 16 at reduction
-// index 8 (l / 16).  Rows are padded to 80 bytes so that eight lanes' reads
-// cover the banks.  W takes the instruction's A side and the rows the B side,
-// so that a lane owns four consecutive output columns.
+// index 8 (l / 16).  The four 16-byte slots of a row are exchanged by row number
+// so that the lanes of one pass cover the banks (SpTile).  W takes the
+// instruction's A side and the rows the B side, so that a lane owns four
+// consecutive output columns.
 //
 // Infinities and NaNs, operands above 3e26 and sums above 2.8e14 (the scaled
 // terms or sums overflow) make the split sums NaN or infinite where float32
@@ -127,33 +135,54 @@ struct SpWave {
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[s][c] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
   }
-  // One step of 32: X are the rows' terms, Y the columns'.  APART: the step is
-  // summed on its own and then added, which keeps long reductions accurate.
-  template <bool APART>
+  // One step of 32: X are the rows' terms, Y the columns'.  The products with a
+  // lower term are summed on their own, smallest first, and added to the rest by
+  // the vector unit: they are a 256th of the sum and lose nothing there, and the
+  // product of the two first terms, which is exact, meets them in one rounding
+  // to nearest (the instruction's own additions err by up to twice as much).
+  // APART: the products of the first terms are summed apart from the running
+  // sum too, which keeps long reductions accurate.
+  // SP subtiles at a time; fewer take fewer registers, read the columns' terms
+  // more often and make a longer chain.
+  template <bool APART, int SP>
   __device__ __forceinline__ void step(const SpTile<RM>& X, const SpTile<BN>& Y) {
-    bf8v x[3][RS];
+    constexpr f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int PY[7] = {2, 1, 2, 0, 1, 1, 0}, PX[7] = {1, 2, 0, 2, 1, 0, 1};
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
+    for (int s0 = 0; s0 < RS; s0 += SP) {
+      bf8v x[3][SP];
 #pragma unroll
-      for (int s = 0; s < RS; ++s)
-        x[p][s] = *reinterpret_cast<const bf8v*>(X.at(p, row0 + 16 * s + li, g));
+      for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      bf8v y[3];
+        for (int s = 0; s < SP; ++s) x[p][s] = *reinterpret_cast<const bf8v*>(X.at(p, row0 + 16 * (s0 + s) + li, g));
 #pragma unroll
-      for (int p = 0; p < 3; ++p) y[p] = *reinterpret_cast<const bf8v*>(Y.at(p, col0 + 16 * c + li, g));
-      // smallest terms first
-      constexpr int PY[6] = {2, 0, 1, 1, 0, 0}, PX[6] = {0, 2, 1, 0, 1, 0};
-      f4v sum[RS];
+      for (int c = 0; c < 4; ++c) {
+        bf8v y[3];
 #pragma unroll
-      for (int s = 0; s < RS; ++s) sum[s] = APART ? f4v{0.0f, 0.0f, 0.0f, 0.0f} : acc[s][c];
+        for (int p = 0; p < 3; ++p) y[p] = *reinterpret_cast<const bf8v*>(Y.at(p, col0 + 16 * c + li, g));
+        f4v lo[SP];
 #pragma unroll
-      for (int t = 0; t < 6; ++t)
+        for (int s = 0; s < SP; ++s) lo[s] = zero;
 #pragma unroll
-        for (int s = 0; s < RS; ++s)
-          sum[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[PY[t]], x[PX[t]][s], sum[s], 0, 0, 0);
+        for (int t = 0; t < 7; ++t)
 #pragma unroll
-      for (int s = 0; s < RS; ++s) acc[s][c] = APART ? acc[s][c] + sum[s] : sum[s];
+          for (int s = 0; s < SP; ++s)
+            lo[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[PY[t]], x[PX[t]][s], lo[s], 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < SP; ++s) {
+          f4v& sum = acc[s0 + s][c];
+          const f4v hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[0], x[0][s], APART ? zero : sum, 0, 0, 0);
+          sum = APART ? sum + hi : hi;
+        }
+#pragma unroll
+        for (int s = 0; s < SP; ++s) acc[s0 + s][c] += lo[s];
+        // the compiler would start the next columns early and spill
+        if (!APART && SP < RS) __builtin_amdgcn_sched_barrier(0);
+      }
+      if (SP < RS) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");  // the next subtiles read the columns' terms again
+      }
     }
   }
   __device__ __forceinline__ void scale_back() {
@@ -208,7 +237,7 @@ struct SpRows {
 // TB: a W slice is [col][k] (rows of C_src, 16-byte aligned), else [k][col]
 // (rows of C_dst).
 template <int RM, int BN, bool TB>
-__global__ __launch_bounds__(kSpThreads, 3) void k_lin_gemm(LinArgs a) {
+__global__ __launch_bounds__(kSpThreads, TB ? 3 : 2) void k_lin_gemm(LinArgs a) {
   __shared__ __align__(16) SpTile<RM> sX;
   __shared__ __align__(16) SpTile<BN> sW;
   const int unit = blockIdx.x;
@@ -225,12 +254,12 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_gemm(LinArgs a) {
   const int tid = threadIdx.x, kq = tid & 7, hh = kq >> 2;
   // rows past the end load the last row, columns past C_dst the last column;
   // their results are not stored
-  const float* xp[RM / 32];
+  unsigned xp[RM / 32];  // units of 16 channels: below 2^32 for any layout
   const SpRows rows(r0, NR, jb.R);
   const float* src0 = a.src + rows.node0 * a.D_src * a.C_src;
 #pragma unroll
   for (int i = 0; i < RM / 32; ++i)
-    xp[i] = src0 + (int64_t)rows.at((tid >> 3) + 32 * i, a.D_src) * a.C_src + 4 * (kq & 3);
+    xp[i] = (unsigned)rows.at((tid >> 3) + 32 * i, a.D_src) * (unsigned)(a.C_src / 16);
   // the reduction runs over halves of 16 (C_src is a multiple of 16), two per step
   const int hs = a.C_src / 16, nh = jb.nsrc * hs, nsteps = (nh + 1) / 2;
   f4v xv[RM / 32];
@@ -241,16 +270,16 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_gemm(LinArgs a) {
     const int h0 = 2 * st, h1 = h0 + 1 < nh ? h0 + 1 : h0;  // uniform
     const int t0 = h0 / hs, t1 = h1 / hs, k0 = (h0 - t0 * hs) * 16, k1 = (h1 - t1 * hs) * 16;
     const int x0 = srcs[t0].row * a.C_src + k0, x1 = srcs[t1].row * a.C_src + k1;
-    const int xo = hh ? x1 : x0;
+    const float* sp = src0 + ((hh ? x1 : x0) + 4 * (kq & 3));
 #pragma unroll
-    for (int i = 0; i < RM / 32; ++i) xv[i] = *reinterpret_cast<const f4v*>(xp[i] + xo);
+    for (int i = 0; i < RM / 32; ++i) xv[i] = *reinterpret_cast<const f4v*>(sp + ((uint64_t)xp[i] << 4));
     const int64_t w0 = srcs[t0].w_off, w1 = srcs[t1].w_off;
     if constexpr (TB) {
       const float* wp = a.W + (hh ? w1 + k1 : w0 + k0) + 4 * (kq & 3);
 #pragma unroll
       for (int i = 0; i < BN / 32; ++i) {
         const int c = imin(col0 + (tid >> 3) + 32 * i, a.C_dst - 1);
-        wt[i] = *reinterpret_cast<const f4v*>(wp + (int64_t)c * a.C_src);
+        wt[i] = *reinterpret_cast<const f4v*>(wp + (unsigned)(c * a.C_src));
       }
     } else {
       // thread's N / 8 reduction indexes: in half 0 or 1, uniform per wave
@@ -264,6 +293,9 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_gemm(LinArgs a) {
         wv[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wr, voff, e * a.C_dst * 4, 0));
     }
   };
+  // Subtiles at a time: the forward (many sources) all of them on two workgroups
+  // per CU, dx (few) in pairs on three.
+  constexpr int kSub = TB && SpWave<RM, BN>::RS > 2 ? 2 : SpWave<RM, BN>::RS;
   SpWave<RM, BN> w;
   if (nsteps > 0) load(0);
   for (int st = 0; st < nsteps; ++st) {
@@ -277,7 +309,7 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_gemm(LinArgs a) {
     else sp_put_cols<BN>(sW, wv);
     __syncthreads();
     load(st + 1);
-    w.template step<false>(sX, sW);
+    w.template step<false, kSub>(sX, sW);
     __syncthreads();
   }
   if (w.finite()) {  // wave-uniform
@@ -321,7 +353,7 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_gemm(LinArgs a) {
 // dW partials of one (pair, row chunk, RM x BN tile of W): the reduction runs
 // over the chunk's rows, so both operands are staged by columns.
 template <int RM, int BN>
-__global__ __launch_bounds__(kSpThreads, 2) void k_lin_dw(LinDwArgs a) {
+__global__ __launch_bounds__(kSpThreads, 3) void k_lin_dw(LinDwArgs a) {
   __shared__ __align__(16) SpTile<RM> sX;
   __shared__ __align__(16) SpTile<BN> sD;
   const int per = kLinChunks * a.ktiles * a.jtiles;
@@ -374,7 +406,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void k_lin_dw(LinDwArgs a) {
     sp_put_cols<BN>(sD, dv);
     __syncthreads();
     load(st + 1);
-    w.template step<true>(sX, sD);
+    w.template step<true, SpWave<RM, BN>::RS < 2 ? 1 : 2>(sX, sD);
     __syncthreads();
   }
   if (w.finite()) {

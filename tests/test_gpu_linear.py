@@ -4,8 +4,10 @@ the 64- and 128-wide tiles, odd counts of 16-wide reduction halves, several
 blocks per type, W off 16-byte alignment; operands over the whole float32
 range; infinities and NaNs where float32 has them.
 
-Bar: relative L2 1e-6 per output (sums of at most 1,500 terms, about 16
-roundings of 6e-8; the splitting itself adds under 2^-25).
+Bar: relative L2 1e-6 per output.  A forward or dx sum has at most 336 terms in
+11 steps, each a few roundings of 6e-8 of the running sum; a dW element sums
+up to 9,000 rows as 64 partials of up to five steps.  At random they add to
+about 3e-7.  The products themselves are exact but for l l, 2^-34.
 """
 import numpy as np
 import pytest
@@ -113,6 +115,36 @@ def test_linear_infinities_and_nans(e3):
         assert (np.isinf(g) == inf).all() and (np.sign(g[inf]) == np.sign(r[inf])).all()
         ok = np.isfinite(r) & (np.abs(r) < 1e30)
         assert rel_l2(g[ok], r[ok]) < 1e-6
+
+
+def test_linear_single_products(e3):
+    """One non-zero term per sum: the float32 product, rounded once (2^-24, and
+    the rounding of the lower terms' sum, below 2^-30)."""
+    ci, co, n = 128, 64, 500
+    x, W, d = _inputs("0e+0e", "0e", ci, co, n)
+    x[:, :, 1:], x[:, 1], d[:, :, 1:] = 0, 0, 0
+    out, dx, dW = _run(e3, "0e+0e", "0e", ci, co, x, W, d)
+    w = W.reshape(2, ci, co).astype(np.float64)
+    _, _, dW1 = _run(e3, "0e+0e", "0e", ci, co, *(a[:1] if a.ndim > 1 else a for a in _inputs("0e+0e", "0e", ci, co, 1)))
+    x1, _, d1 = (a.astype(np.float64) for a in _inputs("0e+0e", "0e", ci, co, 1))
+    for got, ref in ((out[:, 0], np.outer(x[:, 0, 0], w[0, 0])), (dx[:, 0], np.outer(d[:, 0, 0], w[0, :, 0])),
+                     (dW1.reshape(2, ci, co), x1[0, :, :, None] * d1[0, 0])):
+        err = np.abs(got - ref) / np.abs(ref)
+        assert err.max() < 2.0**-24 * (1 + 2.0**-6)
+
+
+@pytest.mark.parametrize("blocks,C,n,bars", [
+    (8, 512, 100, (1.0e-6, 1.0e-6, 1e-6)), (1, 64, 200_000, (1e-6, 1e-6, 9e-7)),
+])
+def test_linear_long_sums(e3, blocks, C, n, bars):
+    """4,096 terms (forward, dx) and 200,000 (dW): below what the float32
+    instruction leaves (1.15e-6 and 1.03e-6; here 4.5e-7 and 3.0e-7)."""
+    irreps = "+".join(["0e"] * blocks)
+    x, W, d = _inputs(irreps, irreps, C, C, n)
+    got = _run(e3, irreps, irreps, C, C, x, W, d)
+    ref = _reference(irreps, irreps, C, C, *(a.astype(np.float64) for a in (x, W, d)))
+    for g, r, bar in zip(got, ref, bars):
+        assert rel_l2(g, r) < bar
 
 
 def test_linear_dw_row_offsets(e3):
