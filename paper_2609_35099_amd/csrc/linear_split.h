@@ -36,8 +36,9 @@
 //
 // Infinities and NaNs, operands above 3e26 and sums above 2.8e14 (the scaled
 // terms or sums overflow) make the split sums NaN or infinite where float32
-// would not: a wave whose sums are not all finite computes its part of the
-// tile again with the float32 instruction.
+// would not: those elements are computed again with the float32 instruction.
+// With every operand past the limit: forward 2147 us, dx 2263, dW 2884; with an
+// infinity in every 500th node: as without.
 #pragma once
 
 namespace {
@@ -127,9 +128,6 @@ struct SpWave {
   __device__ __forceinline__ SpWave() {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     row0 = (w / WC) * 16 * RS, col0 = (w % WC) * 64, li = lane & 15, g = lane >> 4;
-    zero();
-  }
-  __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int s = 0; s < RS; ++s)
 #pragma unroll
@@ -185,21 +183,58 @@ struct SpWave {
       }
     }
   }
-  __device__ __forceinline__ void scale_back() {
+  // The results: the sums scaled back, and in the place of one that is not
+  // finite what the float32 instruction gives, so that an element depends on its
+  // own row and column alone.  row(s, k), col(c, k): the operands at reduction
+  // indexes k + 4 g .. + 3 of the lane's row of subtile s and column of subtile c.
+  template <class FR, class FC>
+  __device__ __forceinline__ void finish(int kn, FR&& row, FC&& col) {
+    constexpr int SP = RS < 2 ? 1 : 2;
 #pragma unroll
-    for (int s = 0; s < RS; ++s)
+    for (int s0 = 0; s0 < RS; s0 += SP) {
+      float z = 0.0f;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[s][c] *= kSpBack;
-  }
-  __device__ __forceinline__ bool finite() const {
-    float z = 0.0f;
+      for (int s = s0; s < s0 + SP; ++s)
 #pragma unroll
-    for (int s = 0; s < RS; ++s)
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+          for (int r = 0; r < 4; ++r) z += acc[s][c][r] * 0.0f;
+      if (__ballot(z != 0.0f) == 0) {  // no NaN in any lane: all finite
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z += acc[s][c][r] * 0.0f;
-    return __ballot(z != 0.0f) == 0;  // a NaN in any lane
+        for (int s = s0; s < s0 + SP; ++s)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[s][c] *= kSpBack;
+        continue;
+      }
+      f4v t[SP][4];
+#pragma unroll
+      for (int s = 0; s < SP; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) t[s][c] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int k = 0; k < kn; k += 16) {
+        f4v x[SP], y[4];
+#pragma unroll
+        for (int s = 0; s < SP; ++s) x[s] = row(s0 + s, k);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y[c] = col(c, k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int s = 0; s < SP; ++s)
+              t[s][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[c][e], x[s][e], t[s][c], 0, 0, 0);
+      }
+#pragma unroll
+      for (int s = 0; s < SP; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float v = acc[s0 + s][c][r];
+            acc[s0 + s][c][r] = v * 0.0f == 0.0f ? v * kSpBack : t[s][c][r];
+          }
+    }
   }
 };
 
@@ -312,31 +347,22 @@ __global__ __launch_bounds__(kSpThreads, TB ? 3 : 2) void k_lin_gemm(LinArgs a) 
     w.template step<false, kSub>(sX, sW);
     __syncthreads();
   }
-  if (w.finite()) {  // wave-uniform
-    w.scale_back();
-  } else {
-    w.zero();
-    const float* rp[SpWave<RM, BN>::RS];
+  w.finish(jb.nsrc * a.C_src,
+           [&](int s, int k) {
+             const int t = k / a.C_src, d = w.row0 + 16 * s + w.li;
+             return *reinterpret_cast<const f4v*>(src0 + ((int64_t)rows.at(d, a.D_src) + srcs[t].row) * a.C_src +
+                                                  (k - t * a.C_src + 4 * w.g));
+           },
+           [&](int c, int k) {
+             const int t = k / a.C_src, kk = k - t * a.C_src + 4 * w.g;
+             const int col = imin(col0 + w.col0 + 16 * c + w.li, a.C_dst - 1);
+             const float* p = a.W + srcs[t].w_off;
+             if constexpr (TB) return *reinterpret_cast<const f4v*>(p + ((int64_t)col * a.C_src + kk));
+             f4v v;
 #pragma unroll
-    for (int s = 0; s < SpWave<RM, BN>::RS; ++s)
-      rp[s] = src0 + (int64_t)rows.at(w.row0 + 16 * s + w.li, a.D_src) * a.C_src + w.g;
-    for (int t = 0; t < jb.nsrc; ++t)
-      for (int k = 0; k < a.C_src; k += 4) {
-        float x[SpWave<RM, BN>::RS], y[4];
-#pragma unroll
-        for (int s = 0; s < SpWave<RM, BN>::RS; ++s) x[s] = rp[s][srcs[t].row * a.C_src + k];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int col = imin(col0 + w.col0 + 16 * c + w.li, a.C_dst - 1);
-          y[c] = a.W[srcs[t].w_off + (TB ? (int64_t)col * a.C_src + k + w.g : (int64_t)(k + w.g) * a.C_dst + col)];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-          for (int s = 0; s < SpWave<RM, BN>::RS; ++s)
-            w.acc[s][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[c], x[s], w.acc[s][c], 0, 0, 0);
-      }
-  }
+             for (int e = 0; e < 4; ++e) v[e] = p[(int64_t)(kk + e) * a.C_dst + col];
+             return v;
+           });
   float* dst0 = a.dst + (rows.node0 * a.D_dst + jb.dst_row) * a.C_dst;
   // lane l of acc[s][c]: row l % 16 of subtile s, columns 4 (l / 16) .. +3 of subtile c
 #pragma unroll
@@ -409,28 +435,20 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_dw(LinDwArgs a) {
     w.template step<true, SpWave<RM, BN>::RS < 2 ? 1 : 2>(sX, sD);
     __syncthreads();
   }
-  if (w.finite()) {
-    w.scale_back();
-  } else {
-    w.zero();
-    for (int k = 0; k < nrows; k += 4) {
-      const bool ok = k + w.g < nrows;
-      const int64_t r = rb + (ok ? k + w.g : 0);
-      const float* xr = a.x + ((r / R) * a.D_in + pr.src_row + r % R) * a.C_in;
-      const float* dr = a.dout + ((r / R) * a.D_out + pr.dst_row + r % R) * a.C_out;
-      float x[SpWave<RM, BN>::RS], d[4];
+  auto operand = [&](const float* p, int D, int row, int C, int ch, int k) {
+    f4v v;
 #pragma unroll
-      for (int s = 0; s < SpWave<RM, BN>::RS; ++s)
-        x[s] = ok ? xr[imin(kc0 + w.row0 + 16 * s + w.li, a.C_in - 1)] : 0.0f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) d[c] = ok ? dr[imin(jc0 + w.col0 + 16 * c + w.li, a.C_out - 1)] : 0.0f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int s = 0; s < SpWave<RM, BN>::RS; ++s)
-          w.acc[s][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[c], x[s], w.acc[s][c], 0, 0, 0);
+    for (int e = 0; e < 4; ++e) {
+      const int i = k + 4 * w.g + e;  // rows past the end: zero
+      const int64_t r = rb + imin(i, nrows - 1);
+      const float u = p[((r / R) * D + row + r % R) * C + imin(ch, C - 1)];
+      v[e] = i < nrows ? u : 0.0f;
     }
-  }
+    return v;
+  };
+  w.finish(nrows,
+           [&](int s, int k) { return operand(a.x, a.D_in, pr.src_row, a.C_in, kc0 + w.row0 + 16 * s + w.li, k); },
+           [&](int c, int k) { return operand(a.dout, a.D_out, pr.dst_row, a.C_out, jc0 + w.col0 + 16 * c + w.li, k); });
   float* out = a.dWp + ((int64_t)p * kLinChunks + chunk) * a.C_in * a.C_out;
 #pragma unroll
   for (int s = 0; s < SpWave<RM, BN>::RS; ++s) {

@@ -185,3 +185,22 @@ def test_linear_dw_long_chunks(e3):
     # whose size is that of its random sum; a step of wrong rows gives 1e-2
     got = to_np(dW).reshape(2, C, C)
     assert rel_l2(got[0], to_np(ref[0])) < 2e-5 and rel_l2(got[1], to_np(ref[1])) < 1e-6
+
+
+def test_linear_elements_depend_on_their_own_operands(e3):
+    """Infinities, NaNs and operands that the terms cannot hold change no bit of
+    any other row (forward, dx) or channel pair (dW)."""
+    ins = outs = "0e+1o"
+    ci, co, n = 64, 128, 400
+    x, W, d = _inputs(ins, outs, ci, co, n)
+    clean = _run(e3, ins, outs, ci, co, x, W, d)
+    xr, xc, dr, dc = [5, 9, 130], [7, 40], [20, 300], [3, 100]
+    x[5, :, 7], x[9, 2, 7], x[130, 0, 40], d[20, :, 3], d[300, 1, 100] = np.inf, np.nan, 1e30, -np.inf, 3.4e38
+    out, dx, dW = _run(e3, ins, outs, ci, co, x, W, d)
+    for got, ref, rows in ((out, clean[0], xr), (dx, clean[1], dr)):
+        keep = np.setdiff1d(np.arange(n), rows)
+        assert (got[keep] == ref[keep]).all()
+        assert not np.isfinite(got[rows[0]]).any()
+    k, j = np.setdiff1d(np.arange(ci), xc), np.setdiff1d(np.arange(co), dc)
+    got, ref = (a.reshape(2, ci, co)[:, k][:, :, j] for a in (dW, clean[2]))
+    assert (got == ref).all()
