@@ -189,19 +189,17 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
   const int lane = threadIdx.x, C = a.C;
   constexpr int kPairs = RB * kWave;
   // first row and channel of the tile, and its number of pairs
-  const int64_t tile = blockIdx.x;
+  const int64_t tile = block_id();
   int64_t r0;
   int c0, np;
   if constexpr (RED) {
-    if (a.pieces == 1) {
-      r0 = tile * a.rpt, c0 = 0;
-      np = (int)(a.rows - r0 < a.rpt ? a.rows - r0 : a.rpt) * C;
-    } else {
-      r0 = tile / a.pieces, c0 = (int)(tile % a.pieces) * kPairs;
-      np = imin(kPairs, C - c0);
-    }
+    r0 = a.pieces == 1 ? tile * a.rpt : tile / a.pieces;
+    if (r0 >= a.rows) return;
+    c0 = a.pieces == 1 ? 0 : (int)(tile % a.pieces) * kPairs;
+    np = a.pieces == 1 ? (int)(a.rows - r0 < a.rpt ? a.rows - r0 : a.rpt) * C : imin(kPairs, C - c0);
   } else {
     const int64_t p0 = tile * kPairs, left = a.rows * C - p0;
+    if (left <= 0) return;
     r0 = p0 / C, c0 = (int)(p0 - r0 * C);
     np = left < kPairs ? (int)left : kPairs;
   }
@@ -1363,7 +1361,7 @@ e3_status lin_gemm(const std::vector<LinJob>& jobs, const LinJob* djobs, const L
   auto* k = wt ? (bn == 128 ? k_lin_gemm<kLinRows, 128, true> : k_lin_gemm<kLinRows, 64, true>)
                : (bn == 128 ? k_lin_gemm<kLinRows, 128, false> : k_lin_gemm<kLinRows, 64, false>);
   TimedLaunch t_(name, st);
-  hipLaunchKernelGGL(k, dim3((unsigned)u), dim3(kSpThreads), 0, st, a);
+  hipLaunchKernelGGL(k, grid_of(u), dim3(kSpThreads), 0, st, a);
   E3_HIP(hipGetLastError());
   return E3_OK;
 }
@@ -1655,7 +1653,7 @@ e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, in
     // over 64 KiB only in float64 with a shared B of many rows
     if (lds > kTpgMaxLds)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kWave), lds, st, a);
+    hipLaunchKernelGGL(k, grid_of(grid), dim3(kWave), lds, st, a);
   };
   if (rb == 4)
     go(std::integral_constant<int, 4>{});

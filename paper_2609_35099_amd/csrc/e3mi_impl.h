@@ -118,6 +118,15 @@ struct TimedLaunch {
 constexpr int kWave = 64;
 constexpr int kXcd = 8;
 
+// A launch of 2^32 threads or more along x wraps without an error, so a grid of
+// many blocks folds into y: block_id() is the block's number, and the kernel
+// returns where it is past the last one.  kGridX is a multiple of kXcd.
+constexpr int kGridX = 1 << 22;  // times 256 threads
+inline dim3 grid_of(int64_t blocks) {
+  return blocks <= kGridX ? dim3((unsigned)blocks) : dim3(kGridX, (unsigned)((blocks + kGridX - 1) / kGridX));
+}
+__device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * kGridX + blockIdx.x; }
+
 // Row-tile kernels (tensor product, its backward, the record path): block ->
 // (tile, part).  With XCD, the `per` parts (groups, channel slabs) of tile T
 // run on XCD T % 8 in consecutive dispatch rounds, so that the parts of one
@@ -1275,12 +1284,12 @@ constexpr int kDxThreads = 256;
 template <class T>
 __device__ __forceinline__ void dx_short_block(const T* __restrict__ P, T* __restrict__ dx,
                                                const int* __restrict__ rowptr_s, int n_nodes, int chunk, int units,
-                                               int accum, int block) {
+                                               int accum, int64_t block) {
   constexpr int W = 16 / sizeof(T);
   typedef T Vt __attribute__((ext_vector_type(W)));
   __shared__ Vt part[kDxThreads];
-  const int node = (block % kXcd) * chunk + block / kXcd;
-  if (node >= n_nodes) return;
+  const int rl = (int)(block / kXcd), node = (int)(block % kXcd) * chunk + rl;
+  if (rl >= chunk || node >= n_nodes) return;
   const int S = kDxThreads / units, tid = threadIdx.x;
   const int sub = tid / units, u = tid - sub * units;
   const int s0 = rowptr_s[node], s1 = rowptr_s[node + 1];
@@ -1303,7 +1312,7 @@ template <class T>
 __global__ __launch_bounds__(kDxThreads) void k_conv_bwd_dx_short(const T* __restrict__ P, T* __restrict__ dx,
                                                                   const int* __restrict__ rowptr_s, int n_nodes,
                                                                   int chunk, int units, int accum) {
-  dx_short_block(P, dx, rowptr_s, n_nodes, chunk, units, accum, (int)blockIdx.x);
+  dx_short_block(P, dx, rowptr_s, n_nodes, chunk, units, accum, block_id());
 }
 
 // dvec of each live edge from its harmonic cotangent (summed over groups).
@@ -1360,9 +1369,9 @@ struct FinishArgs {
 
 template <int L>
 __global__ __launch_bounds__(kDxThreads) void k_conv_bwd_finish(FinishArgs a) {
-  int64_t b = blockIdx.x;
+  int64_t b = block_id();
   if (b < a.dx_blocks) {
-    dx_short_block(a.P, a.dx, a.rowptr_s, a.n_nodes, a.chunk, a.units, 0, (int)b);
+    dx_short_block(a.P, a.dx, a.rowptr_s, a.n_nodes, a.chunk, a.units, 0, b);
     return;
   }
   b -= a.dx_blocks;
@@ -2877,7 +2886,7 @@ template <class T>
 void dx_sum(const T* P, T* dx, const e3_graph* g, int width, int accum, hipStream_t st) {
   const int chunk = (int)((g->n_nodes + kXcd - 1) / kXcd), units = width / (16 / (int)sizeof(T));
   if (units <= kDxShort) {
-    hipLaunchKernelGGL(k_conv_bwd_dx_short<T>, dim3((unsigned)(kXcd * chunk)), dim3(kDxThreads), 0, st, P, dx,
+    hipLaunchKernelGGL(k_conv_bwd_dx_short<T>, grid_of((int64_t)kXcd * chunk), dim3(kDxThreads), 0, st, P, dx,
                        g->rowptr_s, (int)g->n_nodes, chunk, units, accum);
     return;
   }
@@ -2898,10 +2907,8 @@ bool launch_finish(const e3_plan* p, const e3_graph* g, const float* P, float* d
   a.nparts = nparts, a.n_live = g->n_live, a.n_pad = g->n_pad;
   a.ds_width = (int64_t)p->lay.paths.size() * p->lay.C;
   a.dx_blocks = (int64_t)kXcd * a.chunk, a.dvec_blocks = (g->n_live + kDxThreads - 1) / kDxThreads;
-  const int64_t blocks = a.dx_blocks + a.dvec_blocks + a.n_pad;
-  if (blocks > 0x7fffffff) return false;
   TimedLaunch t_("conv_bwd_finish", st);
-  hipLaunchKernelGGL(k_conv_bwd_finish<L>, dim3((unsigned)blocks), dim3(kDxThreads), 0, st, a);
+  hipLaunchKernelGGL(k_conv_bwd_finish<L>, grid_of(a.dx_blocks + a.dvec_blocks + a.n_pad), dim3(kDxThreads), 0, st, a);
   return true;
 }
 

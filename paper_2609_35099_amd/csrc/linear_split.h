@@ -275,7 +275,9 @@ template <int RM, int BN, bool TB>
 __global__ __launch_bounds__(kSpThreads, TB ? 3 : 2) void k_lin_gemm(LinArgs a) {
   __shared__ __align__(16) SpTile<RM> sX;
   __shared__ __align__(16) SpTile<BN> sW;
-  const int unit = blockIdx.x;
+  const int64_t block = block_id();
+  if (block >= a.first[a.njobs]) return;
+  const int unit = (int)block;
   int lo = 0, hi = a.njobs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;

@@ -76,3 +76,20 @@ def test_wide_shared_operands_f64(e3):
     for a, b, c, w in zip(i0, i1, i2, val):
         ref[:, a] += w * x[:, b] * y[:, c, None]
     assert rel_l2(to_np(z), ref) < 1e-14
+
+
+def test_more_tiles_than_a_grid_row(e3):
+    """4.3e9 (row, channel) pairs at one pair per lane: 2^32 threads and more, which
+    a launch wraps without an error if they lie along x."""
+    import torch
+    rows, C = 43_000_000, 100
+    g = torch.Generator(device="cuda").manual_seed(1)
+    k = np.arange(40, dtype=np.int32)
+    tp = e3.RecordTP(1, 40, 1, 0 * k, 0 * k, k, np.ones(40), y_per_channel=False)
+    x = torch.randn(rows, 1, C, generator=g, device="cuda")
+    y = torch.randn(rows, 40, generator=g, device="cuda")
+    print("[case] many tiles", rows * C, flush=True)
+    z = tp.forward(x, y)
+    for a in range(0, rows, 4_000_000):
+        ref = x[a:a + 4_000_000, 0].double() * y[a:a + 4_000_000].double().sum(1, keepdim=True)
+        assert float((z[a:a + 4_000_000, 0].double() - ref).norm() / ref.norm()) < 1e-6

@@ -163,3 +163,35 @@ def test_tensor_product_row_pieces(e3, C):
     print("[case] tp", C, plan.kernels, flush=True)
     z = to_np(e3.tp_fwd(plan, to_dev(x), to_dev(y), to_dev(w)))
     assert rel_l2(z, otp.tp(lay, x, y, w).numpy()) < TOL
+
+
+# a launch holds fewer than 2^32 threads: 17 million nodes with 256 threads each
+# pass that, as do 10 million nodes and as many padding edges in one launch
+@pytest.mark.parametrize("n,n_pad,f64", [(17_000_000, 0, False), (17_000_000, 0, True), (10_000_000, 10_000_000, False)])
+def test_segment_sum_of_many_nodes(e3, n, n_pad, f64):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dt, live = torch.float64 if f64 else torch.float32, 3000
+    pad, E = (n - 1 if n_pad else -1), live + n_pad
+    plan = e3.Plan("4x0e", 1, 1)
+    print("[case] many nodes", n, n_pad, f64, plan.kernels, flush=True)
+    snd, rcv = (torch.randint(0, n - 1, (E,), generator=g, device="cuda", dtype=torch.int32) for _ in range(2))
+    snd[0], snd[1], rcv[2] = n - 2, 0, n - 2
+    snd[live:] = pad
+    x, vec, s, dm = (torch.randn(sh, generator=g, device="cuda", dtype=dt) for sh in
+                     ((n, 1, 4), (E, 3), (E, plan.P, 4), (n, plan.D_out, 4)))
+    G = e3.Graph(snd, rcv, n, pad_node=pad)
+    bwd = e3.conv_bwd_f64 if f64 else e3.conv_bwd
+    torch.cuda.empty_cache()
+    for shape in ((n, 1, 4), (E, 3), (E, plan.P, 4)):  # what the outputs may reuse holds no zeros
+        torch.full(shape, float("nan"), device="cuda", dtype=dt)
+    dx, dvec, ds = bwd(plan, G, x, vec, s, dm)
+    # the nodes that the live edges touch, renumbered for the oracle; dx is zero elsewhere
+    nodes, inv = torch.unique(torch.cat([snd[:live], rcv[:live]]).long(), return_inverse=True)
+    lay = oirreps.layout("4x0e", 1, 1)
+    ref = oconv.conv_bwd(lay, *(to_np(a) for a in (x[nodes], vec[:live], s[:live], dm[nodes], inv[:live], inv[live:])),
+                         len(nodes))
+    for got, want in ((dx[nodes], ref["dx"]), (dvec[:live], ref["dvec"]), (ds[:live], ref["ds"])):
+        assert rel_l2(to_np(got), want.numpy()) < (TOL64 if f64 else TOL)
+    dx[nodes] = 0
+    assert not dx.any() and not ds[live:].any() and not dvec[live:].any()
