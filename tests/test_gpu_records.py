@@ -3,8 +3,11 @@ tiles: record counts around a chunk of 64 and the look-ahead, output rows
 without records (first, last, in between), row and channel remainders, both
 kinds of y, both precisions, against a float64 sum record by record.
 
-Bars: each output row sums at most 140 terms; rel-L2 1e-6 in float32 (about 16
-roundings of 6e-8) and 1e-14 in float64.
+Bars: rel-L2 1e-6 in float32 and 1e-14 in float64.  An output row sums at most
+137 records, and a shared y's cotangent those of its channels too, in runs of
+64 (137 records over 4 output rows, 320 channels: chains of 137, 64 and 5); at
+random the roundings of such chains, each 6e-8 of a partial sum at most, add to
+under 16 of them.
 """
 import numpy as np
 import pytest
@@ -93,3 +96,22 @@ def test_more_tiles_than_a_grid_row(e3):
     for a in range(0, rows, 4_000_000):
         ref = x[a:a + 4_000_000, 0].double() * y[a:a + 4_000_000].double().sum(1, keepdim=True)
         assert float((z[a:a + 4_000_000, 0].double() - ref).norm() / ref.norm()) < 1e-6
+
+
+@pytest.mark.parametrize("C", [64, 100, 128, 256, 320])
+def test_shared_y_channel_sum(e3, C):
+    """One record: dy sums C products of one sign.  Runs of at most 64 channels,
+    then the runs: no further from float64 than that order in numpy (1.1: the
+    order within a run differs)."""
+    rng = np.random.default_rng(C)
+    rows = 20_000
+    tp = e3.RecordTP(1, 1, 1, *(np.zeros(1, np.int32) for _ in range(3)), np.ones(1), y_per_channel=False)
+    x, dz = (rng.uniform(0.5, 1.5, (rows, 1, C)).astype(np.float32) for _ in range(2))
+    y = np.ones((rows, 1), np.float32)
+    print("[case] channel sum", C, flush=True)
+    _, gy = tp.backward(to_dev(x), to_dev(y), to_dev(dz))
+    prod = x[:, 0] * dz[:, 0]
+    runs = [np.cumsum(prod[:, a:a + 64], 1, dtype=np.float32)[:, -1:] for a in range(0, C, 64)]
+    want = np.cumsum(np.concatenate(runs, 1), 1, dtype=np.float32)[:, -1]
+    ref = (x[:, 0].astype(np.float64) * dz[:, 0]).sum(1)
+    assert rel_l2(to_np(gy)[:, 0], ref) < 1.1 * rel_l2(want, ref)
