@@ -275,7 +275,16 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
         const T* qa = sA + __builtin_amdgcn_readlane(my_a, k + j) + lane;
         const T* qb = sB + __builtin_amdgcn_readlane(my_b, k + j) + (BM == kTpgBOnce ? 0 : lane);
 #pragma unroll
-        for (int u = 0; u < RB; ++u) va[j][u] = qa[u * kWave], vb[j][u] = qb[u * kBLanes];
+        for (int u = 0; u < RB; ++u) va[j][u] = qa[u * kWave];
+        if constexpr (BM == kTpgBOnce && RB > 1) {  // the values of a row of B in one read
+          typedef T Bv __attribute__((ext_vector_type(RB)));
+          const Bv b = *reinterpret_cast<const Bv*>(qb);
+#pragma unroll
+          for (int u = 0; u < RB; ++u) vb[j][u] = b[u];
+        } else {
+#pragma unroll
+          for (int u = 0; u < RB; ++u) vb[j][u] = qb[u * kBLanes];
+        }
       }
     };
     auto use = [&](int k, const T (&va)[kTpgAhead][RB], const T (&vb)[kTpgAhead][RB]) {
@@ -1633,8 +1642,9 @@ e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, in
   if ((int64_t)rows_per * std::max(dA, dB) * C * (int64_t)sizeof(T) > 0x7fffffff) return E3_ERR_INVALID_ARG;
   // Pairs per lane.  A shared B is staged once per 64 pairs where that leaves
   // room for more of them (9 + 16 operand rows, 351 records, 100,000 rows of 128
-  // channels: 1160 us with four against 1390 with two); at the same number the
-  // copies per lane read faster (106 + 16 rows: 3230 against 3670 us).
+  // channels: 1160 us with four against 1390 with two; 9 + 9 rows, 50,000 rows of
+  // 128 channels 147 against 188); at the same number the copies per lane read
+  // faster (106 + 16 rows: 3230 against 3670 us).
   auto pairs_that_fit = [&](bool b_once) {
     int r = 4;
     while (r > 1 && tpg_lds(dA, dB, a.dout, b_once, red, sizeof(T), r) > kTpgWant) r /= 2;
