@@ -119,13 +119,16 @@ namespace {
 // their rate), so nothing in the chain waits alone: the float32 operands go
 // straight to LDS with every load in flight at once; a chunk of 64 records is
 // one coalesced load, a record per lane, handed out by v_readlane (scalar loads
-// would share the LDS reads' wait counter); the operands of the next kTpgAhead
-// records are read while the current ones are used, and a group of records in
-// which no segment ends takes no branches.  Per kernel, with 9 + 9 operand rows
-// and 137 records (30,011 rows, C = 100): 189 -> 117 us (2.8 TB/s); 16 + 16
-// rows, 611 records (20,000 rows, C = 64) 303 -> 218 us; 9 + 4 rows, 59 records
-// (40,000 rows, C = 12) 46 -> 16 us; 16 records (50,000 rows, C = 128), at 4.9
-// TB/s before, 62 us either way.  kTpgAhead = 4: 120 and 237 us.
+// would share the LDS reads' wait counter), and the next chunk's is in flight;
+// the operands of the next AH records are read while the current ones are used,
+// and a group of records in which no segment ends takes no branches.  Per
+// kernel, against scalar records, rows of four and slabs of 64 channels: 9 + 9
+// operand rows and 137 records (30,011 rows, C = 100) 189 -> 111 us; 16 + 16
+// rows, 611 records (20,000 rows, C = 64) 303 -> 210 us; 16 records (50,000 rows,
+// C = 128) 63 -> 58 us.  A shared B, staged per channel as well at first, had
+// lost to that (9 + 16 rows, 100,000 rows, C = 128: forward 531, then 663 us, dx
+// 707, then 1053); staged once it takes 562 and 680 us, and with 9 + 9 rows
+// (50,000 rows, C = 128) 135 and 136 us against 148 and 152.
 constexpr int kTpgAhead = 8;
 
 // A segment's last record carries kTpgEnd; a segment without records has one
@@ -165,6 +168,9 @@ __device__ __forceinline__ double lane_of(double v, int l) {
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
+// Rows that `pairs` consecutive (row, channel) pairs can touch.
+__host__ __device__ inline int tpg_tile_rows(int C, int pairs) { return (C + pairs - 2) / C + 1; }
+
 template <class T>
 __device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, int off, int soff) {
   if constexpr (sizeof(T) == 8)
@@ -173,19 +179,20 @@ __device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, int off, int soff)
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
 }
 
-// B: one value per (row, channel), or shared by the channels of a row and staged
-// per lane, or shared and staged once per 64 pairs (C % 64 == 0, where they lie
-// in one row).
-enum TpgB { kTpgBOwn, kTpgBShared, kTpgBOnce };
+// B: one value per (row, channel); or shared by the channels of a row and
+// staged per row of the tile, each lane with its own row's address; or shared
+// and staged per 64 pairs (C % 64 == 0, where they lie in one row), the values
+// of a lane's pairs side by side.
+enum TpgB { kTpgBOwn, kTpgBRow, kTpgBOnce };
 
-template <class T, int BM, bool RED, int RB>
+// AH: records whose operands are read ahead (4 or kTpgAhead).
+template <class T, int BM, bool RED, int RB, int AH>
 __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   T* sA = reinterpret_cast<T*>(lds_raw);     // [dA][RB][64]
   constexpr bool BSH = BM != kTpgBOwn;
-  constexpr int kBLanes = BM == kTpgBOnce ? 1 : kWave;
-  T* sB = sA + a.dA * RB * kWave;            // [dB][RB][64], kTpgBOnce: [dB][RB]
-  T* sP = sB + a.dB * RB * kBLanes;          // RED: [dout][RB][64]
+  T* sB = sA + a.dA * RB * kWave;            // [dB][RB][64], kTpgBRow: [rows][dB | 1], kTpgBOnce: [dB][RB]
+  T* sP = sB + a.dB * RB * kWave;            // RED (own B): [dout][RB][64]
   const int lane = threadIdx.x, C = a.C;
   constexpr int kPairs = RB * kWave;
   // first row and channel of the tile, and its number of pairs
@@ -205,13 +212,15 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
   }
   // the lane's pairs: row r0 + dr, channel q; operand offsets from row r0
   unsigned offA[RB], offB[RB];
+  int rowB[RB];  // kTpgBRow: the pair's row in sB
   T* po[RB];
 #pragma unroll
   for (int u = 0; u < RB; ++u) {
     const int i = u * kWave + lane, at = c0 + i, dr = at / C, q = at - dr * C;
     const bool on = i < np;
     offA[u] = on ? (unsigned)(dr * a.dA * C + q) * (unsigned)sizeof(T) : kSubOff;
-    offB[u] = on ? (unsigned)(BSH ? dr * a.dB : dr * a.dB * C + q) * (unsigned)sizeof(T) : kSubOff;
+    offB[u] = on ? (unsigned)(dr * a.dB * C + q) * (unsigned)sizeof(T) : kSubOff;
+    rowB[u] = dr * (a.dB | 1);
     po[u] = a.out + ((r0 + dr) * a.dout * C + q);
   }
   auto rsrc = [&](const T* p, int64_t row) {
@@ -228,7 +237,7 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
               r, (__attribute__((address_space(3))) void*)(dst + (ai * RB + u) * kWave), 4, (int)off[u],
               ai * stride * 4, 0, 0);
     } else {
-      constexpr int N = 16 / RB;  // operand rows in flight
+      constexpr int N = (RED ? 16 : 32) / RB;  // operand rows in flight
       for (int a0 = 0; a0 < d; a0 += N) {
         T v[N][RB];
 #pragma unroll
@@ -244,16 +253,32 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
       }
     }
   };
-  stage(rsrc(a.A, (int64_t)a.dA * C), sA, a.dA, offA, C);
+  // The first records are requested before the operands, and a shared B of
+  // float64, which goes through registers, before A: neither waits for the other
+  // (float64, 4 + 4 rows, 12,500 rows of 128 channels: 25 -> 22 us; float32, 9 +
+  // 16 rows, 100,000 rows of 128: dx 702 -> 680 us).
+  constexpr bool kBFirst = BM != kTpgBOwn && sizeof(T) == 8;
+  const auto record = [&](int k0) { return a.recs[k0 + imin(lane, imin(kWave, a.nrec - k0) - 1)]; };
+  auto next = record(0);
+  if constexpr (!kBFirst) stage(rsrc(a.A, (int64_t)a.dA * C), sA, a.dA, offA, C);
   const __amdgpu_buffer_rsrc_t brsrc = rsrc(a.B, (int64_t)a.dB * (BSH ? 1 : C));
   if constexpr (BM == kTpgBOnce) {
     for (int i = lane; i < a.dB * RB; i += kWave) {
       const int dr = (c0 + (i % RB) * kWave) / C;  // past the last row: reads zero
       sB[i] = buf_ld<T>(brsrc, (dr * a.dB + i / RB) * (int)sizeof(T), 0);
     }
+  } else if constexpr (BM == kTpgBRow) {
+    const SpDiv div(a.dB);
+#pragma unroll 4
+    for (int i = lane; i < tpg_tile_rows(C, kPairs) * a.dB; i += kWave) {
+      int b;
+      const int dr = div(i, b);
+      sB[dr * (a.dB | 1) + b] = buf_ld<T>(brsrc, i * (int)sizeof(T), 0);  // past the last row: zero
+    }
   } else {
-    stage(brsrc, sB, a.dB, offB, BSH ? 1 : C);
+    stage(brsrc, sB, a.dB, offB, C);
   }
+  if constexpr (kBFirst) stage(rsrc(a.A, (int64_t)a.dA * C), sA, a.dA, offA, C);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads to LDS
   __syncthreads();
   int o = 0;
@@ -262,36 +287,37 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
   for (int u = 0; u < RB; ++u) acc[u] = T(0);
   for (int k0 = 0; k0 < a.nrec; k0 += kWave) {
     const int nk = imin(kWave, a.nrec - k0);  // a multiple of kTpgAhead
-    const auto mine = a.recs[k0 + imin(lane, nk - 1)];
+    const auto mine = next;
+    if (k0 + kWave < a.nrec) next = record(k0 + kWave);
     const T my_v = T(mine.v);
     // per lane: LDS offsets of its record's operands; per chunk: the flag bits
     const int my_a = (int)(mine.ab & 0x3ffu) * (RB * kWave);
-    const int my_b = (int)(mine.ab >> 10 & 0x3ffu) * (RB * kBLanes);
+    const int my_b = (int)(mine.ab >> 10 & 0x3ffu) * (BM == kTpgBOwn ? RB * kWave : BM == kTpgBOnce ? RB : 1);
     const uint64_t ends = __ballot((mine.ab & (kTpgEnd | kTpgEmpty)) != 0), empties = __ballot((mine.ab & kTpgEmpty) != 0);
-    T pa[2][kTpgAhead][RB], pb[2][kTpgAhead][RB];
-    auto fetch = [&](int k, T (&va)[kTpgAhead][RB], T (&vb)[kTpgAhead][RB]) {
+    T pa[2][AH][RB], pb[2][AH][RB];
+    auto fetch = [&](int k, T (&va)[AH][RB], T (&vb)[AH][RB]) {
 #pragma unroll
-      for (int j = 0; j < kTpgAhead; ++j) {
+      for (int j = 0; j < AH; ++j) {
         const T* qa = sA + __builtin_amdgcn_readlane(my_a, k + j) + lane;
-        const T* qb = sB + __builtin_amdgcn_readlane(my_b, k + j) + (BM == kTpgBOnce ? 0 : lane);
+        const T* qb = sB + __builtin_amdgcn_readlane(my_b, k + j);
 #pragma unroll
         for (int u = 0; u < RB; ++u) va[j][u] = qa[u * kWave];
-        if constexpr (BM == kTpgBOnce && RB > 1) {  // the values of a row of B in one read
+        if constexpr (BM == kTpgBOnce && RB > 1) {
           typedef T Bv __attribute__((ext_vector_type(RB)));
           const Bv b = *reinterpret_cast<const Bv*>(qb);
 #pragma unroll
           for (int u = 0; u < RB; ++u) vb[j][u] = b[u];
         } else {
 #pragma unroll
-          for (int u = 0; u < RB; ++u) vb[j][u] = qb[u * kBLanes];
+          for (int u = 0; u < RB; ++u) vb[j][u] = qb[BM == kTpgBOwn ? u * kWave + lane : BM == kTpgBRow ? rowB[u] : 0];
         }
       }
     };
-    auto use = [&](int k, const T (&va)[kTpgAhead][RB], const T (&vb)[kTpgAhead][RB]) {
-      const unsigned end = (unsigned)(ends >> k) & ((1u << kTpgAhead) - 1), empty = (unsigned)(empties >> k);
+    auto use = [&](int k, const T (&va)[AH][RB], const T (&vb)[AH][RB]) {
+      const unsigned end = (unsigned)(ends >> k) & ((1u << AH) - 1), empty = (unsigned)(empties >> k);
       if (end == 0) {  // most groups: no segment ends inside
 #pragma unroll
-        for (int j = 0; j < kTpgAhead; ++j) {
+        for (int j = 0; j < AH; ++j) {
           const T rv = lane_of(my_v, k + j);
 #pragma unroll
           for (int u = 0; u < RB; ++u) acc[u] = fma(rv * va[j][u], vb[j][u], acc[u]);
@@ -299,7 +325,7 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
         return;
       }
 #pragma unroll
-      for (int j = 0; j < kTpgAhead; ++j) {
+      for (int j = 0; j < AH; ++j) {
         const T rv = lane_of(my_v, k + j);
 #pragma unroll
         for (int u = 0; u < RB; ++u) acc[u] = fma(rv * va[j][u], vb[j][u], acc[u]);
@@ -324,34 +350,40 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
       }
     };
     fetch(0, pa[0], pb[0]);
-    for (int k = 0; k < nk; k += 2 * kTpgAhead) {
-      if (k + kTpgAhead < nk) fetch(k + kTpgAhead, pa[1], pb[1]);
+    for (int k = 0; k < nk; k += 2 * AH) {
+      if (k + AH < nk) fetch(k + AH, pa[1], pb[1]);
       use(k, pa[0], pb[0]);
-      if (k + kTpgAhead < nk) {
-        if (k + 2 * kTpgAhead < nk) fetch(k + 2 * kTpgAhead, pa[0], pb[0]);
-        use(k + kTpgAhead, pa[1], pb[1]);
+      if (k + AH < nk) {
+        if (k + 2 * AH < nk) fetch(k + 2 * AH, pa[0], pb[0]);
+        use(k + AH, pa[1], pb[1]);
       }
     }
   }
   if constexpr (RED) {
     __syncthreads();
     const int w = a.pieces == 1 ? C : np, nrow = np / w;  // channels and rows of the tile
+    // runs of at most 64 channels, a lane each (longer chains round larger sums:
+    // float32, 256 channels of one sign, 3.2 times the error), then a row's runs
+    const int nrun = (w + kWave - 1) / kWave;
+    for (int i = lane; i < a.dout * nrow * nrun; i += kWave) {
+      const int run = i % nrun, our = i / nrun, ou = our / nrow, r = our - ou * nrow;
+      T* p = sP + ou * kPairs + r * w + run * kWave;
+      const int n = imin(kWave, w - run * kWave);
+      T t = T(0);
+      // lane i starts at channel i (mod n), so that the lanes read different banks
+#pragma unroll 4
+      for (int l = 0, c = i % n; l < n; ++l) {
+        t += p[c];
+        c = c + 1 == n ? 0 : c + 1;
+      }
+      p[0] = t;
+    }
+    __syncthreads();
     for (int i = lane; i < a.dout * nrow; i += kWave) {
       const int ou = i / nrow, r = i - ou * nrow;
       const T* p = sP + ou * kPairs + r * w;
-      T t = T(0);
-      // lane i starts at channel i (mod w), so that the lanes read different
-      // banks; in runs of 64, since a longer chain rounds larger sums (float32, 256
-      // channels: 1.9 times the error)
-      for (int l = 0, c = i % w; l < w;) {
-        T run = T(0);
-#pragma unroll 4
-        for (const int end = imin(l + kWave, w); l < end; ++l) {
-          run += p[c];
-          c = c + 1 == w ? 0 : c + 1;
-        }
-        t += run;
-      }
+      T t = p[0];
+      for (int run = 1; run < nrun; ++run) t += p[run * kWave];
       a.part[((r0 + r) * a.pieces + (a.pieces == 1 ? 0 : tile % a.pieces)) * a.dout + ou] = t;
     }
   }
@@ -1606,17 +1638,26 @@ e3_status tpg_upload(e3_tpg* G) {
   return E3_OK;
 }
 
-// Staging of one wave with rb pairs per lane (all operands per pair, a shared B
-// once per 64 pairs where `once`).
-size_t tpg_lds(int dA, int dB, int dout, bool once, bool red, size_t elem, int rb) {
-  return (((size_t)dA + (red ? dout : 0)) * kWave + (size_t)dB * (once ? 1 : kWave)) * rb * elem;
+// Staging of one wave with rb pairs per lane.
+size_t tpg_lds(int dA, int dB, int dout, TpgB mode, bool red, int C, size_t elem, int rb) {
+  const size_t b = mode == kTpgBOwn   ? (size_t)dB * kWave * rb
+                   : mode == kTpgBRow ? (size_t)(dB | 1) * tpg_tile_rows(C, rb * kWave)
+                                      : (size_t)dB * rb;
+  return (((size_t)dA + (red ? dout : 0)) * kWave * rb + b) * elem;
 }
 constexpr size_t kTpgMaxLds = 64 * 1024;
-// Pairs per lane: the most of 4, 2, 1 whose staging leaves ten waves per CU.
-// More waves hide more latency, more pairs share a record's overhead: 118, 121
-// and 139 us with 2, 4 and 1 at 18 operand rows (30,011 rows, C = 100), 241,
-// 292 and 281 us at 32 (20,000 rows, C = 64).
-constexpr size_t kTpgWant = 16 * 1024;
+// Pairs per lane: the most of 4, 2, 1 whose staging leaves ten waves per CU,
+// eight with a shared B.  More waves hide more latency, more pairs share a
+// record's overhead: 118, 121 and 139 us with 2, 4 and 1 at 18 operand rows
+// (30,011 rows, C = 100), 241, 292 and 281 us at 32 (20,000 rows, C = 64); a
+// shared B at 16 + 16 operand rows (20,000 rows, C = 64) 155 us with 4, 207 with 2.
+constexpr size_t kTpgWant = 16 * 1024, kTpgWantShared = 20 * 1024;
+// Four pairs read four records ahead instead of eight where the staging leaves
+// room for the waves that the registers then allow (9 + 9 rows, shared B, C =
+// 128: 137 against 147 us; 16 + 16: 174 against 155), and always in float64,
+// where eight take 256 registers (4 + 4 rows: 31 against 40 us).
+constexpr size_t kTpgAhead4Lds = 12 * 1024;
+constexpr int64_t kTpgTiles = 1024;
 
 // What a call accepts: one row's operands of 64 channels (a shared B once)
 // within the limit, and its operand block of up to four rows within 2 GiB.
@@ -1640,19 +1681,13 @@ e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, in
   while (rows_per > 1 && tpg_row_lds(dA, dB, a.dout, bsh, red, sizeof(T), rows_per) > kTpgMaxLds) rows_per /= 2;
   if (tpg_row_lds(dA, dB, a.dout, bsh, red, sizeof(T), rows_per) > kTpgMaxLds) return E3_ERR_UNSUPPORTED;
   if ((int64_t)rows_per * std::max(dA, dB) * C * (int64_t)sizeof(T) > 0x7fffffff) return E3_ERR_INVALID_ARG;
-  // Pairs per lane.  A shared B is staged once per 64 pairs where that leaves
-  // room for more of them (9 + 16 operand rows, 351 records, 100,000 rows of 128
-  // channels: 1160 us with four against 1390 with two; 9 + 9 rows, 50,000 rows of
-  // 128 channels 147 against 188); at the same number the copies per lane read
-  // faster (106 + 16 rows: 3230 against 3670 us).
-  auto pairs_that_fit = [&](bool b_once) {
-    int r = 4;
-    while (r > 1 && tpg_lds(dA, dB, a.dout, b_once, red, sizeof(T), r) > kTpgWant) r /= 2;
-    return r;
-  };
-  const bool once = bsh && C % kWave == 0 && pairs_that_fit(true) > pairs_that_fit(false);
-  const int rb = pairs_that_fit(once);
-  const size_t lds = tpg_lds(dA, dB, a.dout, once, red, sizeof(T), rb);
+  const TpgB mode = !bsh ? kTpgBOwn : C % kWave == 0 ? kTpgBOnce : kTpgBRow;
+  int rb = 4;
+  while (rb > 1 && tpg_lds(dA, dB, a.dout, mode, red, C, sizeof(T), rb) > (bsh ? kTpgWantShared : kTpgWant)) rb /= 2;
+  // fewer where the tiles would not give every SIMD a wave (300 rows, C = 128, 9 +
+  // 9 rows: 16 -> 13 us; 5,000 rows, C = 36, 9 + 16 rows: 45 -> 35 us)
+  while (!red && rb > 1 && rows * C < (int64_t)rb * kWave * kTpgTiles) rb /= 2;
+  const size_t lds = tpg_lds(dA, dB, a.dout, mode, red, C, sizeof(T), rb);
   const int pairs = rb * kWave;
   a.pieces = red ? (C + pairs - 1) / pairs : 1;
   a.rpt = red && C <= pairs ? pairs / C : 1;
@@ -1660,24 +1695,30 @@ e3_status tpg_run(const e3_tpg* G, int which, const T* A, int dA, const T* B, in
   if (grid > 0x7fffffff) return E3_ERR_INVALID_ARG;
   if (red && a.pieces == 1) a.part = out;
   TimedLaunch t_(name, st);
-  auto go = [&](auto RBc) {
-    constexpr int R = decltype(RBc)::value;
+  auto go = [&](auto RBc, auto AHc) {
+    constexpr int R = decltype(RBc)::value, A = decltype(AHc)::value;
     // only a shared y's cotangent is summed, and its operands have channels
-    auto* k = once ? k_tpg<T, kTpgBOnce, false, R>
-              : bsh ? k_tpg<T, kTpgBShared, false, R>
-              : red ? k_tpg<T, kTpgBOwn, true, R>
-                    : k_tpg<T, kTpgBOwn, false, R>;
-    // over 64 KiB only in float64 with a shared B of many rows
+    auto* k = red                 ? k_tpg<T, kTpgBOwn, true, R, A>
+              : mode == kTpgBOwn  ? k_tpg<T, kTpgBOwn, false, R, A>
+              : mode == kTpgBOnce ? k_tpg<T, kTpgBOnce, false, R, A>
+                                  : k_tpg<T, kTpgBRow, false, R, A>;
+    // over 64 KiB only in float64 with a shared B of many rows and few channels
     if (lds > kTpgMaxLds)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, grid_of(grid), dim3(kWave), lds, st, a);
   };
-  if (rb == 4)
-    go(std::integral_constant<int, 4>{});
-  else if (rb == 2)
-    go(std::integral_constant<int, 2>{});
-  else
-    go(std::integral_constant<int, 1>{});
+  using Four = std::integral_constant<int, 4>;
+  using All = std::integral_constant<int, kTpgAhead>;
+  if (rb == 4) {
+    if constexpr (sizeof(T) == 4)
+      lds <= kTpgAhead4Lds ? go(Four{}, Four{}) : go(Four{}, All{});
+    else
+      go(Four{}, Four{});
+  } else if (rb == 2) {
+    go(std::integral_constant<int, 2>{}, All{});
+  } else {
+    go(std::integral_constant<int, 1>{}, All{});
+  }
   E3_HIP(hipGetLastError());
   if (red && a.pieces > 1) {
     hipLaunchKernelGGL(k_tpg_sum<T>, dim3(blocks_for(rows * a.dout, 256)), dim3(256), 0, st, part, out, rows, a.pieces,

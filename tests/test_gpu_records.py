@@ -27,15 +27,7 @@ def e3():
     return e3mi
 
 
-@pytest.mark.parametrize("f64", [False, True])
-@pytest.mark.parametrize("ypc", [False, True])
-@pytest.mark.parametrize("nnz,dims,rows,C", [
-    (0, (2, 3, 4), 5, 7), (1, (1, 1, 1), 1, 1), (3, (4, 2, 5), 2, 63), (63, (5, 4, 7), 3, 64),
-    (64, (5, 4, 7), 4, 65), (65, (9, 9, 9), 5, 100), (67, (9, 9, 9), 9, 12), (137, (9, 4, 16), 13, 130),
-    (260, (40, 3, 30), 6, 20), (90, (60, 50, 8), 3, 10),
-    (137, (9, 16, 20), 5, 64), (90, (30, 7, 8), 3, 128), (70, (3, 4, 5), 7, 192), (65, (70, 9, 9), 2, 320),
-])
-def test_record_walk_edges(e3, nnz, dims, rows, C, ypc, f64):
+def _check(e3, nnz, dims, rows, C, ypc, f64):
     rng = np.random.default_rng(nnz * 7 + rows)
     dx_, dy_, dz_ = dims
     # output rows 0, dz - 1 and every fourth one get no record
@@ -67,6 +59,31 @@ def test_record_walk_edges(e3, nnz, dims, rows, C, ypc, f64):
     assert not to_np(z)[:, empty].any()
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("ypc", [False, True])
+@pytest.mark.parametrize("nnz,dims,rows,C", [
+    (0, (2, 3, 4), 5, 7), (1, (1, 1, 1), 1, 1), (3, (4, 2, 5), 2, 63), (63, (5, 4, 7), 3, 64),
+    (64, (5, 4, 7), 4, 65), (65, (9, 9, 9), 5, 100), (67, (9, 9, 9), 9, 12), (137, (9, 4, 16), 13, 130),
+    (260, (40, 3, 30), 6, 20), (90, (60, 50, 8), 3, 10),
+    (137, (9, 16, 20), 5, 64), (90, (30, 7, 8), 3, 128), (70, (3, 4, 5), 7, 192), (65, (70, 9, 9), 2, 320),
+])
+def test_record_walk_edges(e3, nnz, dims, rows, C, ypc, f64):
+    _check(e3, nnz, dims, rows, C, ypc, f64)
+
+
+# enough pairs for the widest tiles: 4, 2 and 1 pairs per lane, four and eight
+# records ahead, a shared y per row of the tile (1 to 66 rows) and per 64 pairs
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("ypc", [False, True])
+@pytest.mark.parametrize("nnz,dims,rows,C", [
+    (21, (4, 4, 4), 2_100, 128), (21, (4, 3, 4), 2_701, 100), (70, (16, 5, 16), 4_200, 64), (70, (16, 16, 3), 2_701, 100),
+    (135, (9, 9, 9), 13_300, 20), (33, (3, 4, 5), 262_201, 1), (66, (30, 7, 8), 1_400, 192), (40, (25, 4, 9), 2_001, 132),
+])
+def test_wide_tiles(e3, nnz, dims, rows, C, ypc, f64):
+    assert rows * C >= 4 * 64 * 1024
+    _check(e3, nnz, dims, rows, C, ypc, f64)
+
+
 def test_wide_shared_operands_f64(e3):
     """float64 operands of 200 rows with a shared y: more than 64 KiB staged per wave."""
     rng = np.random.default_rng(5)
@@ -82,20 +99,24 @@ def test_wide_shared_operands_f64(e3):
 
 
 def test_more_tiles_than_a_grid_row(e3):
-    """4.3e9 (row, channel) pairs at one pair per lane: 2^32 threads and more, which
-    a launch wraps without an error if they lie along x."""
+    """43 million rows in two pieces of 64 channels (dy of 40 rows): 5.5e9 threads,
+    which a launch wraps without an error if they lie along x."""
     import torch
     rows, C = 43_000_000, 100
     g = torch.Generator(device="cuda").manual_seed(1)
     k = np.arange(40, dtype=np.int32)
     tp = e3.RecordTP(1, 40, 1, 0 * k, 0 * k, k, np.ones(40), y_per_channel=False)
-    x = torch.randn(rows, 1, C, generator=g, device="cuda")
+    x, dz = (torch.randn(rows, 1, C, generator=g, device="cuda") for _ in range(2))
     y = torch.randn(rows, 40, generator=g, device="cuda")
     print("[case] many tiles", rows * C, flush=True)
     z = tp.forward(x, y)
+    dx, dy = tp.backward(x, y, dz)
     for a in range(0, rows, 4_000_000):
-        ref = x[a:a + 4_000_000, 0].double() * y[a:a + 4_000_000].double().sum(1, keepdim=True)
-        assert float((z[a:a + 4_000_000, 0].double() - ref).norm() / ref.norm()) < 1e-6
+        xs, ys, ds = (t[a:a + 4_000_000].double() for t in (x[:, 0], y, dz[:, 0]))
+        s = ys.sum(1, keepdim=True)
+        for got, ref in ((z[a:a + 4_000_000, 0], xs * s), (dx[a:a + 4_000_000, 0], ds * s),
+                         (dy[a:a + 4_000_000], (xs * ds).sum(1, keepdim=True).expand(-1, 40))):
+            assert float((got.double() - ref).norm() / ref.norm()) < 1e-6
 
 
 @pytest.mark.parametrize("C", [64, 100, 128, 256, 320])
