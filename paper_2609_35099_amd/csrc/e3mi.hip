@@ -82,7 +82,7 @@ struct LinDwArgs {
   float* dWp;  // [npairs][kLinChunks][C_in][C_out]
   const LinPair* pairs;
   int64_t n;
-  int D_in, C_in, D_out, C_out, ktiles, jtiles;
+  int D_in, C_in, D_out, C_out, ktiles, jtiles, npairs;
 };
 
 // dW[w_off(p) + e] = sum over the row chunks of pair p, in chunk order.
@@ -1549,13 +1549,13 @@ e3_status e3_linear_bwd(e3_linear* L, const float* x, const float* W, const floa
   a.x = x, a.dout = dout, a.dWp = dWp, a.pairs = dp, a.n = n;
   a.D_in = L->d_in, a.C_in = L->c_in, a.D_out = L->d_out, a.C_out = L->c_out;
   const int km = lin_tile(L->c_in), jm = lin_tile(L->c_out);
-  a.ktiles = (L->c_in + km - 1) / km, a.jtiles = (L->c_out + jm - 1) / jm;
+  a.ktiles = (L->c_in + km - 1) / km, a.jtiles = (L->c_out + jm - 1) / jm, a.npairs = (int)L->pairs.size();
   {
     auto* k = km == 128 ? (jm == 128 ? k_lin_dw<128, 128> : k_lin_dw<128, 64>)
                         : (jm == 128 ? k_lin_dw<64, 128> : k_lin_dw<64, 64>);
     TimedLaunch t_("linear_bwd_dw", st);
     const int64_t units = (int64_t)L->pairs.size() * kLinChunks * a.ktiles * a.jtiles;
-    hipLaunchKernelGGL(k, dim3((unsigned)units), dim3(kSpThreads), 0, st, a);
+    hipLaunchKernelGGL(k, grid_of(units), dim3(kSpThreads), 0, st, a);
     E3_HIP(hipGetLastError());
   }
   {

@@ -385,7 +385,9 @@ __global__ __launch_bounds__(kSpThreads, 3) void k_lin_dw(LinDwArgs a) {
   __shared__ __align__(16) SpTile<RM> sX;
   __shared__ __align__(16) SpTile<BN> sD;
   const int per = kLinChunks * a.ktiles * a.jtiles;
-  const int p = blockIdx.x / per, u = blockIdx.x % per;
+  const int64_t block = block_id();
+  const int p = (int)(block / per), u = (int)(block % per);
+  if (p >= a.npairs) return;
   const int chunk = u / (a.ktiles * a.jtiles), kc0 = (u / a.jtiles) % a.ktiles * RM, jc0 = u % a.jtiles * BN;
   const LinPair pr = a.pairs[p];
   const int R = pr.R, tid = threadIdx.x;

@@ -187,6 +187,33 @@ def test_linear_dw_long_chunks(e3):
     assert rel_l2(got[0], to_np(ref[0])) < 2e-5 and rel_l2(got[1], to_np(ref[1])) < 1e-6
 
 
+def test_linear_dw_more_tiles_than_a_grid_row(e3):
+    """57 x 57 pairs of 528 channels, 81 tiles of 64 in each of 64 chunks: 4.3e9
+    threads, which a launch wraps without an error if they lie along x (the
+    partials take 232 GB)."""
+    import gc
+    import torch
+    gc.collect()
+    torch.cuda.empty_cache()
+    B, C, n = 57, 528, 3
+    irreps = "+".join([f"{C}x0e"] * B)
+    L = e3.Linear(irreps, irreps)
+    assert B * B * 64 * 81 * 256 > 2**32
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x, d = (torch.randn(n, B, C, generator=g, device="cuda") for _ in range(2))
+    W = torch.zeros(L.n_weights, device="cuda")
+    print("[case] dW tiles", L.n_weights, flush=True)
+    _, dW = L.backward(x, W, d)
+    del W
+    dW = dW.reshape(B, B * C, C)
+    xt = x.double().reshape(n, B * C).T.contiguous()
+    for o in range(B):
+        ref = xt @ d[:, o].double()
+        assert float((dW[o].double() - ref).norm() / ref.norm()) < 1e-6
+    del dW, ref, xt
+    torch.cuda.empty_cache()
+
+
 def test_linear_elements_depend_on_their_own_operands(e3):
     """Infinities, NaNs and operands that the terms cannot hold change no bit of
     any other row (forward, dx) or channel pair (dW)."""
