@@ -84,6 +84,36 @@ def test_wide_tiles(e3, nnz, dims, rows, C, ypc, f64):
     _check(e3, nnz, dims, rows, C, ypc, f64)
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("ypc,C", [(True, 100), (False, 100), (False, 64)])
+def test_infinities_and_nans(e3, ypc, C, f64):
+    """Infinities and NaNs where the sum record by record has them, in the first
+    operand rows too, which output rows without records and the table's padding
+    name; every other element as without them."""
+    rng = np.random.default_rng(C)
+    nnz, dx_, dy_, dz_, rows = 67, 5, 4, 9, 50
+    i0 = rng.choice([1, 2, 3, 5, 6, 7], nnz).astype(np.int32)
+    i1, i2 = rng.integers(0, dx_, nnz).astype(np.int32), rng.integers(0, dy_, nnz).astype(np.int32)
+    val, dt = rng.standard_normal(nnz), np.float64 if f64 else np.float32
+    x = rng.standard_normal((rows, dx_, C)).astype(dt)
+    y = rng.standard_normal((rows, dy_, C) if ypc else (rows, dy_)).astype(dt)
+    tp = e3.RecordTP(dx_, dy_, dz_, i0, i1, i2, val, y_per_channel=ypc)
+    print("[case] infinities", ypc, C, f64, flush=True)
+    clean = to_np(tp.forward(to_dev(x), to_dev(y)))
+    x[3, 0, 7], x[20, 2, 99 % C], x[20, 0, 1] = np.inf, np.nan, -np.inf
+    y[(31, 0, 5) if ypc else (31, 0)] = np.inf
+    z = to_np(tp.forward(to_dev(x), to_dev(y)))
+    ref, yc = np.zeros((rows, dz_, C)), y if ypc else np.repeat(y[..., None], C, 2)
+    with np.errstate(all="ignore"):
+        for a, b, c, w in zip(i0, i1, i2, val):
+            ref[:, a] += w * x[:, b].astype(np.float64) * yc[:, c]
+    assert np.array_equal(np.isnan(z), np.isnan(ref)) and np.isnan(ref).any()
+    inf = np.isinf(ref)
+    assert np.array_equal(np.isinf(z), inf) and np.array_equal(np.sign(z[inf]), np.sign(ref[inf])) and inf.any()
+    ok = np.isfinite(ref)
+    assert np.array_equal(z[ok], clean[ok])
+
+
 def test_wide_shared_operands_f64(e3):
     """float64 operands of 200 rows with a shared y: more than 64 KiB staged per wave."""
     rng = np.random.default_rng(5)

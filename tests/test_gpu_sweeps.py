@@ -151,6 +151,88 @@ def test_ragged_slabs(e3, C, composed, n, deg):
         assert rel_l2(to_np(a), b.numpy()) < TOL
 
 
+# the same widths adding to what is there, and with cotangents left out
+@pytest.mark.parametrize("C,composed", [(20, False), (96, False), (96, True), (132, False), (132, True), (160, False),
+                                        (192, False), (200, True)])
+def test_ragged_slabs_accumulate(e3, C, composed):
+    import torch
+    rng = np.random.default_rng(C)
+    irreps, n, E = f"{C}x0e+{C}x1o", 3000, 9000
+    lay = oirreps.layout(irreps, 2, 2)
+    plan = e3.Plan(irreps, 2, 2, composed=composed)
+    snd, rcv = (rng.integers(0, n, E).astype(np.int32) for _ in range(2))
+    x, y, s, dm = (rng.standard_normal(sh).astype(np.float32) for sh in
+                   ((n, lay.d_in, C), (E, lay.d_sh), (E, lay.n_paths, C), (n, lay.d_out, C)))
+    print("[case] ragged accumulate", C, plan.kernels, flush=True)
+    G = e3.Graph(to_dev(snd), to_dev(rcv), n)
+    xs, ys, ss, dms = (to_dev(a) for a in (x, y, s, dm))
+    m = e3.conv_fwd_y(plan, G, xs, ys, ss)
+    d = e3.conv_bwd_y(plan, G, xs, ys, ss, dms)
+    ref = oconv.conv_bwd_from_y(lay, x, y, s, dm, snd, rcv, n)
+    refs = (oconv.conv_fwd_from_y(lay, x, y, s, snd, rcv, n), ref["dx"], ref["dy"], ref["ds"])
+    for a, b in zip((m, *d), refs):
+        assert rel_l2(to_np(a), b.numpy()) < TOL
+    base = [torch.randn_like(t) for t in (m, *d)]
+    acc = [b.clone() for b in base]
+    e3.conv_fwd_y(plan, G, xs, ys, ss, out=acc[0], accumulate=True)
+    e3.conv_bwd_y(plan, G, xs, ys, ss, dms, dx=acc[1], dy=acc[2], ds=acc[3], accumulate=True)
+    # the last product of a ds element may enter the sum unrounded: three roundings apart at most
+    for got, b, t in zip(acc, base, (m, *d)):
+        assert bool(((got.double() - (b + t).double()).abs() <= 3 * 2.0**-24 * (b.abs() + t.abs()).double()).all())
+    for want in (("dx",), ("dy",), ("ds",)):
+        got = e3.conv_bwd_y(plan, G, xs, ys, ss, dms, want=want)
+        for name, full, part in zip(("dx", "dy", "ds"), d, got):
+            assert torch.equal(full, part) if name in want else part is None
+
+
+# one NaN row of x and one infinite row of s: sub-waves (with steps of fewer
+# edges than the wave takes), whole waves, split slabs, short and long segment sums
+@pytest.mark.parametrize("blocks,C,f64,n", [
+    ("0e+1o", 8, False, 0), ("0e+1o", 12, False, 0), ("0e+1o", 32, False, 0), ("0e+1o", 20, True, 0),
+    ("0e+1o", 36, True, 0), ("0e+1o", 64, False, 0), ("0e+1o", 160, False, 3000), ("0e+1o+2e+3o", 128, False, 0),
+])
+def test_infinities_and_nans_stay_where_they_are(e3, blocks, C, f64, n):
+    """What does not depend on them keeps every bit: other receivers, senders,
+    edges and channels."""
+    rng = np.random.default_rng(C)
+    dt = np.float64 if f64 else np.float32
+    irreps = "+".join(f"{C}x{b}" for b in blocks.split("+"))
+    l = 2 if blocks == "0e+1o" else 3
+    lay, plan = oirreps.layout(irreps, l, l), e3.Plan(irreps, l, l)
+    if n:
+        snd, rcv = (rng.integers(0, n, 3 * n).astype(np.int32) for _ in range(2))
+        vec = rng.standard_normal((3 * n, 3))
+    else:
+        snd, rcv, vec, n = _graph(rng, -1)
+    E = rcv.shape[0]
+    x, s, dm = (rng.standard_normal(sh).astype(dt) for sh in
+                ((n, lay.d_in, C), (E, lay.n_paths, C), (n, lay.d_out, C)))
+    G = e3.Graph(to_dev(snd), to_dev(rcv), n)
+    fwd, bwd = (e3.conv_fwd_f64, e3.conv_bwd_f64) if f64 else (e3.conv_fwd, e3.conv_bwd)
+    print("[case] infinities", irreps, f64, n, flush=True)
+
+    def run():
+        a = [to_dev(v) for v in (x, vec.astype(dt), s)]
+        return [to_np(t) for t in (fwd(plan, G, *a), *bwd(plan, G, *a, to_dev(dm)))]
+
+    clean = run()
+    node, cx, edge, cs = int(snd[1]), 3, int(np.flatnonzero(snd != snd[1])[-1]), C - 1
+    x[node, :, cx], s[edge, :, cs] = np.nan, np.inf
+    got = run()
+    out = snd == node
+    keep = [np.ones(a.shape, bool) for a in clean]
+    keep[0][np.unique(rcv[out]), :, cx] = False
+    keep[0][rcv[edge], :, cs] = False
+    keep[1][snd[edge], :, cs] = False
+    keep[2][out], keep[2][edge] = False, False
+    keep[3][out, :, cx] = False
+    for g, c, k in zip(got, clean, keep):
+        assert np.array_equal(g[k], c[k])
+    assert np.isnan(got[0][rcv[out]][:, :, cx]).all() and np.isnan(got[3][out][:, :, cx]).all()
+    assert np.isnan(got[2][out]).any(1).all()
+    assert not np.isfinite(got[0][rcv[edge], :, cs]).all() and not np.isfinite(got[1][snd[edge], :, cs]).any()
+
+
 # rows of whole 64-byte pieces and of others, on one slab and on two
 @pytest.mark.parametrize("C", [4, 16, 20, 36, 64, 68, 100, 128, 132])
 def test_tensor_product_row_pieces(e3, C):
