@@ -238,7 +238,8 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
               ai * stride * 4, 0, 0);
     } else {
       constexpr int N = (RED ? 16 : 32) / RB;  // operand rows in flight
-      for (int a0 = 0; a0 < d; a0 += N) {
+      auto rows = [&](auto n, int a0) {
+        constexpr int N = decltype(n)::value;
         T v[N][RB];
 #pragma unroll
         for (int k = 0; k < N; ++k)
@@ -250,7 +251,18 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
           if (a0 + k < d)
 #pragma unroll
             for (int u = 0; u < RB; ++u) dst[((a0 + k) * RB + u) * kWave + lane] = v[k][u];
-      }
+      };
+      // a remainder takes no more requests than the next power of two (one operand
+      // row, 22,137 rows of 128 channels: 17.7 -> 14.1 us)
+      int a0 = 0;
+      for (; d - a0 > N / 2; a0 += N) rows(std::integral_constant<int, N>{}, a0);
+      const int left = d - a0;
+      if (left > N / 4)
+        rows(std::integral_constant<int, N / 2>{}, a0);
+      else if (left > N / 8)
+        rows(std::integral_constant<int, N / 4>{}, a0);
+      else if (left > 0)
+        rows(std::integral_constant<int, (N < 8 ? 1 : N / 8)>{}, a0);
     }
   };
   // The first records are requested before the operands, and a shared B of
@@ -370,11 +382,24 @@ __global__ __launch_bounds__(kWave) void k_tpg(TpgArgs<T> a) {
       T* p = sP + ou * kPairs + r * w + run * kWave;
       const int n = imin(kWave, w - run * kWave);
       T t = T(0);
-      // lane i starts at channel i (mod n), so that the lanes read different banks
+      // lane i starts at another channel, so that the lanes read different banks
+      constexpr int W = 16 / sizeof(T);
+      if (n == kWave && w % W == 0) {
+        // reads of 16 bytes whose addresses do not wait for one another (22,137 rows
+        // of 128 channels, 4 + 4 operand rows, 9 records: backward 46 -> 41 us)
+        typedef T Tv __attribute__((ext_vector_type(W)));
+#pragma unroll
+        for (int l = 0; l < kWave / W; ++l) {
+          const Tv v = reinterpret_cast<const Tv*>(p)[(l + i) % (kWave / W)];
+#pragma unroll
+          for (int k = 0; k < W; ++k) t += v[k];
+        }
+      } else {
 #pragma unroll 4
-      for (int l = 0, c = i % n; l < n; ++l) {
-        t += p[c];
-        c = c + 1 == n ? 0 : c + 1;
+        for (int l = 0, c = i % n; l < n; ++l) {
+          t += p[c];
+          c = c + 1 == n ? 0 : c + 1;
+        }
       }
       p[0] = t;
     }
