@@ -1559,8 +1559,14 @@ __device__ __forceinline__ void tpb64_task(const Tpb64Args& a, int64_t r0, int s
 #pragma unroll
       for (int i = 0; i < B::NXR; ++i) bst64(dxb, B::XROW[i], t[i]);
     }
-    const double tot = wave_reduce16(dy, lane);
-    if ((lane & 3) == 0) a.DY[(dy_group<V, G>(a, r) * a.nslab + sl) * 16 + (lane >> 2)] = tot;
+    // The branch is always taken.  With 75 rows to load (0e+1o+2e, l <= 2) the
+    // compiler otherwise schedules the reduction with the next row's loads and waits
+    // for those one by one (C = 64, 20,000 rows: 261 against 234 us); with 72 and
+    // fewer it does not, and the branch costs up to 24%.
+    if (B::NXR + B::NPATH + B::NROW <= 72 || a.nslab > 0) {
+      const double tot = wave_reduce16(dy, lane);
+      if ((lane & 3) == 0) a.DY[(dy_group<V, G>(a, r) * a.nslab + sl) * 16 + (lane >> 2)] = tot;
+    }
   }
 }
 
