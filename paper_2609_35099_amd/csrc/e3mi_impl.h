@@ -1615,8 +1615,20 @@ __global__ __launch_bounds__(256) void k_dy_sum64(const double* __restrict__ DY,
 // per lane.  Rows are addressed with a 32-bit lane offset from the tensor's
 // start, so sub-waves need every tensor below kSubMaxBytes; a float64 tensor
 // beyond it runs with whole waves (wide: a descriptor per edge).
+//
+// Bound on a CU's waves by the staged pre-contractions where they are many: in
+// batches of 16 edges instead of 32 the forward takes 70 against 110 us (l <= 3,
+// C = 4, 7,000 nodes of 10 edges) and 138 against 217 in float64 (C = 8, 3,000 of
+// 20); batches of 32 where few waves are there or little is staged (64 nodes, C =
+// 16: 11.8 against 13.3; 0e+1o, l <= 2, C = 8, 7,000 of 20: 22.1 against 23.7).
 constexpr unsigned kSubMaxBytes = 0xf0000000u;  // below kSubOff
 constexpr unsigned kSubOff = 0xfffffff0u;       // lane offset past every descriptor: reads zero, stores dropped
+// float64: s, ds, T and m are accessed without the non-temporal bit where rows are
+// not whole 64-byte pieces (C = 100, 1,220 nodes: forward 68 -> 55 us; C = 20, 3,000:
+// backward 94 -> 77) or one piece, and where all that the sweep streams stays in
+// the 256 MiB Infinity Cache (C = 128, 5,000 edges: 27 -> 24 and 63 -> 53); past it
+// the bit is the faster one (C = 128, 13,700 edges of l <= 3: 110 against 114).
+constexpr int64_t kSubCache = 192 << 20;
 
 template <class T>
 struct SubArgs {
@@ -1629,6 +1641,8 @@ struct SubArgs {
   int wide;   // -1: one edge per wave, descriptors based at the edge's rows; else 0
   int fb;     // edges per staged batch, a multiple of the edges per step
   int accum;  // forward: add to m instead of overwriting it
+  int cached; // see kSubCache
+  int single; // forward: one row buffer (see sub_single)
   unsigned xn, sn, dsn, tn;  // descriptor sizes of x, s, ds, P (0: that output is not wanted, its stores are dropped)
   int xr, pr, orr, ng, g0;   // as in ConvArgs
 };
@@ -1741,7 +1755,22 @@ __device__ __forceinline__ bool sub_task_of(const SubArgs<T>& a, int& b, int& g,
   return rl < a.chunk && b < a.n_nodes;
 }
 
-template <class V, int G, class T>
+// One row buffer instead of two where the second would leave one wave per SIMD:
+// float64 groups of more than 96 values of accumulators and buffers (the
+// natural-parity 0e+1o+2e+3o, l <= 3, 1,848 nodes of 9 edges, C = 36: 91 -> 77 us;
+// elsewhere two are up to 10% faster), in launches of more than one wave per SIMD
+// (0e+1o+2e, l <= 2, 124 nodes, C = 128: 33 with one buffer, 30 with two).
+template <class V, class T, int G = 0>
+constexpr bool sub_single() {
+  if constexpr (sizeof(T) == 4 || G == V::NFG) {
+    return false;
+  } else {
+    using F = typename V::template FG<G>;
+    return F::NROW + 2 * (F::NXR + F::NPATH) > 96 || sub_single<V, T, G + 1>();
+  }
+}
+
+template <class V, int G, class T, bool CACHED, bool SINGLE>
 __device__ __forceinline__ void sub_fwd_task(const SubArgs<T>& a, int b, int sl, T* sA) {
   using F = typename V::template FG<G>;
   const int lane = threadIdx.x, lgl = a.lgl, S = kWave >> lgl, sub = lane >> lgl;
@@ -1775,8 +1804,16 @@ __device__ __forceinline__ void sub_fwd_task(const SubArgs<T>& a, int b, int sl,
 #pragma unroll
       for (int i = 0; i < F::NXR; ++i) sld(xr, F::XROW[i], xv[i]);
 #pragma unroll
-      for (int i = 0; i < F::NPATH; ++i) sld<kNT>(sr, F::PATH[i], sv[i]);
+      for (int i = 0; i < F::NPATH; ++i) sld<CACHED ? 0 : kNT>(sr, F::PATH[i], sv[i]);
     };
+    if constexpr (SINGLE) {
+      for (int j = 0; j < nr; j += S) {
+        load(j, xa, sa);
+        F::template edge<1>(sA + (j + sub) * F::NA, xa, sa, acc);
+      }
+      __syncthreads();
+      continue;
+    }
     load(0, xa, sa);
     for (int j = 0; j < nr; j += 2 * S) {
       if (j + S < nr) load(j + S, xb, sb);
@@ -1823,34 +1860,34 @@ __device__ __forceinline__ void sub_fwd_task(const SubArgs<T>& a, int b, int sl,
     }
   }
 #pragma unroll
-  for (int i = 0; i < F::NROW; ++i) sst<kST>(mb, F::OROW[i], acc[i]);
+  for (int i = 0; i < F::NROW; ++i) sst<CACHED ? 0 : kST>(mb, F::OROW[i], acc[i]);
 }
 
-template <class V, int G, class T>
+template <class V, int G, class T, bool CACHED, bool SINGLE>
 __device__ __forceinline__ void sub_fwd_dispatch(const SubArgs<T>& a, int b, int g, int sl, T* sA) {
   if constexpr (G < V::NFG) {
     if (g == G)
-      sub_fwd_task<V, G, T>(a, b, sl, sA);
+      sub_fwd_task<V, G, T, CACHED, SINGLE>(a, b, sl, sA);
     else
-      sub_fwd_dispatch<V, G + 1, T>(a, b, g, sl, sA);
+      sub_fwd_dispatch<V, G + 1, T, CACHED, SINGLE>(a, b, g, sl, sA);
   }
 }
 
 constexpr int sub_min_waves(size_t elem) { return elem == 4 ? 2 : 1; }
 
 // dynamic LDS: fb * V::MAX_NA_F values
-template <class V, class T>
-__global__ __launch_bounds__(kWave, sub_min_waves(sizeof(T))) void k_conv_fwd_sub(SubArgs<T> a) {
+template <class V, class T, bool CACHED, bool SINGLE>
+__global__ __launch_bounds__(kWave, SINGLE ? 2 : sub_min_waves(sizeof(T))) void k_conv_fwd_sub(SubArgs<T> a) {
   extern __shared__ __align__(32) unsigned char sub_lds[];
   int b, g, sl;
   if (!sub_task_of<V::NFG>(a, b, g, sl)) return;
-  sub_fwd_dispatch<V, 0, T>(a, b, g, sl, reinterpret_cast<T*>(sub_lds));
+  sub_fwd_dispatch<V, 0, T, CACHED, SINGLE>(a, b, g, sl, reinterpret_cast<T*>(sub_lds));
 }
 
 // Backward sweep in receiver order: ds per edge, the x-cotangent partials P at
 // the edge's sender-CSR slot, the harmonic cotangent partials.  ACC: ds += the
 // result; the old rows are loaded before the contraction (as in bwd_task).
-template <class V, int G, class T, bool ACC>
+template <class V, int G, class T, bool ACC, bool CACHED>
 __device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl, T* sA, T* sY) {
   using B = typename V::template BG<G>;
   const int lane = threadIdx.x, lgl = a.lgl, S = kWave >> lgl, sub = lane >> lgl;
@@ -1895,7 +1932,7 @@ __device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl,
 #pragma unroll
       for (int i = 0; i < B::NXR; ++i) sld(xr, B::XROW[i], xv[i]);
 #pragma unroll
-      for (int i = 0; i < B::NPATH; ++i) sld<kNT>(sr, B::PATH[i], sv[i]);
+      for (int i = 0; i < B::NPATH; ++i) sld<CACHED ? 0 : kNT>(sr, B::PATH[i], sv[i]);
     };
     auto compute = [&](int j, const T (&xv)[B::NXR][1], const T (&sv)[B::NPATH][1]) {
       const int je = j + sub;
@@ -1919,15 +1956,15 @@ __device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl,
         auto st = [&](int pl, const T (&v)[1]) {
           if constexpr (ACC) {
             const T o[1] = {old[pl][0] + v[0]};
-            sst<kST>(dsr, B::PATH[pl], o);
+            sst<CACHED ? 0 : kST>(dsr, B::PATH[pl], o);
           } else {
-            sst<kST>(dsr, B::PATH[pl], v);
+            sst<CACHED ? 0 : kST>(dsr, B::PATH[pl], v);
           }
         };
         B::template edge<E3_BWD_ALOAD_PIN != 0, 1>(sA + je * B::NA, Yv, xv, sv, dmv, t, dyl, st);
         const SubRow<T> tr = sub_row(a.P, a.tn, slot, x_rows<V>(a) * C, q, true, C, a.wide);
 #pragma unroll
-        for (int i = 0; i < B::NXR; ++i) sst<E3_T_STORE_AUX>(tr, B::XROW[i], t[i]);
+        for (int i = 0; i < B::NXR; ++i) sst<CACHED ? 0 : E3_T_STORE_AUX>(tr, B::XROW[i], t[i]);
 #pragma unroll
         for (int i = 0; i < V::D_SH; ++i) dy[i] = dyl[i];
       }
@@ -1946,24 +1983,24 @@ __device__ __forceinline__ void sub_bwd_task(const SubArgs<T>& a, int b, int sl,
   }
 }
 
-template <class V, int G, class T, bool ACC>
+template <class V, int G, class T, bool ACC, bool CACHED>
 __device__ __forceinline__ void sub_bwd_dispatch(const SubArgs<T>& a, int b, int g, int sl, T* sA, T* sY) {
   if constexpr (G < V::NBG) {
     if (g == G)
-      sub_bwd_task<V, G, T, ACC>(a, b, sl, sA, sY);
+      sub_bwd_task<V, G, T, ACC, CACHED>(a, b, sl, sA, sY);
     else
-      sub_bwd_dispatch<V, G + 1, T, ACC>(a, b, g, sl, sA, sY);
+      sub_bwd_dispatch<V, G + 1, T, ACC, CACHED>(a, b, g, sl, sA, sY);
   }
 }
 
 // dynamic LDS: fb * (V::MAX_NA_B + V::D_SH) values
-template <class V, class T, bool ACC>
+template <class V, class T, bool ACC, bool CACHED>
 __global__ __launch_bounds__(kWave, sub_min_waves(sizeof(T))) void k_conv_bwd_sub(SubArgs<T> a) {
   extern __shared__ __align__(32) unsigned char sub_lds[];
   int b, g, sl;
   if (!sub_task_of<V::NBG>(a, b, g, sl)) return;
   T* sA = reinterpret_cast<T*>(sub_lds);
-  sub_bwd_dispatch<V, 0, T, ACC>(a, b, g, sl, sA, sA + a.fb * V::MAX_NA_B);
+  sub_bwd_dispatch<V, 0, T, ACC, CACHED>(a, b, g, sl, sA, sA + a.fb * V::MAX_NA_B);
 }
 
 // dvec of each live edge from its harmonic cotangent (summed over groups).
@@ -2699,13 +2736,6 @@ inline bool sub_fits(const e3_graph* g, int64_t xr, int64_t pr, int64_t C, int64
   return rows * C * elem <= (int64_t)kSubMaxBytes;
 }
 
-// Lanes per edge for w channels.
-template <class T>
-void sub_width(SubArgs<T>& a, int w) {
-  a.lgl = w > 32 ? 6 : w > 16 ? 5 : w > 8 ? 4 : 3;
-  a.fb = a.lgl >= 5 ? 16 : 32;
-}
-
 // The channels of a float32 sweep whose last slab would leave half of its lanes
 // or more idle, in two launches: the whole slabs, then the last w channels on
 // sub-waves (w <= 32) or, in the forward, on one slab of 64 with one channel
@@ -2721,33 +2751,58 @@ inline int split_of(const e3_plan* p, const e3_graph* g, int64_t waves, int xr, 
   return r <= 32 && !sub_fits(g, xr, pr, C, sizeof(float)) ? 0 : r;
 }
 
-// xr, pr, orr, ng, g0: of the whole layout (as in KindCall); V: the layout or
-// the single-block kind whose rows are swept.
+// The sweep of channels c0 .. c0 + w - 1.  V: the layout or the single-block kind
+// whose rows are swept; kc: of the whole layout.
 template <class V, class T>
-SubArgs<T> sub_args(const e3_plan* p, const e3_graph* g, int xr, int pr, int orr, int ng, int g0) {
+SubArgs<T> sub_args(const e3_plan* p, const e3_graph* g, const KindCall& kc, bool fwd, int c0, int w) {
+  const int xr = kc.xr, pr = kc.pr;
   SubArgs<T> a{};
   a.rowptr = g->rowptr_r, a.eid = g->eid_r, a.src = g->src_r, a.r2s = g->r2s;
   a.n_nodes = (int)g->n_nodes;
   a.chunk = (int)((g->n_nodes + kXcd - 1) / kXcd);
   a.C = p->lay.C;
-  a.nslab = a.nsd = (a.C + kWave - 1) / kWave;
+  a.c0 = c0, a.sl0 = c0 / kWave, a.nslab = (w + kWave - 1) / kWave, a.nsd = (a.C + kWave - 1) / kWave;
   const int64_t row = (int64_t)a.C * sizeof(T);
   a.wide = sub_fits(g, xr, pr, a.C, sizeof(T)) ? 0 : -1;
-  sub_width(a, a.wide ? kWave : a.C);
+  // Lanes per edge.  Receivers of fewer than two edges on average leave sub-waves
+  // idle, and the forward then pays for adding their sums.
+  a.lgl = w > 32 || a.wide ? 6 : w > 16 ? 5 : w > 8 ? 4 : 3;
+  const bool few = fwd && a.lgl < 6 && g->n_live < 2 * g->n_nodes;
+  if (few) a.lgl = 5;
+  // Edges per staged batch: 32 on sub-waves of 16 lanes or fewer, 16 else; in the
+  // forward halved while the staging leaves a CU fewer waves than the launch and
+  // the registers do.
+  constexpr int64_t kCuLds = 160 * 1024, kCus = 256;
+  const int64_t per_cu = (g->n_nodes * V::NFG * a.nslab + kCus - 1) / kCus;
+  a.single = sub_single<V, T>() && per_cu > 4;
+  const int64_t want = std::min<int64_t>(per_cu, sizeof(T) == 4 ? 12 : a.single ? 8 : 6);
+  a.fb = few ? 8 : a.lgl >= 5 ? 16 : 32;
+  while (fwd && a.fb > (a.single ? 8 : 16) && kCuLds / (a.fb * V::MAX_NA_F * (int64_t)sizeof(T)) < want)
+    a.fb /= 2;
+  // see kSubCache
+  const int64_t moved = row * (g->n_edges * pr * (fwd ? 1 : 2) + (fwd ? 0 : g->n_live * xr));
+  a.cached = sizeof(T) == 8 && (row % 64 != 0 || row <= 64 || moved <= kSubCache);
   auto bytes = [&](int64_t n, int64_t stride, int64_t rows) {
     return (unsigned)(a.wide ? rows * row : n > 0 ? ((n - 1) * stride + rows) * row : 0);
   };
   a.xn = bytes(g->n_nodes, xr, V::D_IN), a.sn = bytes(g->n_edges, pr, V::NP), a.tn = bytes(g->n_live, xr, V::D_IN);
   a.dsn = a.sn;
-  a.xr = xr, a.pr = pr, a.orr = orr, a.ng = ng, a.g0 = g0;
+  a.xr = xr, a.pr = pr, a.orr = kc.orr, a.ng = kc.ng, a.g0 = kc.g0;
   return a;
 }
 
 template <class V, class T>
 e3_status launch_fwd_sub(const SubArgs<T>& a, const char* name, hipStream_t st) {
   TimedLaunch t_(name, st);
-  hipLaunchKernelGGL((k_conv_fwd_sub<V, T>), dim3((unsigned)(kXcd * a.chunk * V::NFG * a.nslab)), dim3(kWave),
-                     (size_t)a.fb * V::MAX_NA_F * sizeof(T), st, a);
+  const dim3 grid((unsigned)(kXcd * a.chunk * V::NFG * a.nslab));
+  const size_t lds = (size_t)a.fb * V::MAX_NA_F * sizeof(T);
+  auto* k = k_conv_fwd_sub<V, T, false, false>;
+  if constexpr (sizeof(T) == 8) {
+    if (a.cached) k = k_conv_fwd_sub<V, T, true, false>;
+    if constexpr (sub_single<V, T>())
+      if (a.single) k = a.cached ? k_conv_fwd_sub<V, T, true, true> : k_conv_fwd_sub<V, T, false, true>;
+  }
+  hipLaunchKernelGGL(k, grid, dim3(kWave), lds, st, a);
   E3_HIP(hipGetLastError());
   return E3_OK;
 }
@@ -2758,14 +2813,13 @@ e3_status launch_bwd_sub(const SubArgs<T>& a, bool accum, const char* name, hipS
   TimedLaunch t_(name, st);
   const dim3 grid((unsigned)(kXcd * a.chunk * V::NBG * a.nslab));
   const size_t lds = (size_t)a.fb * (V::MAX_NA_B + V::D_SH) * sizeof(T);
+  auto* k = k_conv_bwd_sub<V, T, false, false>;
   if constexpr (sizeof(T) == 4) {
-    if (accum) {
-      hipLaunchKernelGGL((k_conv_bwd_sub<V, T, true>), grid, dim3(kWave), lds, st, a);
-      E3_HIP(hipGetLastError());
-      return E3_OK;
-    }
+    if (accum) k = k_conv_bwd_sub<V, T, true, false>;
+  } else {
+    if (a.cached) k = k_conv_bwd_sub<V, T, false, true>;
   }
-  hipLaunchKernelGGL((k_conv_bwd_sub<V, T, false>), grid, dim3(kWave), lds, st, a);
+  hipLaunchKernelGGL(k, grid, dim3(kWave), lds, st, a);
   E3_HIP(hipGetLastError());
   return E3_OK;
 }
@@ -2775,10 +2829,8 @@ template <class V, bool ACCT>
 e3_status launch_fwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const KindCall& kc, const char* name,
                      hipStream_t st) {
   auto sub = [&](int c0, int w) {
-    auto b = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+    auto b = sub_args<V, float>(p, g, kc, true, c0, w);
     b.x = a.x, b.vec = a.vec, b.y = a.y, b.s = a.s, b.m = a.m, b.accum = a.accum;
-    b.c0 = c0, b.nslab = 1;
-    sub_width(b, w);
     return launch_fwd_sub<V>(b, name, st);
   };
   const int C = a.C;
@@ -2813,12 +2865,10 @@ template <class V, bool ACCT>
 e3_status launch_bwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const KindCall& kc, const char* name,
                      hipStream_t st) {
   auto sub = [&](int c0, int w) {
-    auto b = sub_args<V, float>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+    auto b = sub_args<V, float>(p, g, kc, false, c0, w);
     b.x = a.x, b.vec = a.vec, b.y = a.y, b.s = a.s, b.dm = a.dm, b.ds = a.ds, b.P = a.T, b.DY = a.DY;
     if (!a.ds_row) b.dsn = 0;
     if (!a.t_row) b.tn = 0;
-    b.c0 = c0, b.sl0 = c0 / kWave, b.nslab = 1, b.nsd = p->nslab_b;
-    sub_width(b, w);
     return launch_bwd_sub<V>(b, a.accum, name, st);
   };
   static_assert(E3_BWD_CPL == 1, "the launches below count slabs of 64 channels");
@@ -3241,7 +3291,7 @@ template <class V>
 e3_status run_fwd64(const e3_plan* p, const e3_graph* g, const double* x, const double* vec, const double* s,
                     double* m, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  auto a = sub_args<V, double>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
+  auto a = sub_args<V, double>(p, g, KindCall{V::D_IN, V::NP, V::D_OUT, V::NBG, 0}, true, 0, p->lay.C);
   a.x = x, a.vec = vec, a.s = s, a.m = m;
   return launch_fwd_sub<V>(a, "conv_fwd_f64", st);
 }
@@ -3251,7 +3301,7 @@ e3_status run_bwd64(const e3_plan* p, const e3_graph* g, const double* x, const 
                     const double* dm, double* dx, double* dvec, double* ds, void* ws, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
   const Ws w = bwd_ws64<V>(p, g);
-  auto a = sub_args<V, double>(p, g, V::D_IN, V::NP, V::D_OUT, V::NBG, 0);
+  auto a = sub_args<V, double>(p, g, KindCall{V::D_IN, V::NP, V::D_OUT, V::NBG, 0}, false, 0, p->lay.C);
   a.x = x, a.vec = vec, a.s = s, a.dm = dm, a.ds = ds, a.P = reinterpret_cast<double*>(ws);
   a.DY = reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + w.t_bytes);
   if (g->n_live > 0) {
@@ -3341,7 +3391,7 @@ template <class V>
 e3_status kind_fwd64(const e3_plan* p, const e3_graph* g, const double* x, const double* vec, const double* s,
                      double* m, const KindCall& kc, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  auto a = sub_args<V, double>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+  auto a = sub_args<V, double>(p, g, kc, true, 0, p->lay.C);
   a.x = x, a.vec = vec, a.s = s, a.m = m;
   return launch_fwd_sub<V>(a, "kind_fwd_f64", st);
 }
@@ -3350,7 +3400,7 @@ template <class V>
 e3_status kind_bwd64(const e3_plan* p, const e3_graph* g, const double* x, const double* vec, const double* s,
                      const double* dm, double* T, double* DY, double* ds, const KindCall& kc, hipStream_t st) {
   if (g->n_live == 0) return E3_OK;
-  auto a = sub_args<V, double>(p, g, kc.xr, kc.pr, kc.orr, kc.ng, kc.g0);
+  auto a = sub_args<V, double>(p, g, kc, false, 0, p->lay.C);
   a.x = x, a.vec = vec, a.s = s, a.dm = dm, a.ds = ds, a.P = T, a.DY = DY;
   return launch_bwd_sub<V>(a, false, "kind_bwd_f64", st);
 }

@@ -185,6 +185,43 @@ def test_ragged_slabs_accumulate(e3, C, composed):
             assert torch.equal(full, part) if name in want else part is None
 
 
+# launches of many waves: smaller batches, one row buffer (float64, groups of many
+# rows), receivers of fewer than two edges on average; and the layouts of many
+# paths whose last slab is split off (C = 80, 96 backward, 192 forward, from about
+# 4,100 and 1,024 nodes on)
+@pytest.mark.parametrize("blocks,l,natural,C,f64,n,E", [
+    ("0e+1o+2e+3o", 3, True, 36, True, 700, 2500), ("0e+1o+2e+3o", 3, True, 8, True, 700, 2500),
+    ("0e+1o+2e", 2, False, 16, True, 1200, 3000), ("0e+1o+2e", 2, False, 68, True, 600, 1500),
+    ("0e+1o+2e+3o", 3, False, 20, True, 1100, 2500), ("0e+1o+2e", 3, False, 12, True, 1500, 2000),
+    ("0e+1o+2e+3o", 3, False, 8, False, 1500, 7000), ("0e+1o+2e", 2, False, 16, False, 4000, 9000),
+    ("0e+1o+2e+3o", 3, False, 4, False, 2000, 2000), ("0e+1o+2e", 3, False, 32, False, 1500, 1600),
+    ("2e+0o+1e", 3, False, 12, False, 1500, 1600),
+    ("0e+1o+2e", 3, False, 80, False, 4200, 2500), ("0e+1o+2e", 3, False, 96, False, 4200, 2500),
+    ("0e+1o+2e", 3, False, 192, False, 1100, 1000),
+])
+def test_sweeps_of_many_waves(e3, blocks, l, natural, C, f64, n, E):
+    rng = np.random.default_rng(n + C)
+    dt = np.float64 if f64 else np.float32
+    irreps = "+".join(f"{C}x{b}" for b in blocks.split("+"))
+    lay = oirreps.layout(irreps, l, l, "natural" if natural else "all")
+    plan = e3.Plan(irreps, l, l, natural=natural)
+    snd, rcv = (rng.integers(0, n, E).astype(np.int32) for _ in range(2))
+    rcv[:40], rcv[40:57] = 5, 6   # two receivers of more than one batch
+    pad = n - 1
+    vec = rng.standard_normal((E, 3)).astype(dt)
+    x, s, dm = (rng.standard_normal(sh).astype(dt) for sh in
+                ((n, lay.d_in, C), (E, lay.n_paths, C), (n, lay.d_out, C)))
+    print("[case] many waves", irreps, f64, plan.kernels, n, E, flush=True)
+    G = e3.Graph(to_dev(snd), to_dev(rcv), n, pad_node=pad)
+    fwd, bwd = (e3.conv_fwd_f64, e3.conv_bwd_f64) if f64 else (e3.conv_fwd, e3.conv_bwd)
+    dev = [to_dev(a) for a in (x, vec, s)]
+    got = (fwd(plan, G, *dev), *bwd(plan, G, *dev, to_dev(dm)))
+    ref = oconv.conv_bwd(lay, x, vec, s, dm, snd, rcv, n, pad_node=pad)
+    refs = (oconv.conv_fwd(lay, x, vec, s, snd, rcv, n, pad_node=pad), ref["dx"], ref["dvec"], ref["ds"])
+    for a, b in zip(got, refs):
+        assert rel_l2(to_np(a), b.numpy()) < (TOL64 if f64 else TOL)
+
+
 # one NaN row of x and one infinite row of s: sub-waves (with steps of fewer
 # edges than the wave takes), whole waves, split slabs, short and long segment sums
 @pytest.mark.parametrize("blocks,C,f64,n", [
