@@ -679,7 +679,7 @@ struct ConvArgs {
   int chunk;  // receivers per XCD
   int C;
   int nslab;  // channel slabs of 64 lanes x CPL channels
-  int c0;     // plain sweeps: first channel of the launch's first slab
+  int c0;     // plain forward: first channel of the launch's first slab
   int nsd;    // backward sweep: slabs of a harmonic-partial slot (all launches')
   const float* y;  // harmonics [E, D_sh] given by the caller, or null: from vec
   int accum;       // add to m (forward) / ds (backward) instead of overwriting it
@@ -2736,19 +2736,31 @@ inline bool sub_fits(const e3_graph* g, int64_t xr, int64_t pr, int64_t C, int64
   return rows * C * elem <= (int64_t)kSubMaxBytes;
 }
 
-// The channels of a float32 sweep whose last slab would leave half of its lanes
-// or more idle, in two launches: the whole slabs, then the last w channels on
-// sub-waves (w <= 32) or, in the forward, on one slab of 64 with one channel
-// per lane.  Forward, slabs of 128, C > 128 (1,500 nodes, l <= 3): 348 -> 300 us
-// at C = 160, 358 -> 292 us at 132, 360 -> 338 us at 192; no better at 65 to 96
-// or from 224 on.  Backward, slabs of 64, w = 32: 2295 -> 2050 us at C = 96
-// (5,001 nodes), 727 -> 716 us at 160; other w gained nothing.  Graphs of fewer waves than kSplitWaves keep one
-// launch: they do not fill the chip, and two launches are two latencies.
-constexpr int64_t kSplitWaves = 4096;
-inline int split_of(const e3_plan* p, const e3_graph* g, int64_t waves, int xr, int pr, bool fwd) {
-  const int C = p->lay.C, r = C % (fwd ? 2 * kWave : kWave);
-  if (waves < kSplitWaves || (fwd ? C <= 2 * kWave || r > kWave : C <= kWave || r != 32)) return 0;
-  return r <= 32 && !sub_fits(g, xr, pr, C, sizeof(float)) ? 0 : r;
+// The last w channels of a float32 sweep that run in a launch of their own, on
+// sub-waves (64: one channel per lane), because their slab would leave half of its
+// lanes or more idle; 0 where one launch is no slower.  (Split against one launch, us.)
+// Forward, slabs of 128, 129 to 160 channels: C = 132 68 against 75 (0e+1o, l <= 2,
+// 3,000 nodes) and 263 against 312 (l <= 3, 2,000), 144 279 against 304, 160 269
+// against 290.  More: C = 192 of 16 paths or more, l <= 3, 5,000 nodes 459 against 485,
+// natural parities 328 against 354; 0e+1o 122 against 116, and others: C = 164 560
+// against 534, 184 579 against 549 (l <= 3).  A third slab: C = 272 292 against 276, 288
+// 107 against 104, 448 158 against 151.
+// Backward, slabs of 64, C = 80, 96 and 16 paths or more: l <= 3, 6,000 nodes 1123
+// against 1227 and 1142 against 1221.  Fewer paths: 0e+1o, 5,000 nodes of C = 96
+// 255 against 242.  Pieces of 64 bytes split between the launches: C = 76 612
+// against 463.  A third slab: C = 160 361 against 347, 288 1123 against 1106.
+// Single-block kinds, a launch per block: backward of C = 96 154 against 123.
+// Small graphs do not fill the chip twice: forward of C = 160 at 3,000 waves 45
+// against 42, at 6,000 104 against 107, at 20,000 269 against 296; backward of C = 96 at
+// 6,000 waves 370 against 352, at 12,000 290 against 283, at 18,000 387 against 406.
+template <class V>
+int split_of(const e3_plan* p, const e3_graph* g, const KindCall& kc, bool fwd) {
+  const int slab = fwd ? 2 * kWave : kWave, C = p->lay.C, w = C - slab;
+  const int64_t waves = 2 * g->n_nodes * (fwd ? V::NFG : V::NBG);
+  if (fwd && w == kWave) return !V::RT && V::NP >= 16 && waves >= 4096 ? w : 0;
+  if (w <= 0 || w > 32 || !sub_fits(g, kc.xr, kc.pr, C, sizeof(float))) return 0;
+  if (fwd) return waves >= 4096 ? w : 0;
+  return !V::RT && w % 16 == 0 && V::NP >= 16 && waves >= 16384 ? w : 0;
 }
 
 // The sweep of channels c0 .. c0 + w - 1.  V: the layout or the single-block kind
@@ -2852,9 +2864,8 @@ e3_status launch_fwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const Kind
     E3_HIP(hipGetLastError());
     return E3_OK;
   };
-  const int cpl = p->cpl_f, slab = kWave * cpl;
-  const int w = split_of(p, g, g->n_nodes * V::NFG * p->nslab_f, kc.xr, kc.pr, true);
-  const e3_status r = main(0, cpl, (C - w + slab - 1) / slab);
+  const int w = split_of<V>(p, g, kc, true), slab = kWave * p->cpl_f;
+  const e3_status r = main(0, p->cpl_f, (C - w + slab - 1) / slab);
   if (r != E3_OK || w == 0) return r;
   return w <= 32 ? sub(C - w, w) : main(C - w, 1, 1);
 }
@@ -2874,7 +2885,7 @@ e3_status launch_bwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const Kind
   static_assert(E3_BWD_CPL == 1, "the launches below count slabs of 64 channels");
   const int C = a.C;
   if (C <= 32 && sub_fits(g, kc.xr, kc.pr, C, sizeof(float))) return sub(0, C);
-  const int w = split_of(p, g, g->n_nodes * V::NBG * p->nslab_b, kc.xr, kc.pr, false);
+  const int w = split_of<V>(p, g, kc, false);
   a.nsd = p->nslab_b, a.nslab = (C - w + kWave - 1) / kWave;
   // several slabs of rows that are not whole 64-byte pieces (see k_conv_bwd_edges)
   const bool cached = C > kWave && C % 16 != 0;
