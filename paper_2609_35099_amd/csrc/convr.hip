@@ -854,7 +854,6 @@ e3_status comp_create(e3_plan* p) {
   p->composed = true;
   p->cpl_f = C <= kWave ? 1 : E3_FWD_CPL;
   p->nslab_f = (C + kWave * p->cpl_f - 1) / (kWave * p->cpl_f);
-  p->cpl_b = 1;
   p->nslab_b = (C + kWave - 1) / kWave;
   return E3_OK;
 }

@@ -638,9 +638,6 @@ __global__ void k_graph_r2s(const int32_t* __restrict__ eid_r, const int32_t* __
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-int cpl_index(int cpl) { return cpl == 1 ? 0 : 1; }
-int cpl_of(const e3_plan* p) { return p->cpl_f; }
-
 // A compiled variant (every entry point).
 e3_status check_plan(const e3_plan* p) {
   if (!p) return E3_ERR_INVALID_ARG;
@@ -780,8 +777,7 @@ e3_status e3_plan_create(const char* irreps_x, int lmax_sh, int lmax_out, unsign
   if (p->variant >= 0) {
     p->cpl_f = C <= kWave ? 1 : E3_FWD_CPL;
     p->nslab_f = (C + kWave * p->cpl_f - 1) / (kWave * p->cpl_f);
-    p->cpl_b = C <= kWave ? 1 : E3_BWD_CPL;
-    p->nslab_b = (C + kWave * p->cpl_b - 1) / (kWave * p->cpl_b);
+    p->nslab_b = (C + kWave - 1) / kWave;
   } else if ((flags & E3_PLAN_RECORDS) || comp_create(p) != E3_OK) {
     // still a valid plan (its tables can be queried) when neither path takes
     // it: its compute calls report why
@@ -1022,7 +1018,7 @@ e3_status e3_tp_fwd(const e3_plan* p, const float* x, const float* y, const floa
   if (rows == 0) return E3_OK;
   if (p->variant < 0) return rec_fwd(p, nullptr, rows, x, nullptr, y, w, z, 0, reinterpret_cast<hipStream_t>(stream));
   const VariantOps& v = (*kVariants[p->variant]());
-  return v.tp[cpl_index(cpl_of(p))](p, x, y, w, z, rows, reinterpret_cast<hipStream_t>(stream));
+  return v.tp[p->cpl_f == 1 ? 0 : 1](p, x, y, w, z, rows, reinterpret_cast<hipStream_t>(stream));
 }
 
 e3_status e3_tp_workspace_size(const e3_plan* p, int64_t rows, size_t* bwd_bytes) {
@@ -1072,7 +1068,7 @@ e3_status e3_conv_fwd(const e3_plan* p, const e3_graph* g, const float* x, const
   if (g->n_live > 0 && (!vec || !s || !aligned16(s))) return E3_ERR_INVALID_ARG;
   if (p->variant < 0) return rec_fwd(p, g, 0, x, vec, nullptr, s, m, 0, reinterpret_cast<hipStream_t>(stream));
   const VariantOps& v = (*kVariants[p->variant]());
-  return v.fwd[cpl_index(cpl_of(p))](p, g, x, vec, nullptr, s, m, 0, reinterpret_cast<hipStream_t>(stream));
+  return v.fwd(p, g, x, vec, nullptr, s, m, 0, reinterpret_cast<hipStream_t>(stream));
 }
 
 e3_status e3_conv_bwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* s,
@@ -1091,8 +1087,7 @@ e3_status e3_conv_bwd(const e3_plan* p, const e3_graph* g, const float* x, const
     return rec_bwd(p, g, 0, x, vec, nullptr, s, dm, dx, dvec, nullptr, ds, 0, ws,
                    reinterpret_cast<hipStream_t>(stream));
   const VariantOps& v = (*kVariants[p->variant]());
-  return v.bwd[cpl_index(cpl_of(p))](p, g, x, vec, nullptr, s, dm, dx, dvec, nullptr, ds, 0, ws,
-                                     reinterpret_cast<hipStream_t>(stream));
+  return v.bwd(p, g, x, vec, nullptr, s, dm, dx, dvec, nullptr, ds, 0, ws, reinterpret_cast<hipStream_t>(stream));
 }
 
 // ---- float64 builds
@@ -1237,8 +1232,7 @@ e3_status e3_conv_bwd_noalloc(const e3_plan* p, const e3_graph* g, const float* 
     return rec_bwd(p, g, 0, x, vec, nullptr, s, dm, dx, dvec, nullptr, ds, 0, ptr,
                    reinterpret_cast<hipStream_t>(stream));
   const VariantOps& v = (*kVariants[p->variant]());
-  return v.bwd[cpl_index(cpl_of(p))](p, g, x, vec, nullptr, s, dm, dx, dvec, nullptr, ds, 0, ptr,
-                                     reinterpret_cast<hipStream_t>(stream));
+  return v.bwd(p, g, x, vec, nullptr, s, dm, dx, dvec, nullptr, ds, 0, ptr, reinterpret_cast<hipStream_t>(stream));
 }
 
 e3_status e3_conv_radial_workspace_size(const e3_plan* p, const e3_graph* g, int K, size_t* bwd_bytes) {
@@ -1288,8 +1282,7 @@ e3_status e3_conv_fwd_y(const e3_plan* p, const e3_graph* g, const float* x, con
   if (p->variant < 0)
     return rec_fwd(p, g, 0, x, nullptr, y, s, m, accumulate != 0, reinterpret_cast<hipStream_t>(stream));
   const VariantOps& v = (*kVariants[p->variant]());
-  return v.fwd[cpl_index(cpl_of(p))](p, g, x, nullptr, y, s, m, accumulate != 0,
-                                     reinterpret_cast<hipStream_t>(stream));
+  return v.fwd(p, g, x, nullptr, y, s, m, accumulate != 0, reinterpret_cast<hipStream_t>(stream));
 }
 
 e3_status e3_conv_bwd_y(const e3_plan* p, const e3_graph* g, const float* x, const float* y, const float* s,
@@ -1308,9 +1301,8 @@ e3_status e3_conv_bwd_y(const e3_plan* p, const e3_graph* g, const float* x, con
     return rec_bwd(p, g, 0, x, nullptr, y, s, dm, dx, nullptr, dy, ds, accumulate ? (kAccDx | kAccDy | kAccDs) : 0,
                    ws, reinterpret_cast<hipStream_t>(stream));
   const VariantOps& v = (*kVariants[p->variant]());
-  return v.bwd[cpl_index(cpl_of(p))](p, g, x, nullptr, y, s, dm, dx, nullptr, dy, ds,
-                                     accumulate ? (kAccDx | kAccDy | kAccDs) : 0, ws,
-                                     reinterpret_cast<hipStream_t>(stream));
+  return v.bwd(p, g, x, nullptr, y, s, dm, dx, nullptr, dy, ds, accumulate ? (kAccDx | kAccDy | kAccDs) : 0, ws,
+               reinterpret_cast<hipStream_t>(stream));
 }
 
 e3_status e3_conv_bwd2(const e3_plan* p, const e3_graph* g, const float* x, const float* y, const float* s,
@@ -1340,17 +1332,10 @@ e3_status e3_conv_bwd2(const e3_plan* p, const e3_graph* g, const float* x, cons
     return rec_bwd(p, g, 0, x, nullptr, y, dds, dm, gx, nullptr, gy, nullptr, kAccDx | kAccDy, ws, hs);
   }
   const VariantOps& v = (*kVariants[p->variant]());
-  const int ci = cpl_index(cpl_of(p));
   // ddm = conv(ddx, y, s) + conv(x, ddy, s) + conv(x, y, dds), in one pass
   if ((st = v.fwd3(p, g, x, ddx, y, ddy, s, dds, gdm, hs)) != E3_OK) return st;
-  // gx, gy, gs in one sweep where the backward runs one channel per lane
-  if (p->cpl_b == 1) return v.bwd3(p, g, x, ddx, y, ddy, s, dds, dm, gx, gy, gs, ws, hs);
-  // (-, d_x y, d_x s) = conv_bwd(ddx, y, s, dm)
-  if ((st = v.bwd[ci](p, g, ddx, nullptr, y, s, dm, nullptr, nullptr, gy, gs, 0, ws, hs)) != E3_OK) return st;
-  // (d_y x, -, d_y s) = conv_bwd(x, ddy, s, dm)
-  if ((st = v.bwd[ci](p, g, x, nullptr, ddy, s, dm, gx, nullptr, nullptr, gs, kAccDs, ws, hs)) != E3_OK) return st;
-  // (d_s x, d_s y, -) = conv_bwd(x, y, dds, dm)
-  return v.bwd[ci](p, g, x, nullptr, y, dds, dm, gx, nullptr, gy, nullptr, kAccDx | kAccDy, ws, hs);
+  // gx, gy, gs in one sweep
+  return v.bwd3(p, g, x, ddx, y, ddy, s, dds, dm, gx, gy, gs, ws, hs);
 }
 
 }  // extern "C"

@@ -156,15 +156,12 @@ inline int64_t tile_grid(bool xcd, int64_t rows, int rows_per_tile, int per) {
 
 // Build-time tuning knobs: minimum resident waves per SIMD requested from the
 // compiler for the forward and backward sweeps, and channels per lane of the
-// backward sweep when C > 64.
+// forward when C > 64 (the backward has one).
 #ifndef E3_FWD_MIN_WAVES
 #define E3_FWD_MIN_WAVES 2
 #endif
 #ifndef E3_BWD_MIN_WAVES
 #define E3_BWD_MIN_WAVES 2
-#endif
-#ifndef E3_BWD_CPL
-#define E3_BWD_CPL 1
 #endif
 #ifndef E3_FWD_CPL
 #define E3_FWD_CPL 2
@@ -2533,7 +2530,7 @@ struct e3_plan {
   int variant = -1;
   // Channels per lane of the forward / tensor-product / dx kernels (the
   // backward sweep always uses 1) and the number of 64-lane channel slabs.
-  int cpl_f = 0, cpl_b = 0, nslab_f = 0, nslab_b = 0;
+  int cpl_f = 0, nslab_f = 0, nslab_b = 0;
   // A layout without a compiled variant runs on the record path, whose
   // tables are uploaded at plan creation (null when that was not possible).
   RecPlan* rec = nullptr;
@@ -2625,9 +2622,9 @@ e3_status comp_tpb64(const e3_plan* p, const double* x, const double* y, const d
 struct VariantOps {
   const char* sig;
   int d_in, d_sh, d_out, np, lsh, nbg;
-  e3_status (*fwd[2])(const e3_plan*, const e3_graph*, const float*, const float*, const float*, const float*,
+  e3_status (*fwd)(const e3_plan*, const e3_graph*, const float*, const float*, const float*, const float*,
                       float*, int, hipStream_t);
-  e3_status (*bwd[2])(const e3_plan*, const e3_graph*, const float*, const float*, const float*, const float*,
+  e3_status (*bwd)(const e3_plan*, const e3_graph*, const float*, const float*, const float*, const float*,
                       const float*, float*, float*, float*, float*, int, void*, hipStream_t);
   e3_status (*tp[2])(const e3_plan*, const float*, const float*, const float*, float*, int64_t, hipStream_t);
   Ws (*ws)(const e3_plan*, const e3_graph*);
@@ -2882,7 +2879,6 @@ e3_status launch_bwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const Kind
     if (!a.t_row) b.tn = 0;
     return launch_bwd_sub<V>(b, a.accum, name, st);
   };
-  static_assert(E3_BWD_CPL == 1, "the launches below count slabs of 64 channels");
   const int C = a.C;
   if (C <= 32 && sub_fits(g, kc.xr, kc.pr, C, sizeof(float))) return sub(0, C);
   const int w = split_of<V>(p, g, kc, false);
@@ -2905,7 +2901,7 @@ e3_status launch_bwd(const e3_plan* p, const e3_graph* g, ConvArgs a, const Kind
 
 // One forward convolution.  y: caller's harmonics or null (from vec);
 // accum: m += instead of m =.
-template <class V, int CPL>
+template <class V>
 e3_status run_fwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* y,
                   const float* s, float* m, int accum, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
@@ -2986,7 +2982,7 @@ bool launch_finish(const e3_plan* p, const e3_graph* g, const float* P, float* d
 // contents instead of overwriting them.
 constexpr int kAccDx = 1, kAccDy = 2, kAccDs = 4;
 
-template <class V, int CPLX>
+template <class V>
 e3_status run_bwd(const e3_plan* p, const e3_graph* g, const float* x, const float* vec, const float* y,
                   const float* s, const float* dm, float* dx, float* dvec, float* dy, float* ds, int accum, void* ws,
                   hipStream_t st) {
@@ -3041,14 +3037,12 @@ e3_status run_bwd(const e3_plan* p, const e3_graph* g, const float* x, const flo
 
 // The double backward's three backward terms in one sweep (k_conv_bwd3),
 // then the sender segment sum (gx) and the harmonic cotangent sum (gy); all
-// three outputs overwritten.  One channel per lane: the workspace layout of
-// e3_conv_bwd with one channel per lane (cpl_b == 1).
+// three outputs overwritten.  The workspace layout of e3_conv_bwd.
 template <class V>
 e3_status run_bwd3(const e3_plan* p, const e3_graph* g, const float* x, const float* x2, const float* y,
                    const float* y2, const float* s, const float* s2, const float* dm, float* gx, float* gy,
                    float* gs, void* ws, hipStream_t st) {
   if (g->n_nodes == 0) return E3_OK;
-  if (p->cpl_b != 1) return E3_ERR_UNSUPPORTED;
   Ws w = bwd_ws<V>(p, g);
   ConvArgs a = base_args(p, g);
   a.x = x, a.x2 = x2, a.y = y, a.y2 = y2, a.s = s, a.s2 = s2, a.dm = dm, a.ds = gs;
@@ -3530,8 +3524,8 @@ e3_status kind_bwd3(const e3_plan* p, const e3_graph* g, const float* x, const f
              e3gen::V::NP,                                                                               \
              e3gen::V::LSH,                                                                              \
              e3gen::V::NBG,                                                                              \
-             {&run_fwd<e3gen::V, 1>, &run_fwd<e3gen::V, 2>},                                             \
-             {&run_bwd<e3gen::V, 1>, &run_bwd<e3gen::V, 2>},                                             \
+             &run_fwd<e3gen::V>,                                                                         \
+             &run_bwd<e3gen::V>,                                                                         \
              {&run_tp<e3gen::V, 1>, &run_tp<e3gen::V, 2>},                                               \
              &bwd_ws<e3gen::V>,                                                                          \
              &run_tp_bwd<e3gen::V, 1>,                                                                   \
