@@ -2778,16 +2778,17 @@ SubArgs<T> sub_args(const e3_plan* p, const e3_graph* g, const KindCall& kc, boo
   a.lgl = w > 32 || a.wide ? 6 : w > 16 ? 5 : w > 8 ? 4 : 3;
   const bool few = fwd && a.lgl < 6 && g->n_live < 2 * g->n_nodes;
   if (few) a.lgl = 5;
-  // Edges per staged batch: 32 on sub-waves of 16 lanes or fewer, 16 else; in the
-  // forward halved while the staging leaves a CU fewer waves than the launch and
-  // the registers do.
-  constexpr int64_t kCuLds = 160 * 1024, kCus = 256;
+  // Edges per staged batch: 32 on sub-waves of 16 lanes or fewer, 16 else; halved
+  // while the staging takes more than a launch gets unasked (at most 60 KiB in the
+  // layouts built here), and in the forward while it leaves a CU fewer waves than
+  // the launch and the registers do.
+  constexpr int64_t kCuLds = 160 * 1024, kCus = 256, kMaxLds = 64 * 1024;
   const int64_t per_cu = (g->n_nodes * V::NFG * a.nslab + kCus - 1) / kCus;
   a.single = sub_single<V, T>() && per_cu > 4;
   const int64_t want = std::min<int64_t>(per_cu, sizeof(T) == 4 ? 12 : a.single ? 8 : 6);
+  const int64_t staged = sizeof(T) * (fwd ? V::MAX_NA_F : V::MAX_NA_B + V::D_SH);
   a.fb = few ? 8 : a.lgl >= 5 ? 16 : 32;
-  while (fwd && a.fb > (a.single ? 8 : 16) && kCuLds / (a.fb * V::MAX_NA_F * (int64_t)sizeof(T)) < want)
-    a.fb /= 2;
+  while (a.fb * staged > kMaxLds || (fwd && a.fb > (a.single ? 8 : 16) && kCuLds / (a.fb * staged) < want)) a.fb /= 2;
   // see kSubCache
   const int64_t moved = row * (g->n_edges * pr * (fwd ? 1 : 2) + (fwd ? 0 : g->n_live * xr));
   a.cached = sizeof(T) == 8 && (row % 64 != 0 || row <= 64 || moved <= kSubCache);
