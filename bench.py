@@ -35,9 +35,9 @@ HBM_PEAK_GBS = 8000.0
 # the published 157.3 TFLOP/s counts the packed FMA.
 VALU_PEAK_TFLOPS = 78.6
 VALU_PEAK_PACKED_TFLOPS = 157.3
-# The linear mixing makes a float32 product of six bf16 term products on the
+# The linear mixing makes a float32 product of eight bf16 term products on the
 # matrix cores (2.5 PFLOP/s dense).
-LIN_PEAK_TFLOPS = 2500.0 / 6
+LIN_PEAK_TFLOPS = 2500.0 / 8
 
 
 def log(*a):
@@ -313,8 +313,19 @@ PROF_TRACE = ("rocprofv3 --kernel-trace --stats --output-format csv -d $OUT/trac
               "-- python -u $REPO/bench.py --only {s} --steps 10 --warmup 2 --no-cpu-baseline")
 PROF_PMC = ("rocprofv3 --pmc {c} --output-format csv -d $OUT/pmc_{s}_{c} -o p "
             "-- python -u $REPO/bench.py --only {s} --steps 2 --warmup 1 --no-cpu-baseline --copy-probe")
-PROF_UTIL = ("rocprofv3 --pmc MfmaUtil VALUBusy LdsUtil SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_INSTS_VALU --output-format csv "
+PROF_UTIL = ("rocprofv3 --pmc MfmaUtil VALUBusy LdsUtil {m} SQ_INSTS_VALU --output-format csv "
              "-d $OUT/util_{s} -o u -- python -u $REPO/bench.py --only {s} --steps 2 --warmup 1 --no-cpu-baseline")
+# the small, narrow and float64 workloads of perf/cases.py, whose kernels the sections above do not reach
+PROF_CASES = ("rocprofv3 --kernel-trace --stats --output-format csv -d $OUT/trace_{s} -o trace -- python -u -c "
+              "\"import sys; sys.path.insert(0, '$REPO'); from perf import cases as c; "
+              "s = [c.prepare(x, 1) for x in c.listed() if x['name'] == '{s}'][0]; [c.run(s) for _ in range(12)]\"")
+
+
+def mops(sec):
+    """The matrix operation counter of a section: its kernels' type."""
+    return "SQ_INSTS_VALU_MFMA_MOPS_" + ("BF16" if sec == "linear" else "F32")
+
+
 PROF_FILES = [  # file, kind, sections, title
     ("conv_water8k_tp200k_kernel_trace.txt", "trace", ["conv", "tp"],
      "Kernel-time summary: convolution forward+backward (24,000-atom water box, 128 ch, l<=3) and weighted TP "
@@ -334,6 +345,10 @@ PROF_FILES = [  # file, kind, sections, title
     ("radial_water8k_hbm_bytes.txt", "hbm", ["radial"],
      "HBM byte counters per dispatch (FETCH_SIZE, WRITE_SIZE in KiB), scaled by a plain 2 GiB device copy; "
      "one counter per run"),
+    ("cases_kernel_trace.txt", "cases",
+     ["conv_cluster64_c8", "md_1503_c128", "conv_9999_c32", "conv_5001_c96_natural", "conv64_1503_c32",
+      "records_30011_c100"],
+     "Kernel-time summary: small, narrow and float64 workloads of perf/cases.py"),
     ("util_water8k_tp200k.txt", "util", ["conv", "linear", "radial", "tp", "bwd2", "generic"],
      "Per-kernel utilisation (rocprofv3 derived metrics, per dispatch, mean over dispatches)"),
 ]
@@ -341,6 +356,9 @@ PROF_FILES = [  # file, kind, sections, title
 PROF_NAMES = [("k_conv_bwd_edges", "conv_bwd_edges"), ("k_conv_bwd3", "conv_bwd3"), ("k_conv_fwd3", "conv_fwd3"),
               ("k_conv_fwd_rad", "conv_fwd_rad"), ("k_conv_bwd_rad", "conv_bwd_rad_edges"),
               ("k_conv_fwd", "conv_fwd"), ("k_conv_bwd_dx", "conv_bwd_dx"), ("k_conv_bwd_dvec", "conv_bwd_dvec"),
+              ("k_conv_fwd_sub", "conv_fwd_sub"), ("k_conv_bwd_sub", "conv_bwd_sub"),
+              ("k_conv_bwd_dx_short", "conv_bwd_dx_short"), ("k_conv_bwd_dvec64", "conv_bwd_dvec_f64"),
+              ("k_sort_hist", "sort_hist"), ("k_sort_scan", "sort_scan"), ("k_sort_scatter", "sort_scatter"),
               ("k_conv_bwd_finish", "conv_bwd_finish"), ("k_conv_bwd_dy", "conv_bwd_dy"), ("k_zero_pad", "zero_pad"),
               ("k_rad_grad", "rad_grad"),
               ("k_rad_dw_sum", "rad_dw_sum"), ("k_rad_dh_sum", "rad_dh_sum"), ("k_lin_gemm", "linear_gemm(fwd+dx)"),
@@ -433,7 +451,7 @@ def _prof_hbm(root, sec, h):
 
 
 def _prof_util(root, sec, h):
-    mets = ["MfmaUtil", "VALUBusy", "LdsUtil", "SQ_INSTS_VALU_MFMA_MOPS_F32", "SQ_INSTS_VALU"]
+    mets = ["MfmaUtil", "VALUBusy", "LdsUtil", mops(sec), "SQ_INSTS_VALU"]
     d = {}
     for r in _prof_rows(root, f"util_{sec}/**/*counter_collection.csv"):
         k = _prof_short(r["Kernel_Name"])
@@ -445,7 +463,7 @@ def _prof_util(root, sec, h):
     for k in sorted(d, key=lambda k: -sum(d[k].get("SQ_INSTS_VALU", {0: 0}).values())):
         m = {n: sum(v.values()) / len(v) for n, v in d[k].items()}
         lines.append(f"{k:<24s} {m.get('MfmaUtil', 0):8.2f} {m.get('VALUBusy', 0):7.2f} {m.get('LdsUtil', 0):7.2f} "
-                     f"{m.get('SQ_INSTS_VALU_MFMA_MOPS_F32', 0):14.0f} {m.get('SQ_INSTS_VALU', 0):14.0f}")
+                     f"{m.get(mops(sec), 0):14.0f} {m.get('SQ_INSTS_VALU', 0):14.0f}")
         for n in ("MfmaUtil", "VALUBusy", "LdsUtil"):
             lines.append(f"util {k} {n} {h} {m.get(n, 0):.2f}")
     return lines
@@ -458,8 +476,8 @@ def summarize_profiles(root, only=None):
     for fname, kind, secs, title in PROF_FILES:
         if only and fname not in only:
             continue
-        if kind == "trace":
-            cmds = [PROF_TRACE.format(s=s) for s in secs]
+        if kind in ("trace", "cases"):
+            cmds = [(PROF_TRACE if kind == "trace" else PROF_CASES).format(s=s) for s in secs]
             body = ["# columns: kernel | calls | avg ms | min ms | max ms | share of the run's GPU time"]
             for sec in secs:
                 body += _prof_trace(root, sec)
@@ -469,9 +487,10 @@ def summarize_profiles(root, only=None):
             for sec in secs:
                 body += _prof_hbm(root, sec, h)
         else:
-            cmds = [PROF_UTIL.format(s=s) for s in secs]
-            body = ["# MfmaUtil, VALUBusy, LdsUtil in percent of the kernel's duration; MOPS_F32 in units of "
-                    "512 flop", "# kernel | MfmaUtil | VALUBusy | LdsUtil | SQ_INSTS_VALU_MFMA_MOPS_F32 | "
+            cmds = [PROF_UTIL.format(s=s, m=mops(s)) for s in secs]
+            body = ["# MfmaUtil, VALUBusy, LdsUtil in percent of the kernel's duration; MOPS (F32, section linear: "
+                    "BF16) in units of 512 flop",
+                    "# kernel | MfmaUtil | VALUBusy | LdsUtil | SQ_INSTS_VALU_MFMA_MOPS | "
                     "SQ_INSTS_VALU"]
             for sec in secs:
                 body += _prof_util(root, sec, h)
@@ -1071,7 +1090,7 @@ def main():
                     lk[name]["TFLOPs"] = round(flops / (ms * 1e-3) / 1e12, 2)
                     lk[name]["frac_split_peak"] = round(flops / (ms * 1e-3) / 1e12 / LIN_PEAK_TFLOPS, 4)
         out["linear"] = {"workload": f"equivariant mixing of the convolution output, {N} nodes: 34 path blocks "
-                                     f"(D {L.D_in}) -> 8 irreps (D {L.D_out}), {C} -> {C} channels, fp32 as six "
+                                     f"(D {L.D_in}) -> 8 irreps (D {L.D_out}), {C} -> {C} channels, fp32 as eight "
                                      "bf16 term products",
                          "gflop_per_pass": round(flops / 1e9, 2),
                          "bound": "mfma", "peak_TFLOPs": round(LIN_PEAK_TFLOPS, 1), "kernels": lk}
